@@ -61,7 +61,7 @@ enum l1csr_status {
 
 /* dense_wgrad operand precision */
 enum l1csr_precision {
-    L1CSR_F32 = 0,           /* fp32 operands, fp32 matrix cores: the 1e-4 contract */
+    L1CSR_F32 = 0,           /* fp32 operands at full precision: the 1e-4 contract */
     L1CSR_BF16 = 1,          /* operands rounded to bf16 (nearest even), exact products, fp32 sums */
     L1CSR_BF16X3 = 2         /* operands split into bf16 hi + lo, three exact products, fp32 sums */
 };
@@ -88,7 +88,8 @@ enum l1csr_op {
     L1CSR_OP_SOFTMAX_XENT = 6,
     L1CSR_OP_PROX_RECOMPRESS = 7,
     L1CSR_OP_DENSE_WGRAD = 8,
-    L1CSR_OP_WGRAD_PROX = 9    /* dense_wgrad_prox, fp32 (other precisions need none) */
+    L1CSR_OP_WGRAD_PROX = 9,   /* dense_wgrad_prox, fp32 (other precisions need none) */
+    L1CSR_OP_WGRAD_PACKED = 10 /* dense_wgrad / dense_wgrad_prox with packed operands (nnz unused) */
 };
 
 /* Human-readable name of a status code (static string, never NULL). */
@@ -231,6 +232,13 @@ int csr_spmm_bwd_t(int32_t n_rows, int32_t n_cols, int64_t nnz,
  * (conv filter banks over batch x positions) split its reduction into ranges
  * whose partial sums are added in a fixed order afterwards; the size is 0
  * when no split is planned.  Results are reproducible either way.
+ * With l1csr_workspace_bytes(L1CSR_OP_WGRAD_PACKED, N, K, 0, B) bytes (0: not
+ * taken at these sizes) F32 and BF16X3 products pack their operands into ws
+ * first, split into bf16 parts: F32 into three that hold all 24 significand
+ * bits, six exact products per pair (those left out are at most 2^-23 of it)
+ * and fp32 sums, so the result is as close to the exact one as the fp32
+ * instruction's.  Operands whose parts would over- or underflow (NaN,
+ * infinities, beyond 2^60, rows all below 2^-100) take the fp32 instruction.
  */
 int dense_wgrad(int32_t N, int32_t K, int32_t B,
                 const float *dY, int64_t ldy, const float *X, int64_t ldx,
@@ -330,7 +338,9 @@ int prox_l1_recompress(int32_t n_rows, int32_t n_cols, int64_t nnz,
  * [N][ceil(K/32)] (written); the outputs must be disjoint from each other
  * and from every input (L1CSR_EINVAL).  ws as
  * l1csr_workspace_bytes(L1CSR_OP_WGRAD_PROX, N, K, nnz, B) for fp32 (0 unless
- * the product splits its reduction: few output tiles, a long batch).
+ * the product splits its reduction: few output tiles, a long batch); with
+ * l1csr_workspace_bytes(L1CSR_OP_WGRAD_PACKED, N, K, 0, B) bytes the operands
+ * are packed as dense_wgrad does.
  */
 int dense_wgrad_prox(int32_t N, int32_t K, int32_t B,
                      const float *dY, int64_t ldy, const float *X, int64_t ldx, int precision,

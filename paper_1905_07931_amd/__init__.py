@@ -10,6 +10,7 @@ library's HIP kernels; there is no CPU fallback.
 from __future__ import annotations
 
 import ctypes as C
+import functools
 import os
 from dataclasses import dataclass
 
@@ -36,6 +37,7 @@ OP_CSC_BUILD, OP_RECOMPRESS, OP_SDDMM, OP_SPMM, OP_COMPACT, OP_SOFTMAX_XENT = 1,
 OP_PROX_RECOMPRESS = 7
 OP_DENSE_WGRAD = 8
 OP_WGRAD_PROX = 9
+OP_WGRAD_PACKED = 10
 
 
 class L1CSRError(RuntimeError):
@@ -119,6 +121,7 @@ def status_str(status: int) -> str:
     return lib().l1csr_status_str(int(status)).decode()
 
 
+@functools.lru_cache(maxsize=4096)  # a pure function of the sizes
 def workspace_bytes(op: int, n_rows: int, n_cols: int, nnz: int, B: int) -> int:
     return int(lib().l1csr_workspace_bytes(op, n_rows, n_cols, nnz, B))
 
@@ -548,7 +551,8 @@ def dense_wgrad(dY, X, dW=None, precision=F32, stream=None):
     Nw, Kw, ldw = _mat(dW, "dW")
     if (Nw, Kw) != (N, K):
         raise ValueError("dW must be [N][K]")
-    ws, wsb = _workspace(workspace_bytes(OP_DENSE_WGRAD, N, K, 0, B), dY.device, stream)
+    ws, wsb = _workspace(max(workspace_bytes(OP_DENSE_WGRAD, N, K, 0, B),
+                             0 if precision == BF16 else workspace_bytes(OP_WGRAD_PACKED, N, K, 0, B)), dY.device, stream)
     _check(lib().dense_wgrad(N, K, B, _p(dY), ldy, _p(X), ldx, _p(dW), ldw, int(precision), _p(ws), wsb,
                              _stream(stream)), "dense_wgrad")
     return dW
@@ -676,8 +680,9 @@ def dense_wgrad_prox(W: CSR, dY, X, eta, lam, bitmap: Bitmap, Z=None, word_count
     if not word_counts.is_contiguous() or word_counts.numel() < N * kw:
         raise ValueError("word_counts must be contiguous with N * ceil(K/32) entries")
     ws, wsb = (None, 0)
-    if precision == F32:
-        ws, wsb = _workspace(workspace_bytes(OP_WGRAD_PROX, N, K, nnz, B), dev, stream)
+    if precision != BF16:
+        ws, wsb = _workspace(max(workspace_bytes(OP_WGRAD_PROX, N, K, nnz, B),
+                                 workspace_bytes(OP_WGRAD_PACKED, N, K, 0, B)), dev, stream)
     _check(lib().dense_wgrad_prox(N, K, B, _p(dY), ldy, _p(X), ldx, int(precision), nnz, _p(W.row_ptr),
                                   _p(W.col_idx), _p(W.vals), _p(bitmap.mask), _p(bitmap.pos), float(eta), float(lam),
                                   _p(Z), ldz, _p(word_counts), _p(ws), wsb, _stream(stream)), "dense_wgrad_prox")

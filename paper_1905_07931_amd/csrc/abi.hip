@@ -270,6 +270,11 @@ size_t l1csr_workspace_bytes(int op, int32_t n_rows, int32_t n_cols, int64_t nnz
         case L1CSR_OP_PROX_RECOMPRESS: return round_up(prox_recompress_workspace_bytes(n_rows, n_cols));
         case L1CSR_OP_DENSE_WGRAD: return round_up(wgrad_workspace_bytes(n_rows, n_cols, B));
         case L1CSR_OP_WGRAD_PROX: return round_up(wgrad_prox_split_bytes(n_rows, n_cols, B, L1CSR_F32));
+        case L1CSR_OP_WGRAD_PACKED: {  // room for either precision that packs its operands
+            const size_t f = split_wgrad_bytes(n_rows, n_cols, B, L1CSR_F32),
+                         x3 = split_wgrad_bytes(n_rows, n_cols, B, L1CSR_BF16X3);
+            return round_up(f > x3 ? f : x3);
+        }
         case L1CSR_OP_SOFTMAX_XENT: return round_up(sizeof(float) * (size_t)(ceil_div(B, 256) + 1));
         default: return 0;
     }
@@ -370,6 +375,9 @@ int dense_wgrad(int32_t N, int32_t K, int32_t B, const float *dY, int64_t ldy, c
     if (ceil_div(N, 128) > kMaxGridY) return L1CSR_EUNSUPPORTED;
     if (precision == L1CSR_BF16)
         return hip_status(launch_wgrad_bf16(N, K, B, dY, ldy, X, ldx, dW, ldw, stream));
+    const size_t packed = split_wgrad_bytes(N, K, B, precision);
+    if (packed > 0 && ws != nullptr && ws_bytes >= packed)
+        return hip_status(launch_split_wgrad(N, K, B, precision, dY, ldy, X, ldx, dW, ldw, ws, stream));
     if (precision == L1CSR_BF16X3)
         return hip_status(launch_wgrad_bf16x3(N, K, B, dY, ldy, X, ldx, dW, ldw, stream));
     return hip_status(launch_wgrad_f32(N, K, B, dY, ldy, X, ldx, dW, ldw, ws, stream));
@@ -509,7 +517,7 @@ int dense_wgrad_prox(int32_t N, int32_t K, int32_t B, const float *dY, int64_t l
     const double t = (double)eta * (double)lambda;  // exact in double
     return hip_status(launch_wgrad_prox(N, K, B, dY, ldy, X, ldx, precision, vals,
                                         reinterpret_cast<const unsigned *>(mask), pos, eta, t, Z, ldz, word_counts,
-                                        split > 0 ? ws : nullptr, stream));
+                                        ws, ws_bytes, stream));
 }
 
 int csr_recompress_counted(int32_t n_rows, int32_t n_cols, const float *Z, int64_t ldz,

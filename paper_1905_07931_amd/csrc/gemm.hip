@@ -563,6 +563,13 @@ size_t wgrad_workspace_bytes(int N, int K, int B) {
     return p.splits > 1 ? sizeof(float) * (size_t)p.splits * N * K : 0;
 }
 
+hipError_t launch_wgrad_reduce(int N, int K, int splits, const float *parts, float *dW, int64_t ldw, hipStream_t s) {
+    const int64_t n = (int64_t)N * K;
+    const unsigned rgrid = (unsigned)(ceil_div(n, 256) < 4096 ? ceil_div(n, 256) : 4096);
+    wgrad_reduce_kernel<<<rgrid, 256, 0, s>>>(N, K, splits, parts, dW, ldw);
+    return hipGetLastError();
+}
+
 hipError_t launch_wgrad_f32(int N, int K, int B, const float *dY, int64_t ldy, const float *X,
                             int64_t ldx, float *dW, int64_t ldw, void *ws, hipStream_t s) {
     if (N == 0 || K == 0) return hipSuccess;
@@ -577,10 +584,7 @@ hipError_t launch_wgrad_f32(int N, int K, int B, const float *dY, int64_t ldy, c
             wgrad_split_kernel<false><<<grid, kThreads, 0, s>>>(N, K, B, p.chunk, dY, ldy, X, ldx, P);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
-        const int64_t n = (int64_t)N * K;
-        const unsigned rgrid = (unsigned)(ceil_div(n, 256) < 4096 ? ceil_div(n, 256) : 4096);
-        wgrad_reduce_kernel<<<rgrid, 256, 0, s>>>(N, K, p.splits, P, dW, ldw);
-        return hipGetLastError();
+        return launch_wgrad_reduce(N, K, p.splits, P, dW, ldw, s);
     }
     return launch_f32_tiles<false>(N, K, B, dY, ldy, X, ldx, dW, ldw, v4, prox_epi{}, s);
 }

@@ -80,6 +80,19 @@ int wgrad_f32_prox_slab(int N, int K, int B);
 int wgrad_bf16x3_prox_slab(int N, int K, int B);
 // dense_wgrad precision codes (the ABI's l1csr_precision)
 constexpr int kPrecF32 = 0, kPrecBF16 = 1, kPrecBF16X3 = 2;
+// dW = parts[0] + parts[1] + ... (N x K each), in that order
+hipError_t launch_wgrad_reduce(int N, int K, int splits, const float *parts, float *dW, int64_t ldw, hipStream_t s);
+// split_gemm.hip: dW (or Z) with the operands packed as bf16 parts into ws
+// (split_wgrad_bytes(); 0 where that path is not taken), three parts for F32
+// (fp32 accuracy), two for BF16X3
+size_t split_wgrad_bytes(int N, int K, int B, int precision);
+// launch_split_wgrad_prox() runs the prox in the product's epilogue (else the
+// reduction is split: dW into Z, then the prox in place)
+bool split_wgrad_prox_fused(int N, int K, int B);
+hipError_t launch_split_wgrad(int N, int K, int B, int precision, const float *dY, int64_t ldy, const float *X,
+                              int64_t ldx, float *dW, int64_t ldw, void *ws, hipStream_t s);
+hipError_t launch_split_wgrad_prox(int N, int K, int B, int precision, const float *dY, int64_t ldy, const float *X,
+                                   int64_t ldx, float *Z, int64_t ldz, const prox_epi &P, void *ws, hipStream_t s);
 // Z = S_t(W - eta * dY.X^T) and P.counts, in one GEMM launch
 hipError_t launch_wgrad_f32_prox(int N, int K, int B, const float *dY, int64_t ldy, const float *X,
                                  int64_t ldx, float *Z, int64_t ldz, const prox_epi &P, hipStream_t s);
@@ -87,8 +100,9 @@ hipError_t launch_wgrad_bf16x3_prox(int N, int K, int B, const float *dY, int64_
                                     int64_t ldx, float *Z, int64_t ldz, const prox_epi &P, hipStream_t s);
 // the l1 update in two calls (wgrad_prox.hip):
 //   launch_wgrad_prox: Z and the per-(row, 32-column word) nonzero counts
-//     (counts [N][ceil(K / 32)]) from W's bitmap index (mask / pos); split_ws
-//     holds wgrad_prox_split_bytes() (fp32 products that split their batch);
+//     (counts [N][ceil(K / 32)]) from W's bitmap index (mask / pos); ws
+//     (nullable, ws_bytes) holds the packed operands (split_wgrad_bytes()) or
+//     at least wgrad_prox_split_bytes() (fp32 products that split their batch);
 //   launch_counted_sums: the row totals of the counts and their totals per
 //     block of 16-64 rows into ws (counted_ws_ints(N) ints);
 //   launch_counted_row_ptr: row_ptr_out (row_ptr_out[N] = nnz') by a scan of
@@ -101,8 +115,8 @@ size_t word_counts_bytes(int N, int K);
 size_t wgrad_prox_split_bytes(int N, int K, int B, int precision);
 hipError_t launch_wgrad_prox(int N, int K, int B, const float *dY, int64_t ldy, const float *X,
                              int64_t ldx, int precision, const float *vals, const unsigned *mask, const int *pos,
-                             float eta, double t, float *Z, int64_t ldz, int *counts, void *split_ws,
-                             hipStream_t s);
+                             float eta, double t, float *Z, int64_t ldz, int *counts, void *ws,
+                             size_t ws_bytes, hipStream_t s);
 size_t counted_ws_ints(int N);
 bool counted_prefix_in_compact(int N);
 hipError_t launch_counted_sums(int N, int K, const int *counts, int *ws, hipStream_t s);

@@ -1,0 +1,463 @@
+// C[M][Nn] = A[M][Kr] . B[Nn][Kr]^T in fp32 accuracy on the bf16 matrix cores
+// (v_mfma_f32_32x32x16_bf16): every fp32 operand is split into bf16 parts,
+// packed once per call in the order the matrix cores read them.
+//
+// Parts.  Three (hi, mid, lo): hi = bf16(x), mid = bf16(x - hi), lo = bf16(x -
+// hi - mid), each to nearest even; 3 x 8 significand bits hold the 24 of x, so
+// hi + mid + lo = x.  A product takes the six terms down to 2^-16 of it (hi hi,
+// mid hi, hi mid, mid mid, lo hi, hi lo); each is exact in fp32 and summed in
+// fp32.  What is left out (mid lo, lo mid, lo lo) is at most 2^-23 of |a b|, of
+// random sign.  16 products are summed per instruction instead of 2, so there
+// are fewer roundings than in the fp32 instruction's sum: at 4096 x 9216 x
+// 1024 the result is 4.9e-7 off the 64-bit one (2-norm), 5.7e-7 with
+// v_mfma_f32_32x32x2_f32.  The bf16 pipe is 16x the fp32 one, so six products
+// have 2.7x its peak.  Two parts (hi, lo) with three terms are the BF16X3
+// arithmetic (2^-16 left out).
+//
+// The exactness of the parts holds for |x| in [2^-100, 2^60] (no part under- or
+// overflows) and for zeros.  The pack kernel flags every (32-row group,
+// 256-index block) that holds a NaN, an infinity, an |x| above 2^60 or a row
+// whose values there are all below 2^-100; tiles that touch a flagged group
+// run the fp32 matrix-core instruction on the operands themselves.
+//
+// What bounds it: the matrix pipe, and through it the power limit.  With every
+// CU's matrix pipe 71 % busy the shader clock falls to 1.64 GHz (2.38 GHz under
+// the fp32 instruction), 1.2-1.27 PFLOP/s of bf16 at 4096 x 9216 x 1024, where
+// a large bf16 library product reaches 1.12.
+#include <cmath>
+
+#include "common.hpp"
+#include "launch.hpp"
+#include "prox_epilogue.hpp"
+
+namespace l1csr {
+
+namespace {
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __attribute__((address_space(3))) void sg_lds_void;
+
+constexpr int kGroup = 32;         // rows of a packed group
+constexpr int kStep = 16;          // reduction indices of a packed block
+constexpr int kBlockBytes = 1024;  // one part of a (group, step): 64 lanes x 16 bytes
+constexpr int kPackK = 256;        // reduction indices of a pack workgroup (one flag)
+constexpr float kPartMax = 0x1p60f, kPartMin = 0x1p-100f;
+
+// A packed operand: [group][step][part][lane][8] bf16.  Lane l of a block holds
+// row l % 32 of the group and reduction indices 8 (l / 32) .. + 7 of the step,
+// the operand fragment of one MFMA: the copy into LDS and the fragment reads
+// are both linear in the lane (whole cache lines, no bank conflicts, no
+// swizzle).  Rows and indices past the matrix are zeros.
+struct packed {
+    char *data;
+    int *flags;  // [group][kPackK block]: not exact in parts
+    int groups, steps, kblocks;
+};
+
+int64_t packed_bytes(int rows, int kr, int np) {
+    return ceil_div(rows, kGroup) * ceil_div(kr, kStep) * (int64_t)(np * kBlockBytes);
+}
+int64_t flag_bytes(int rows, int kr) {
+    return ceil_div(ceil_div(rows, kGroup) * ceil_div(kr, kPackK) * (int64_t)sizeof(int), 256) * 256;
+}
+// carves rows x kr out of p (advanced past it)
+packed carve_packed(char *&p, int rows, int kr, int np) {
+    packed o;
+    o.groups = (int)ceil_div(rows, kGroup);
+    o.steps = (int)ceil_div(kr, kStep);
+    o.kblocks = (int)ceil_div(kr, kPackK);
+    o.data = p;
+    p += packed_bytes(rows, kr, np);
+    o.flags = reinterpret_cast<int *>(p);
+    p += flag_bytes(rows, kr);
+    return o;
+}
+
+template <int NP>
+__device__ __forceinline__ void split8(const float (&x)[8], bf16x8 (&p)[NP]) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        float r = x[e];
+#pragma unroll
+        for (int q = 0; q < NP; ++q) {
+            const __bf16 h = (__bf16)r;
+            p[q][e] = h;
+            r -= (float)h;
+        }
+    }
+}
+
+// one operand of a pack launch: rows of a row-major fp32 matrix, the reduction
+// index contiguous (v4: 16-byte aligned rows)
+struct pack_src {
+    const float *p;
+    int64_t ld;
+    int rows, v4;
+    packed out;
+};
+
+// Both operands of a product in one launch.  A workgroup takes one 32-row group
+// and 256 reduction indices; a wave a step of 16 at a time: lane l reads the 8
+// floats of its row and half and writes its 16 bytes of each part, 1 KB a store.
+// Memory-bound: 4 bytes read and 2 NP written per element, 22.5 us for 54.5 MB
+// in and 82 MB out (6.0 TB/s) with three parts at 4096 + 9216 rows of 1024.
+template <int NP>
+__global__ __launch_bounds__(256) void pack_rows_kernel(pack_src s0, pack_src s1, int kr) {
+    __shared__ unsigned rowmax[kGroup];
+    const bool first = (int)blockIdx.x < s0.out.groups;
+    const pack_src s = first ? s0 : s1;
+    const int g = first ? blockIdx.x : blockIdx.x - s0.out.groups;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    if (threadIdx.x < kGroup) rowmax[threadIdx.x] = 0u;
+    __syncthreads();
+    const int row = g * kGroup + (lane & 31);
+    const float *src = s.p + (int64_t)row * s.ld;
+    unsigned mx = 0u;  // magnitudes as ordered integers; NaN above infinity
+#pragma unroll
+    for (int i = 0; i < kPackK / kStep / 4; ++i) {
+        const int st = blockIdx.y * (kPackK / kStep) + i * 4 + wave;
+        if (st >= s.out.steps) break;
+        const int k = st * kStep + (lane >> 5) * 8;
+        float x[8];
+        if (s.v4 && row < s.rows && k + 7 < kr) {
+            const float4 a = *reinterpret_cast<const float4 *>(src + k);
+            const float4 b = *reinterpret_cast<const float4 *>(src + k + 4);
+            x[0] = a.x; x[1] = a.y; x[2] = a.z; x[3] = a.w;
+            x[4] = b.x; x[5] = b.y; x[6] = b.z; x[7] = b.w;
+        } else {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) x[e] = row < s.rows && k + e < kr ? src[k + e] : 0.f;
+        }
+#pragma unroll
+        for (int e = 0; e < 8; ++e) mx = max(mx, __float_as_uint(x[e]) & 0x7fffffffu);
+        bf16x8 p[NP];
+        split8<NP>(x, p);
+        char *d = s.out.data + ((int64_t)g * s.out.steps + st) * (NP * kBlockBytes) + lane * 16;
+#pragma unroll
+        for (int q = 0; q < NP; ++q) *reinterpret_cast<bf16x8 *>(d + q * kBlockBytes) = p[q];
+    }
+    atomicMax(&rowmax[lane & 31], mx);
+    __syncthreads();
+    if (wave == 0) {
+        const unsigned m = rowmax[lane & 31];
+        const bool odd = m > __float_as_uint(kPartMax) || (m != 0u && m < __float_as_uint(kPartMin));
+        const uint64_t any = __ballot(odd);
+        if (lane == 0) s.out.flags[g * s.out.kblocks + blockIdx.y] = any != 0ull;
+    }
+}
+
+__device__ __forceinline__ floatx16 mfma16(bf16x8 a, bf16x8 b, floatx16 c) {
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
+}
+
+// One 1 KB block global -> LDS (16 bytes per lane), base and lds wave-uniform.
+// As an instruction of its own rather than the builtin: the compiler orders the
+// builtin's loads against the reads of the other buffers and waited for the
+// loads just issued (vmcnt(0)) in one step of three.  It writes no register;
+// wait_vm() below counts it.
+__device__ __forceinline__ void dma16(const char *base, unsigned off, unsigned lds) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(base)
+                 : "memory", "m0");
+}
+
+template <int N>
+__device__ __forceinline__ void wait_vm() {  // at most N vector memory operations and no LDS access outstanding
+    static_assert(N < 16, "low field only");
+    __builtin_amdgcn_s_waitcnt(0x0070 | N);
+}
+
+// The tile: 128 x 128, 2 x 2 waves of 64 x 64 (2 x 2 MFMA tiles each), a step of
+// 16 reduction indices a time.  A step is 4 + 4 groups of NP blocks (24 KB with
+// three parts), three steps in LDS (72 KB): two workgroups share a CU, so one's
+// epilogue runs under the other's products.  Per step a wave reads 4 NP
+// fragments for 24 (NP = 2: 12) MFMAs.  Larger tiles and waves (256 x 288 with
+// 12 waves, 256 x 256 with 8 or 16, 128 x 256, 128 x 128 of two waves) measured
+// 400-450 us at 4096 x 9216 x 1024 against 365-377 us: the pipe is held by
+// power, not by LDS reads, and the smaller tile wastes least at the edges.
+constexpr int TM = 2, TN = 2, WM = 2, WN = 2;
+constexpr int BM = 32 * TM * WM, BN = 32 * TN * WN, NT = 64 * WM * WN;
+constexpr int RGA = TM * WM, RGB = TN * WN;  // groups of a tile
+
+enum { kEpiStore = 0, kEpiProx = 1 };
+
+struct gemm_args {
+    int M, Nn, Kr;                // sizes (Kr: all reduction indices)
+    packed A, B;
+    const float *a32, *b32;       // the operands themselves, for flagged groups
+    int64_t lda, ldb;
+    int tiles_m, tiles_n;
+    int split_steps;              // steps per split (blockIdx.y); the splits' C are M * ldc apart
+    float *C;
+    int64_t ldc;
+    prox_epi P;
+};
+
+template <int NP, int EPI>
+__global__ __launch_bounds__(NT, 2) void split_gemm_kernel(gemm_args G) {
+    constexpr int PIECES = (RGA + RGB) * NP;     // 1 KB blocks of a step
+    constexpr int LPW = PIECES / (NT / kWave);   // loads per wave and step
+    static_assert(PIECES % (NT / kWave) == 0, "every wave issues the same number of loads");
+    constexpr int SB = PIECES * kBlockBytes;
+    __shared__ __attribute__((aligned(16))) char S0[SB];
+    __shared__ __attribute__((aligned(16))) char S1[SB];
+    __shared__ __attribute__((aligned(16))) char S2[SB];
+    // tile order: bands of 8 tile rows walked column by column; each XCD
+    // (blocks are dealt round-robin) takes one contiguous range of it, so the
+    // tiles it runs at one time share operand rows in its L2
+    int tm, tn;
+    {
+        const int T = G.tiles_m * G.tiles_n, per = (T + 7) / 8;
+        const int t = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
+        if ((int)(blockIdx.x >> 3) >= per || t >= T) return;
+        const int band = t / (8 * G.tiles_n), r = t - band * 8 * G.tiles_n;
+        const int h = min(8, G.tiles_m - band * 8);
+        tn = r / h;
+        tm = band * 8 + (r - tn * h);
+    }
+    const int m0 = tm * BM, n0 = tn * BN;
+    const int wave = uniform(threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
+    const int wgm = (wave / WN) * TM, wgn = (wave % WN) * TN;  // the wave's first group of A / B in the tile
+    const int c0 = blockIdx.y * G.split_steps;
+    const int steps = min(G.split_steps, G.A.steps - c0);      // >= 1, or 0 if Kr == 0
+
+    // this wave's blocks of a step: piece p = wave + j * waves
+    const char *src[LPW];
+#pragma unroll
+    for (int j = 0; j < LPW; ++j) {
+        const int p = wave + j * (NT / kWave);
+        const int g = p / NP, q = p - g * NP;
+        const int64_t gs = (int64_t)G.A.steps * (NP * kBlockBytes);
+        // groups past the operand: never stored, any data will do
+        src[j] = (g < RGA ? G.A.data + min(tm * RGA + g, G.A.groups - 1) * gs
+                          : G.B.data + min(tn * RGB + (g - RGA), G.B.groups - 1) * gs) +
+                 (int64_t)c0 * (NP * kBlockBytes) + q * kBlockBytes;
+    }
+    const unsigned l0 = (unsigned)(uintptr_t)(sg_lds_void *)S0 + wave * kBlockBytes;
+    const unsigned l1 = (unsigned)(uintptr_t)(sg_lds_void *)S1 + wave * kBlockBytes;
+    const unsigned l2 = (unsigned)(uintptr_t)(sg_lds_void *)S2 + wave * kBlockBytes;
+    auto load = [&](unsigned dst, int c) {
+        const unsigned off = (unsigned)c * (NP * kBlockBytes) + lane * 16;
+#pragma unroll
+        for (int j = 0; j < LPW; ++j) dma16(src[j], off, dst + j * (NT / kWave) * kBlockBytes);
+    };
+    // flagged groups of the tile (the same answer in every wave)
+    bool odd = false;
+    {
+        const int kb0 = c0 / (kPackK / kStep), kb1 = (c0 + steps + kPackK / kStep - 1) / (kPackK / kStep);
+        for (int kb = kb0 + (lane >> 3); kb < kb1; kb += 8) {
+            const int g = lane & 7;
+            const int *f = g < RGA ? G.A.flags + (int64_t)min(tm * RGA + g, G.A.groups - 1) * G.A.kblocks
+                                   : G.B.flags + (int64_t)min(tn * RGB + g - RGA, G.B.groups - 1) * G.B.kblocks;
+            odd |= f[kb] != 0;
+        }
+        odd = __ballot(odd) != 0ull;
+    }
+    static_assert(RGA + RGB == 8, "one lane per group");
+
+    floatx16 acc[TM][TN];
+#pragma unroll
+    for (int a = 0; a < TM; ++a)
+#pragma unroll
+        for (int b = 0; b < TN; ++b)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.f;
+
+    const int lr = lane & 31, lh = lane >> 5;
+    if (!odd) {
+        const int oa = wgm * (NP * kBlockBytes) + lane * 16;
+        const int ob = (RGA + wgn) * (NP * kBlockBytes) + lane * 16;
+        auto compute = [&](const char *cur) {
+            bf16x8 af[NP][TM], bf[NP][TN];
+#pragma unroll
+            for (int q = 0; q < NP; ++q) {
+#pragma unroll
+                for (int a = 0; a < TM; ++a)
+                    af[q][a] = *reinterpret_cast<const bf16x8 *>(cur + oa + (a * NP + q) * kBlockBytes);
+#pragma unroll
+                for (int b = 0; b < TN; ++b)
+                    bf[q][b] = *reinterpret_cast<const bf16x8 *>(cur + ob + (b * NP + q) * kBlockBytes);
+            }
+            auto term = [&](int qa, int qb) {
+#pragma unroll
+                for (int a = 0; a < TM; ++a)
+#pragma unroll
+                    for (int b = 0; b < TN; ++b) acc[a][b] = mfma16(af[qa][a], bf[qb][b], acc[a][b]);
+            };
+            if constexpr (NP == 2) {
+                // the two small terms first, then hi . hi
+                term(1, 0);
+                term(0, 1);
+                term(0, 0);
+            } else {
+                // in the order the fragments arrive
+                term(0, 0);
+                term(1, 0);
+                term(0, 1);
+                term(1, 1);
+                term(2, 0);
+                term(0, 2);
+            }
+        };
+        // step c: its blocks have landed everywhere (the loads of step c + 1 may
+        // still be out), and the buffer that the loads of step c + 2 fill was
+        // last read in step c - 1, whose reads every wave has finished here
+        auto step = [&](int c, const char *cur, unsigned nxt2) {
+            if (c + 1 < steps)
+                wait_vm<LPW>();
+            else
+                wait_vm<0>();
+            asm volatile("" ::: "memory");
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+            if (c + 2 < steps) load(nxt2, c + 2);
+            compute(cur);
+        };
+        if (steps > 0) load(l0, 0);
+        if (steps > 1) load(l1, 1);
+        for (int c = 0; c < steps; c += 3) {
+            step(c, S0, l2);
+            if (c + 1 < steps) step(c + 1, S1, l0);
+            if (c + 2 < steps) step(c + 2, S2, l1);
+        }
+    } else {
+        // not exact in parts: the fp32 instruction, lane half h of a pair of indices
+        const int k0 = c0 * kStep, k1 = min(G.Kr, (c0 + steps) * kStep);
+        for (int k = k0; k < k1; k += 2) {
+            const int kk = k + lh;
+            float av[TM], bv[TN];
+#pragma unroll
+            for (int a = 0; a < TM; ++a) {
+                const int row = m0 + (wgm + a) * 32 + lr;
+                av[a] = row < G.M && kk < k1 ? G.a32[row * G.lda + kk] : 0.f;
+            }
+#pragma unroll
+            for (int b = 0; b < TN; ++b) {
+                const int row = n0 + (wgn + b) * 32 + lr;
+                bv[b] = row < G.Nn && kk < k1 ? G.b32[row * G.ldb + kk] : 0.f;
+            }
+#pragma unroll
+            for (int a = 0; a < TM; ++a)
+#pragma unroll
+                for (int b = 0; b < TN; ++b)
+                    acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[a], bv[b], acc[a][b], 0, 0, 0);
+        }
+    }
+    if constexpr (EPI == kEpiProx) {
+        __syncthreads();  // every wave has read its last fragments: the buffers are free
+        // the staged index words, then two gather buffers of one MFMA tile (8 KB) per wave
+        constexpr int GBF = 2 * 16 * kWave;  // floats per wave
+        constexpr int kStageBytes = 8 * BM * (BN / 32);
+        constexpr int W0 = (SB - kStageBytes) / (4 * GBF), W1 = SB / (4 * GBF);
+        static_assert(W0 >= 1 && W0 + 2 * W1 >= NT / kWave, "gather space");
+        int2 *stage = reinterpret_cast<int2 *>(S0);
+        prox_stage<BM, BN, NT>(G.P, G.M, m0, n0, stage);
+        float *gbuf = wave < W0 ? reinterpret_cast<float *>(S0 + kStageBytes) + wave * GBF
+                                : (wave < W0 + W1 ? reinterpret_cast<float *>(S1) + (wave - W0) * GBF
+                                                  : reinterpret_cast<float *>(S2) + (wave - W0 - W1) * GBF);
+        prox_store<TN, BN, 1, 2>(acc, G.M, G.Nn, m0, n0, wgm * 32, wgn * 32, stage, gbuf, G.C, G.ldc, G.P);
+        return;
+    }
+    // D layout of the 32x32 MFMA: lane l, register r holds
+    // row 8*(r/4) + 4*(l/32) + r%4, column l%32 of the 32x32 tile.
+    float *C = G.C + (int64_t)blockIdx.y * G.M * G.ldc;
+#pragma unroll
+    for (int a = 0; a < TM; ++a)
+#pragma unroll
+        for (int b = 0; b < TN; ++b) {
+            const int col = n0 + (wgn + b) * 32 + lr;
+            if (col >= G.Nn) continue;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int row = m0 + (wgm + a) * 32 + 8 * (r >> 2) + 4 * lh + (r & 3);
+                if (row < G.M) C[(int64_t)row * G.ldc + col] = acc[a][b][r];
+            }
+        }
+}
+
+template <int NP>
+hipError_t launch_pack(const pack_src &a, const pack_src &b, int kr, hipStream_t s) {
+    dim3 grid((unsigned)(a.out.groups + b.out.groups), (unsigned)a.out.kblocks);
+    pack_rows_kernel<NP><<<grid, 256, 0, s>>>(a, b, kr);
+    return hipGetLastError();
+}
+
+template <int NP, int EPI>
+hipError_t launch_tiles(const gemm_args &G, int splits, hipStream_t s) {
+    dim3 grid((unsigned)(ceil_div((int64_t)G.tiles_m * G.tiles_n, 8) * 8), (unsigned)splits);
+    split_gemm_kernel<NP, EPI><<<grid, NT, 0, s>>>(G);
+    return hipGetLastError();
+}
+
+// dY . X^T with the operands packed into ws; a product of few tiles splits its
+// reduction by wgrad_plan() into partial results behind the packed operands,
+// which wgrad_reduce_kernel adds in order
+template <int NP, int EPI>
+hipError_t wgrad(int N, int K, int B, const float *dY, int64_t ldy, const float *X, int64_t ldx, float *C,
+                 int64_t ldc, const prox_epi &P, void *ws, hipStream_t s) {
+    char *p = static_cast<char *>(ws);
+    gemm_args G{};
+    G.A = carve_packed(p, N, B, NP);
+    G.B = carve_packed(p, K, B, NP);
+    hipError_t e = launch_pack<NP>(pack_src{dY, ldy, N, ldy % 4 == 0 && aligned16(dY), G.A},
+                                   pack_src{X, ldx, K, ldx % 4 == 0 && aligned16(X), G.B}, B, s);
+    if (e != hipSuccess) return e;
+    G.M = N; G.Nn = K; G.Kr = B;
+    G.a32 = dY; G.lda = ldy; G.b32 = X; G.ldb = ldx;
+    G.tiles_m = (int)ceil_div(N, BM); G.tiles_n = (int)ceil_div(K, BN);
+    G.split_steps = G.A.steps;
+    G.C = C; G.ldc = ldc; G.P = P;
+    const wgrad_split w = wgrad_plan(N, K, B);
+    if (w.splits == 1) return launch_tiles<NP, EPI>(G, 1, s);
+    float *parts = reinterpret_cast<float *>(p);
+    G.split_steps = w.chunk / kStep;
+    G.C = parts; G.ldc = K;
+    e = launch_tiles<NP, kEpiStore>(G, w.splits, s);
+    if (e != hipSuccess) return e;
+    return launch_wgrad_reduce(N, K, w.splits, parts, C, ldc, s);
+}
+
+}  // namespace
+
+// Where the split product is taken (times in us, fp32 tiles -> split product,
+// dense_wgrad).  The packing launch costs 5-6 us, so the batch has to be long
+// enough for the faster products to win it back.  F32: 2048 x 2048 x 64 12.1 ->
+// 17.1, 2000 x 300 x 128 15.1 -> 17.4, 300 x 784 x 256 24.5 -> 18.5, 4096 x 9216
+// x 128 103 -> 79 (with the prox epilogue 128 -> 115; x 64: 86 -> 93).  And
+// where an output is small against long operands, packing moves more than the
+// products save: 50 x 500 x 16384 42.8 -> 59.5, 128 x 1000 x 20000 74 -> 107, 100
+// x 1000 x 3000 33.3 -> 29.4, 300 x 9216 x 1024 114 -> 70.  BF16X3 (whose other
+// path does not split a reduction): 2048 x 2048 x 256 17.0 -> 19.6, 2049 x 3001 x
+// 333 47 -> 31, 4096 x 4096 x 512 67 -> 60, 50 x 500 x 16384 712 -> 50.
+size_t split_wgrad_bytes(int N, int K, int B, int precision) {
+    const bool f32 = precision == kPrecF32;
+    if ((!f32 && precision != kPrecBF16X3) || N == 0 || K == 0) return 0;
+    const double nk = (double)N * K, rows = (double)N + K;
+    if (f32) {
+        if (B < (nk >= 4e6 ? 96 : 160)) return 0;
+        if (nk < 200 * rows && rows * B > 4e6) return 0;
+    } else if (B < 320) {
+        return 0;
+    }
+    if (B > (1 << 22)) return 0;  // 32-bit offsets inside a group
+    const int np = f32 ? 3 : 2;
+    return (size_t)(packed_bytes(N, B, np) + flag_bytes(N, B) + packed_bytes(K, B, np) + flag_bytes(K, B)) +
+           wgrad_workspace_bytes(N, K, B);
+}
+
+bool split_wgrad_prox_fused(int N, int K, int B) { return wgrad_plan(N, K, B).splits == 1; }
+
+hipError_t launch_split_wgrad(int N, int K, int B, int precision, const float *dY, int64_t ldy, const float *X,
+                              int64_t ldx, float *dW, int64_t ldw, void *ws, hipStream_t s) {
+    return precision == kPrecF32
+               ? wgrad<3, kEpiStore>(N, K, B, dY, ldy, X, ldx, dW, ldw, prox_epi{}, ws, s)
+               : wgrad<2, kEpiStore>(N, K, B, dY, ldy, X, ldx, dW, ldw, prox_epi{}, ws, s);
+}
+
+hipError_t launch_split_wgrad_prox(int N, int K, int B, int precision, const float *dY, int64_t ldy, const float *X,
+                                   int64_t ldx, float *Z, int64_t ldz, const prox_epi &P, void *ws, hipStream_t s) {
+    return precision == kPrecF32 ? wgrad<3, kEpiProx>(N, K, B, dY, ldy, X, ldx, Z, ldz, P, ws, s)
+                                 : wgrad<2, kEpiProx>(N, K, B, dY, ldy, X, ldx, Z, ldz, P, ws, s);
+}
+
+}  // namespace l1csr

@@ -393,8 +393,8 @@ size_t wgrad_prox_split_bytes(int N, int K, int B, int precision) {
 
 hipError_t launch_wgrad_prox(int N, int K, int B, const float *dY, int64_t ldy, const float *X,
                              int64_t ldx, int precision, const float *vals, const unsigned *mask, const int *pos,
-                             float eta, double t, float *Z, int64_t ldz, int *counts, void *split_ws,
-                             hipStream_t s) {
+                             float eta, double t, float *Z, int64_t ldz, int *counts, void *ws,
+                             size_t ws_bytes, hipStream_t s) {
     if (N == 0 || K == 0) return hipSuccess;
     prox_epi P{};
     P.mask = mask;
@@ -404,13 +404,20 @@ hipError_t launch_wgrad_prox(int N, int K, int B, const float *dY, int64_t ldy, 
     P.t = t;
     P.kw = (int)ceil_div(K, 32);
     P.counts = counts;
-    if (precision == kPrecF32 && wgrad_f32_prox_slab(N, K, B) > 0)
+    const size_t packed = split_wgrad_bytes(N, K, B, precision);
+    const bool split = packed > 0 && ws != nullptr && ws_bytes >= packed;
+    if (split && split_wgrad_prox_fused(N, K, B))
+        return launch_split_wgrad_prox(N, K, B, precision, dY, ldy, X, ldx, Z, ldz, P, ws, s);
+    if (!split && precision == kPrecF32 && wgrad_f32_prox_slab(N, K, B) > 0)
         return launch_wgrad_f32_prox(N, K, B, dY, ldy, X, ldx, Z, ldz, P, s);
-    if (precision == kPrecBF16X3) return launch_wgrad_bf16x3_prox(N, K, B, dY, ldy, X, ldx, Z, ldz, P, s);
+    if (!split && precision == kPrecBF16X3)
+        return launch_wgrad_bf16x3_prox(N, K, B, dY, ldy, X, ldx, Z, ldz, P, s);
     // dW into Z, then the prox in place
     hipError_t e;
-    if (precision == kPrecF32)
-        e = launch_wgrad_f32(N, K, B, dY, ldy, X, ldx, Z, ldz, split_ws, s);
+    if (split)
+        e = launch_split_wgrad(N, K, B, precision, dY, ldy, X, ldx, Z, ldz, ws, s);
+    else if (precision == kPrecF32)
+        e = launch_wgrad_f32(N, K, B, dY, ldy, X, ldx, Z, ldz, ws, s);
     else
         e = launch_wgrad_bf16(N, K, B, dY, ldy, X, ldx, Z, ldz, s);
     if (e != hipSuccess) return e;

@@ -1,0 +1,108 @@
+"""GPU: the weight gradient from packed bf16 parts (dense_wgrad / dense_wgrad_prox
+with the packed workspace) against 64-bit references, at tile edges, ragged
+sizes, split reductions and operands outside the parts' range."""
+import numpy as np
+import pytest
+
+import paper_1905_07931_amd as L1
+from _helpers import bits_equal, h, t
+
+pytestmark = pytest.mark.gpu
+
+
+def operands(N, K, B, seed=0, pad=0):
+    rng = np.random.default_rng(seed)
+    dY = rng.standard_normal((N, B + pad)).astype(np.float32)
+    X = rng.random((K, B + pad)).astype(np.float32)
+    return dY, X
+
+
+def bound(B, prec):
+    """|error| / sum |a b|: the terms left out (2^-22 with three parts, 3 (1 + 2^-7) 2^-16 with
+    two) and an fp32 rounding per instruction and per product inside one."""
+    terms = 6 if prec == L1.F32 else 3
+    left_out = 2.0 ** -22 if prec == L1.F32 else 3 * (1 + 2.0 ** -7) * 2.0 ** -16
+    return left_out + (terms * (-(-B // 16)) + 16 + 64) * 2.0 ** -24
+
+
+# one tile exactly, one row / column / index past tiles and steps, less than a
+# tile, a partial last band of tile rows, split reductions (< 256 tiles, B >= 512)
+@pytest.mark.parametrize("N,K,B,pad", [(128, 128, 160, 0), (129, 257, 161, 0), (127, 1, 175, 3), (1, 300, 320, 0),
+                                       (1153, 2177, 333, 0), (2049, 2100, 97, 1), (300, 1000, 1024, 0),
+                                       (65, 129, 4097, 2), (1100, 1300, 777, 0)])
+@pytest.mark.parametrize("prec", [L1.F32, L1.BF16X3])
+def test_packed_wgrad(N, K, B, pad, prec):
+    dYh, Xh = operands(N, K, B, seed=N + K + B, pad=pad)
+    dY, X = t(dYh)[:, :B], t(Xh)[:, :B]
+    assert L1.workspace_bytes(L1.OP_WGRAD_PACKED, N, K, 0, B) > 0
+    got = h(L1.dense_wgrad(dY, X, precision=prec)).astype(np.float64)
+    a, x = dYh[:, :B].astype(np.float64), Xh[:, :B].astype(np.float64)
+    err = np.abs(got - a @ x.T)
+    assert (err <= bound(B, prec) * (np.abs(a) @ np.abs(x).T)).all()
+
+
+def test_packed_is_deterministic_and_needs_its_workspace():
+    N, K, B = 300, 1000, 1024
+    dY, X = (t(v) for v in operands(N, K, B))
+    assert bits_equal(h(L1.dense_wgrad(dY, X)), h(L1.dense_wgrad(dY, X)))
+    # a workspace of the older size is still taken: the fp32 tiles
+    import ctypes as C
+    import torch
+    need = L1.workspace_bytes(L1.OP_DENSE_WGRAD, N, K, 0, B)
+    ws = torch.empty(max(need, 1), dtype=torch.uint8, device="cuda")
+    dW = torch.empty((N, K), device="cuda")
+    rc = L1.lib().dense_wgrad(N, K, B, C.c_void_p(dY.data_ptr()), B, C.c_void_p(X.data_ptr()), B,
+                              C.c_void_p(dW.data_ptr()), K, L1.F32, C.c_void_p(ws.data_ptr()), need,
+                              C.c_void_p(torch.cuda.current_stream().cuda_stream))
+    assert rc == L1.OK
+    ref = h(dY).astype(np.float64) @ h(X).astype(np.float64).T
+    assert np.abs(h(dW) - ref).max() <= 1e-4 * np.abs(ref).max()
+
+
+@pytest.mark.parametrize("scale_a,scale_x", [(2.0 ** -95, 2.0 ** 20), (2.0 ** -112, 2.0 ** 40), (2.0 ** 75, 2.0 ** -40)])
+def test_packed_wgrad_scales(scale_a, scale_x):
+    # inside the parts' range, below it and above it: the error stays relative to the products
+    N, K, B = 200, 300, 320
+    dYh, Xh = operands(N, K, B, seed=3)
+    dYh *= np.float32(scale_a)
+    Xh *= np.float32(scale_x)
+    got = h(L1.dense_wgrad(t(dYh), t(Xh))).astype(np.float64)
+    a, x = dYh.astype(np.float64), Xh.astype(np.float64)
+    assert (np.abs(got - a @ x.T) <= (2.0 ** -22 + B * 2.0 ** -24) * (np.abs(a) @ np.abs(x).T)).all()
+
+
+@pytest.mark.parametrize("prec", [L1.F32, L1.BF16X3])
+def test_packed_wgrad_nonfinite(prec):
+    # infinities and NaN reach exactly the entries that multiply them
+    N, K, B = 260, 390, 322
+    dYh, Xh = operands(N, K, B, seed=5)
+    dYh[7, 11], dYh[200, 300], Xh[5, 3] = np.inf, -np.inf, np.nan
+    dYh[31, 40] = 3.4e38  # hi would round to infinity
+    Xh[9, 11] = 0.0       # inf * 0
+    got = h(L1.dense_wgrad(t(dYh), t(Xh), precision=prec))
+    with np.errstate(invalid="ignore", over="ignore"):
+        a, x = dYh.astype(np.float64), Xh.astype(np.float64)
+        # column by column: a BLAS product may spread NaN
+        ref = np.stack([(a * x[k]).sum(axis=1) for k in range(K)], axis=1).astype(np.float32)
+    assert np.array_equal(np.isnan(got), np.isnan(ref))
+    assert np.array_equal(got[np.isinf(ref)], ref[np.isinf(ref)])
+    ok = np.isfinite(ref)
+    m = np.abs(np.where(np.isfinite(a), a, 0)) @ np.abs(np.where(np.isfinite(x), x, 0)).T
+    assert (np.abs(got[ok] - ref[ok].astype(np.float64)) <= 1e-4 * m[ok]).all()
+
+
+@pytest.mark.parametrize("N,K,B", [(1153, 2177, 333), (300, 1000, 1024)])
+@pytest.mark.parametrize("prec", [L1.F32, L1.BF16X3])
+def test_packed_prox_equals_the_calls(N, K, B, prec):
+    # the fused update and dense_wgrad + prox_l1_recompress: the same bits
+    rng = np.random.default_rng(1)
+    mask = rng.random((N, K)) < 0.1
+    rp = np.concatenate([[0], np.cumsum(mask.sum(1))]).astype(np.int32)
+    ci = np.nonzero(mask)[1].astype(np.int32)
+    W = L1.CSR.from_host(rp, ci, rng.standard_normal(len(ci)).astype(np.float32), K)
+    dY, X = (t(v) for v in operands(N, K, B, seed=2))
+    lam = float(np.sqrt(B / 3.0))
+    Z, out = L1.dense_wgrad_prox_recompress(W, dY, X, 0.01, lam, precision=prec)
+    ref = L1.prox_l1_recompress(W, L1.dense_wgrad(dY, X, precision=prec), 0.01, lam)
+    for a, b in zip(out.to_host(), ref.to_host()):
+        assert bits_equal(a, b)
