@@ -89,7 +89,9 @@ enum l1csr_op {
     L1CSR_OP_PROX_RECOMPRESS = 7,
     L1CSR_OP_DENSE_WGRAD = 8,
     L1CSR_OP_WGRAD_PROX = 9,   /* dense_wgrad_prox, fp32 (other precisions need none) */
-    L1CSR_OP_WGRAD_PACKED = 10 /* dense_wgrad / dense_wgrad_prox with packed operands (nnz unused) */
+    L1CSR_OP_WGRAD_PACKED = 10, /* dense_wgrad / dense_wgrad_prox with packed operands (nnz unused) */
+    L1CSR_OP_SDDMM_PACKED = 11, /* sddmm_masked_wgrad over a dense pattern, packed operands */
+    L1CSR_OP_SPMM_PACKED = 12   /* csr_spmm_fwd / csr_spmm_bwd_t over a dense pattern, packed operands */
 };
 
 /* Human-readable name of a status code (static string, never NULL). */
@@ -127,6 +129,13 @@ int l1csr_host_free_mapped(void *host);
  * each summed in ascending p order and the k partial sums then added in piece
  * order.  Either order is fixed by the operands alone, so results are
  * reproducible run to run and under any schedule.
+ * With l1csr_workspace_bytes(L1CSR_OP_SPMM_PACKED, n_rows, n_cols, nnz, B)
+ * bytes (0: not taken at these sizes) a product over a dense pattern packs W,
+ * zeros written out, and X as bf16 parts into ws and runs on the matrix cores
+ * as dense_wgrad's packed products do (all 24 significand bits, fp32 sums by
+ * 16 columns; ranges of columns summed apart and added in order).  Where a
+ * value's parts would over- or underflow the stored entries are summed in
+ * ascending p order instead.
  */
 int csr_spmm_fwd(int32_t n_rows, int32_t n_cols, int64_t nnz,
                  const int32_t *row_ptr, const int32_t *col_idx, const float *vals,
@@ -140,7 +149,7 @@ int csr_spmm_fwd(int32_t n_rows, int32_t n_cols, int64_t nnz,
  * (row pieces, their deal to the waves, the pair stream holding W's column
  * offsets and values) into the caller's buffer plan; csr_spmm_planned then
  * computes Y = W . X from it, the same bits as csr_spmm_fwd with the same
- * arguments.  Arguments as for csr_spmm_fwd; plan must hold
+ * arguments and a workspace of L1CSR_OP_SPMM's size.  Arguments as for csr_spmm_fwd; plan must hold
  * l1csr_workspace_bytes(L1CSR_OP_SPMM, n_rows, n_cols, nnz, B) bytes (0: the
  * product does not take the tiled path, plan may be NULL and csr_spmm_plan
  * enqueues nothing).  Preconditions: both calls get the same n_rows, n_cols,
@@ -196,7 +205,7 @@ int csc_update_vals(int32_t n_cols, int64_t nnz, const int32_t *col_ptr, const i
  * csc_build, all non-NULL) this is the forward product of W^T: a gather in
  * ascending row order, reproducible; ws (nullable) as for csr_spmm_fwd with
  * the dimensions swapped, l1csr_workspace_bytes(L1CSR_OP_SPMM, n_cols, n_rows,
- * nnz, B).  With all three NULL the call scatters W's CSR with float atomics
+ * nnz, B) (or L1CSR_OP_SPMM_PACKED).  With all three NULL the call scatters W's CSR with float atomics
  * instead (the summation order, and so the low bits, vary from run to run);
  * dX is zeroed first by the call.  dY is [n_rows][ldy], dX is [n_cols][ldx].
  */
@@ -251,7 +260,9 @@ int dense_wgrad(int32_t N, int32_t K, int32_t B,
  * on W's pattern:
  *     gv[p] = sum_{b < B} dY[row(p)][b] * X[col_idx[p]][b],  0 <= p < nnz.
  * gv has nnz entries (host nnz = row_ptr[n_rows]).  ws must hold
- * l1csr_workspace_bytes(L1CSR_OP_SDDMM, n_rows, n_cols, nnz, B) bytes.
+ * l1csr_workspace_bytes(L1CSR_OP_SDDMM, n_rows, n_cols, nnz, B) bytes; with
+ * those of L1CSR_OP_SDDMM_PACKED (0: not taken at these sizes) the gradient
+ * over a dense pattern is the packed product's, sampled in its epilogue.
  */
 int sddmm_masked_wgrad(int32_t n_rows, int32_t n_cols, int64_t nnz,
                        const int32_t *row_ptr, const int32_t *col_idx,

@@ -38,6 +38,8 @@ OP_PROX_RECOMPRESS = 7
 OP_DENSE_WGRAD = 8
 OP_WGRAD_PROX = 9
 OP_WGRAD_PACKED = 10
+OP_SDDMM_PACKED = 11
+OP_SPMM_PACKED = 12
 
 
 class L1CSRError(RuntimeError):
@@ -124,6 +126,12 @@ def status_str(status: int) -> str:
 @functools.lru_cache(maxsize=4096)  # a pure function of the sizes
 def workspace_bytes(op: int, n_rows: int, n_cols: int, nnz: int, B: int) -> int:
     return int(lib().l1csr_workspace_bytes(op, n_rows, n_cols, nnz, B))
+
+
+def _spmm_bytes(n_rows, n_cols, nnz, B):
+    """Workspace of a product of an n_rows x n_cols CSR (or CSC) operand."""
+    return max(workspace_bytes(OP_SPMM, n_rows, n_cols, nnz, B),
+               workspace_bytes(OP_SPMM_PACKED, n_rows, n_cols, nnz, B))
 
 
 # ---------------------------------------------------------------------------
@@ -411,7 +419,7 @@ def csr_spmm_fwd(W: CSR, X, Y=None, stream=None):
     N, By, ldy = _mat(Y, "Y")
     if N != W.n_rows or By != B:
         raise ValueError("Y must be [n_rows][B]")
-    ws, wsb = _workspace(workspace_bytes(OP_SPMM, W.n_rows, W.n_cols, nnz, B), X.device, stream)
+    ws, wsb = _workspace(_spmm_bytes(W.n_rows, W.n_cols, nnz, B), X.device, stream)
     _check(lib().csr_spmm_fwd(W.n_rows, W.n_cols, nnz, _p(W.row_ptr), _p(W.col_idx), _p(W.vals),
                               _p(X), ldx, B, _p(Y), ldy, _p(ws), wsb, _stream(stream)),
            "csr_spmm_fwd")
@@ -420,7 +428,9 @@ def csr_spmm_fwd(W: CSR, X, Y=None, stream=None):
 
 class SpmmPlan:
     """A caller-owned plan of a tiled product (csr_spmm_plan): its device
-    buffer and the (n_rows, n_cols, nnz, B) it was made for."""
+    buffer and the (n_rows, n_cols, nnz, B) it was made for.  Where the product
+    packs its operands instead (OP_SPMM_PACKED) there is nothing to plan: the
+    plan is empty and the planned call is the whole product."""
 
     def __init__(self, n_rows, n_cols, nnz, B, device):
         self.buf = None
@@ -432,7 +442,8 @@ class SpmmPlan:
         (the caller orders the reuse after the last use of the old plan)."""
         torch = _torch()
         self.key = (n_rows, n_cols, nnz, B)
-        self.nbytes = workspace_bytes(OP_SPMM, n_rows, n_cols, nnz, B)
+        self.packed = workspace_bytes(OP_SPMM_PACKED, n_rows, n_cols, nnz, B) > 0
+        self.nbytes = 0 if self.packed else workspace_bytes(OP_SPMM, n_rows, n_cols, nnz, B)
         if self.nbytes and (self.buf is None or self.buf.numel() < self.nbytes):
             self.buf = torch.empty(self.nbytes, dtype=torch.uint8, device=self.device)
         return self
@@ -451,6 +462,8 @@ def csr_spmm_plan(W: CSR, B: int, plan: SpmmPlan | None = None, stream=None) -> 
     if plan is None:
         plan = SpmmPlan(*key, W.row_ptr.device)
     pp, pb = _plan_args(plan, key)
+    if plan.packed:
+        return plan
     _check(lib().csr_spmm_plan(W.n_rows, W.n_cols, nnz, _p(W.row_ptr), _p(W.col_idx), _p(W.vals), int(B), pp, pb,
                                _stream(stream)), "csr_spmm_plan")
     return plan
@@ -469,6 +482,8 @@ def csr_spmm_planned(W: CSR, X, plan: SpmmPlan, Y=None, stream=None):
     if N != W.n_rows or By != B:
         raise ValueError("Y must be [n_rows][B]")
     pp, pb = _plan_args(plan, (W.n_rows, W.n_cols, nnz, B))
+    if plan.packed:
+        return csr_spmm_fwd(W, X, Y, stream)
     _check(lib().csr_spmm_planned(W.n_rows, W.n_cols, nnz, _p(W.row_ptr), _p(W.col_idx), _p(W.vals), _p(X), ldx, B,
                                   _p(Y), ldy, pp, pb, _stream(stream)), "csr_spmm_planned")
     return Y
@@ -529,7 +544,7 @@ def csr_spmm_bwd_t(W: CSR, dY, csc: CSC | None = None, dX=None, stream=None):
     wsb = 0
     if csc is not None:
         cp, ri, vt = csc.col_ptr, csc.row_idx, csc.vals_t
-        ws, wsb = _workspace(workspace_bytes(OP_SPMM, W.n_cols, W.n_rows, nnz, B), dY.device, stream)
+        ws, wsb = _workspace(_spmm_bytes(W.n_cols, W.n_rows, nnz, B), dY.device, stream)
     _check(lib().csr_spmm_bwd_t(W.n_rows, W.n_cols, nnz, _p(W.row_ptr), _p(W.col_idx), _p(W.vals),
                                 _p(cp), _p(ri), _p(vt), _p(dY), ldy, B, _p(dX), ldx, _p(ws), wsb,
                                 _stream(stream)), "csr_spmm_bwd_t")
@@ -568,7 +583,8 @@ def sddmm_masked_wgrad(W: CSR, dY, X, gv=None, stream=None):
         raise ValueError("shape mismatch")
     if gv is None:
         gv = torch.empty(max(nnz, 1), dtype=torch.float32, device=dY.device)
-    ws, wsb = _workspace(workspace_bytes(OP_SDDMM, W.n_rows, W.n_cols, nnz, B), dY.device, stream)
+    ws, wsb = _workspace(max(workspace_bytes(OP_SDDMM, W.n_rows, W.n_cols, nnz, B),
+                             workspace_bytes(OP_SDDMM_PACKED, W.n_rows, W.n_cols, nnz, B)), dY.device, stream)
     _check(lib().sddmm_masked_wgrad(W.n_rows, W.n_cols, nnz, _p(W.row_ptr), _p(W.col_idx), _p(dY),
                                     ldy, _p(X), ldx, B, _p(gv), _p(ws), wsb, _stream(stream)),
            "sddmm_masked_wgrad")

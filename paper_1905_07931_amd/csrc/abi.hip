@@ -275,6 +275,8 @@ size_t l1csr_workspace_bytes(int op, int32_t n_rows, int32_t n_cols, int64_t nnz
                          x3 = split_wgrad_bytes(n_rows, n_cols, B, L1CSR_BF16X3);
             return round_up(f > x3 ? f : x3);
         }
+        case L1CSR_OP_SDDMM_PACKED: return round_up(packed_sddmm_bytes(n_rows, n_cols, nnz, B));
+        case L1CSR_OP_SPMM_PACKED: return round_up(packed_spmm_bytes(n_rows, n_cols, nnz, B));
         case L1CSR_OP_SOFTMAX_XENT: return round_up(sizeof(float) * (size_t)(ceil_div(B, 256) + 1));
         default: return 0;
     }
@@ -287,6 +289,9 @@ int csr_spmm_fwd(int32_t n_rows, int32_t n_cols, int64_t nnz, const int32_t *row
     if (bad_dense(X, n_cols, B, ldx) || bad_dense(Y, n_rows, B, ldy)) return L1CSR_EINVAL;
     if (ws != nullptr && ws_bytes < spmm_workspace_bytes(n_rows, n_cols, nnz, B)) return L1CSR_EINVAL;
     if (ceil_div(B, kWave) > kMaxGridY) return L1CSR_EUNSUPPORTED;
+    const size_t packed = packed_spmm_bytes(n_rows, n_cols, nnz, B);
+    if (packed > 0 && ws != nullptr && ws_bytes >= packed)
+        return hip_status(launch_packed_spmm(n_rows, n_cols, row_ptr, col_idx, vals, X, ldx, B, Y, ldy, ws, stream));
     return hip_status(launch_spmm(n_rows, n_cols, nnz, row_ptr, col_idx, vals, X, ldx, B, Y, ldy, ws,
                                   stream));
 }
@@ -356,6 +361,9 @@ int csr_spmm_bwd_t(int32_t n_rows, int32_t n_cols, int64_t nnz, const int32_t *r
     }
     if (bad_dense(dY, n_rows, B, ldy) || bad_dense(dX, n_cols, B, ldx)) return L1CSR_EINVAL;
     if (ceil_div(B, kWave) > kMaxGridY) return L1CSR_EUNSUPPORTED;
+    const size_t packed = use_csc ? packed_spmm_bytes(n_cols, n_rows, nnz, B) : 0;
+    if (packed > 0 && ws != nullptr && ws_bytes >= packed)
+        return hip_status(launch_packed_spmm(n_cols, n_rows, col_ptr, row_idx, vals_t, dY, ldy, B, dX, ldx, ws, stream));
     if (use_csc)  // the forward product of the transposed matrix
         return hip_status(launch_spmm(n_cols, n_rows, nnz, col_ptr, row_idx, vals_t, dY, ldy, B, dX,
                                       ldx, ws, stream));
@@ -394,6 +402,9 @@ int sddmm_masked_wgrad(int32_t n_rows, int32_t n_cols, int64_t nnz, const int32_
     const size_t need = sddmm_workspace_bytes(n_rows, n_cols, nnz, B);
     if (need > 0 && (ws == nullptr || ws_bytes < need)) return L1CSR_EINVAL;
     if (ceil_div(B, kWave) > kMaxGridY) return L1CSR_EUNSUPPORTED;
+    const size_t packed = packed_sddmm_bytes(n_rows, n_cols, nnz, B);
+    if (packed > 0 && ws != nullptr && ws_bytes >= packed)
+        return hip_status(launch_packed_sddmm(n_rows, n_cols, row_ptr, col_idx, dY, ldy, X, ldx, B, gv, ws, stream));
     return hip_status(
         launch_sddmm(n_rows, n_cols, nnz, row_ptr, col_idx, dY, ldy, X, ldx, B, gv, ws, stream));
 }

@@ -93,6 +93,13 @@ hipError_t launch_split_wgrad(int N, int K, int B, int precision, const float *d
                               int64_t ldx, float *dW, int64_t ldw, void *ws, hipStream_t s);
 hipError_t launch_split_wgrad_prox(int N, int K, int B, int precision, const float *dY, int64_t ldy, const float *X,
                                    int64_t ldx, float *Z, int64_t ldz, const prox_epi &P, void *ws, hipStream_t s);
+// products over dense patterns on the same kernels (ws: the bytes, 0 where not taken)
+size_t packed_sddmm_bytes(int N, int K, int64_t nnz, int B);
+hipError_t launch_packed_sddmm(int N, int K, const int *ptr, const int *idx, const float *dY, int64_t ldy,
+                               const float *X, int64_t ldx, int B, float *gv, void *ws, hipStream_t s);
+size_t packed_spmm_bytes(int N, int K, int64_t nnz, int B);
+hipError_t launch_packed_spmm(int N, int K, const int *ptr, const int *idx, const float *vals, const float *X,
+                              int64_t ldx, int B, float *Y, int64_t ldy, void *ws, hipStream_t s);
 // Z = S_t(W - eta * dY.X^T) and P.counts, in one GEMM launch
 hipError_t launch_wgrad_f32_prox(int N, int K, int B, const float *dY, int64_t ldy, const float *X,
                                  int64_t ldx, float *Z, int64_t ldz, const prox_epi &P, hipStream_t s);

@@ -87,6 +87,30 @@ __device__ __forceinline__ void split8(const float (&x)[8], bf16x8 (&p)[NP]) {
     }
 }
 
+// What the packing of 8 values shares: their parts stored, magnitudes tracked
+template <int NP>
+__device__ __forceinline__ void pack8(const float (&x)[8], unsigned &mx, char *d) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) mx = max(mx, __float_as_uint(x[e]) & 0x7fffffffu);
+    bf16x8 p[NP];
+    split8<NP>(x, p);
+#pragma unroll
+    for (int q = 0; q < NP; ++q) *reinterpret_cast<bf16x8 *>(d + q * kBlockBytes) = p[q];
+}
+
+// rowmax: the 32 rows' magnitudes in LDS (zeroed, a barrier behind it); ends the workgroup's pack
+__device__ __forceinline__ void store_flag(unsigned *rowmax, unsigned mx, int *flag) {
+    const int lane = threadIdx.x & 63;
+    atomicMax(&rowmax[lane & 31], mx);
+    __syncthreads();
+    if (threadIdx.x < kWave) {
+        const unsigned m = rowmax[lane & 31];
+        const bool odd = m > __float_as_uint(kPartMax) || (m != 0u && m < __float_as_uint(kPartMin));
+        const uint64_t any = __ballot(odd);
+        if (lane == 0) *flag = any != 0ull;
+    }
+}
+
 // one operand of a pack launch: rows of a row-major fp32 matrix, the reduction
 // index contiguous (v4: 16-byte aligned rows)
 struct pack_src {
@@ -128,22 +152,102 @@ __global__ __launch_bounds__(256) void pack_rows_kernel(pack_src s0, pack_src s1
 #pragma unroll
             for (int e = 0; e < 8; ++e) x[e] = row < s.rows && k + e < kr ? src[k + e] : 0.f;
         }
-#pragma unroll
-        for (int e = 0; e < 8; ++e) mx = max(mx, __float_as_uint(x[e]) & 0x7fffffffu);
-        bf16x8 p[NP];
-        split8<NP>(x, p);
-        char *d = s.out.data + ((int64_t)g * s.out.steps + st) * (NP * kBlockBytes) + lane * 16;
-#pragma unroll
-        for (int q = 0; q < NP; ++q) *reinterpret_cast<bf16x8 *>(d + q * kBlockBytes) = p[q];
+        pack8<NP>(x, mx, s.out.data + ((int64_t)g * s.out.steps + st) * (NP * kBlockBytes) + lane * 16);
     }
-    atomicMax(&rowmax[lane & 31], mx);
+    store_flag(rowmax, mx, &s.out.flags[g * s.out.kblocks + blockIdx.y]);
+}
+
+// Both operands of a sparse product in one launch: a CSR matrix (the first
+// groups) and the transpose of the dense operand X [Kr][ldx], whose packed rows
+// are its columns.  A workgroup takes a 32-row group and 256 reduction indices
+// of either.  The CSR part: the rows' first entries at both ends of the index
+// range are searched for, the entries between them scattered into a zeroed LDS
+// tile, which is packed.  The X part: a lane's 8 values are 8 rows apart, 32 lanes
+// read 128 consecutive bytes of each.  Memory-bound on the parts written (6
+// bytes per weight, zeros included): 25 us at 4096 x 4096 x 512 and 5 % stored
+// (108 MB, 4.4 TB/s), 42 us at 50 % (180 MB, 4.3 TB/s).
+constexpr int kCsrStride = kPackK + 4;  // floats: 16-byte reads of 32 rows spread over the banks
+
+__global__ __launch_bounds__(256) void pack_spmm_kernel(int n_rows, const int *__restrict__ ptr,
+                                                        const int *__restrict__ idx, const float *__restrict__ vals,
+                                                        packed A, const float *__restrict__ X, int64_t ldx, int Kr,
+                                                        int cols, packed B) {
+    __shared__ unsigned rowmax[kGroup];
+    __shared__ __attribute__((aligned(16))) float tile[kGroup * kCsrStride];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    if (threadIdx.x < kGroup) rowmax[threadIdx.x] = 0u;
+    unsigned mx = 0u;
+    const int kb = blockIdx.y, k0 = kb * kPackK;
+    if ((int)blockIdx.x >= A.groups) {  // X
+        const int g = blockIdx.x - A.groups;
+        const int col = g * kGroup + (lane & 31);
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < kPackK / kStep / 4; ++i) {
+            const int st = kb * (kPackK / kStep) + i * 4 + wave;
+            if (st >= B.steps) break;
+            const int k = st * kStep + (lane >> 5) * 8;
+            float x[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) x[e] = col < cols && k + e < Kr ? X[(int64_t)(k + e) * ldx + col] : 0.f;
+            pack8<3>(x, mx, B.data + ((int64_t)g * B.steps + st) * (3 * kBlockBytes) + lane * 16);
+        }
+        store_flag(rowmax, mx, &B.flags[g * B.kblocks + kb]);
+        return;
+    }
+    const int g = blockIdx.x;
+    for (int i = threadIdx.x; i < kGroup * kCsrStride / 4; i += 256)
+        reinterpret_cast<float4 *>(tile)[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+    // eight lanes per row: the row's first entries at or past k0 and k0 + 256,
+    // eight probes a round (four dependent loads for 4096 entries, not twelve)
+    const int r = threadIdx.x >> 3, j = threadIdx.x & 7, row = g * kGroup + r;
+    int lo0 = 0, hi0 = 0;
+    if (row < n_rows) {
+        lo0 = ptr[row];
+        hi0 = ptr[row + 1];
+    }
+    int lo1 = lo0, hi1 = hi0;
+    while (__ballot(lo0 < hi0 || lo1 < hi1)) {
+        auto probe = [&](int &lo, int &hi, int target) {
+            const int n = hi - lo;
+            auto at = [&](int q) { return lo + (int)((unsigned)n * (unsigned)(q + 1) / 9u); };  // n < 2^28
+            const bool less = n > 0 && idx[at(j)] < target;
+            const int c = __popcll((__ballot(less) >> (lane & 56)) & 0xffull);
+            if (n > 0) {
+                const int nlo = c > 0 ? at(c - 1) + 1 : lo, nhi = c < 8 ? at(c) : hi;
+                lo = nlo;
+                hi = nhi;
+            }
+        };
+        probe(lo0, hi0, k0);
+        probe(lo1, hi1, k0 + kPackK);
+    }
     __syncthreads();
-    if (wave == 0) {
-        const unsigned m = rowmax[lane & 31];
-        const bool odd = m > __float_as_uint(kPartMax) || (m != 0u && m < __float_as_uint(kPartMin));
-        const uint64_t any = __ballot(odd);
-        if (lane == 0) s.out.flags[g * s.out.kblocks + blockIdx.y] = any != 0ull;
+    for (int p0 = lo0 + j; p0 < lo1; p0 += 32) {  // four entries a lane in flight
+        int c[4];
+        float v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int p = p0 + 8 * u;
+            c[u] = p < lo1 ? idx[p] - k0 : -1;
+            v[u] = p < lo1 ? vals[p] : 0.f;
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (c[u] >= 0) tile[r * kCsrStride + c[u]] = v[u];
     }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kPackK / kStep / 4; ++i) {
+        const int st = kb * (kPackK / kStep) + i * 4 + wave;
+        if (st >= A.steps) break;
+        const float4 *t = reinterpret_cast<const float4 *>(tile + (lane & 31) * kCsrStride +
+                                                           (i * 4 + wave) * kStep + (lane >> 5) * 8);
+        const float4 a = t[0], b = t[1];
+        const float x[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+        pack8<3>(x, mx, A.data + ((int64_t)g * A.steps + st) * (3 * kBlockBytes) + lane * 16);
+    }
+    store_flag(rowmax, mx, &A.flags[g * A.kblocks + kb]);
 }
 
 __device__ __forceinline__ floatx16 mfma16(bf16x8 a, bf16x8 b, floatx16 c) {
@@ -155,10 +259,13 @@ __device__ __forceinline__ floatx16 mfma16(bf16x8 a, bf16x8 b, floatx16 c) {
 // builtin's loads against the reads of the other buffers and waited for the
 // loads just issued (vmcnt(0)) in one step of three.  It writes no register;
 // wait_vm() below counts it.
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"  // m0 is reserved: the clobber orders it, nothing keeps it
 __device__ __forceinline__ void dma16(const char *base, unsigned off, unsigned lds) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(base)
                  : "memory", "m0");
 }
+#pragma clang diagnostic pop
 
 template <int N>
 __device__ __forceinline__ void wait_vm() {  // at most N vector memory operations and no LDS access outstanding
@@ -178,7 +285,27 @@ constexpr int TM = 2, TN = 2, WM = 2, WN = 2;
 constexpr int BM = 32 * TM * WM, BN = 32 * TN * WN, NT = 64 * WM * WN;
 constexpr int RGA = TM * WM, RGB = TN * WN;  // groups of a tile
 
-enum { kEpiStore = 0, kEpiProx = 1 };
+enum {
+    kEpiStore = 0,  // C
+    kEpiProx = 1,   // Z = S_t(W - eta C) and its word counts
+    kEpiMask = 2,   // C's entries on W's pattern, in CSR order
+    kEpiSpmm = 3    // C; A is a packed CSR matrix, B a packed transpose
+};
+
+// How a sum is accumulated over the steps (relative error against 64 bits,
+// 2-norm, at 1024 / 512 reduction indices; every rounding of the running sum
+// costs 2^-25 of it, and the five small terms would each cause one):
+//   one set of registers                                     4.9e-7 / 3.5e-7
+//   the five small terms in a set of their own               1.8e-7 / 1.2e-7
+//   that, and the large terms moved to a third set every six
+//   steps (its chain and theirs are then both short)         8.6e-8 / 7.5e-8
+// The sums that a kernel replaces set which one it needs: a row of fp32 matrix
+// instructions 5.7e-7 / 4.1e-7 (the dense gradient: one set), a sequential fp32
+// row sum 3-5e-7 (the sparse products: two), a tree over 64 lanes 8.5e-8 (the
+// masked gradient: three).  The second set is free (353 and 354 us at 4096 x
+// 9216 x 1024), the third costs 3 %.
+enum { kAccOne = 1, kAccSmall = 2, kAccTree = 3 };
+constexpr int kTreeSteps = 6;  // a multiple of the three steps in LDS
 
 struct gemm_args {
     int M, Nn, Kr;                // sizes (Kr: all reduction indices)
@@ -189,10 +316,12 @@ struct gemm_args {
     int split_steps;              // steps per split (blockIdx.y); the splits' C are M * ldc apart
     float *C;
     int64_t ldc;
-    prox_epi P;
+    prox_epi P;                   // (kEpiMask: mask, pos and kw; C is the entry array)
+    const int *ptr, *idx;         // kEpiSpmm: A as CSR, b32 [Kr][ldb]
+    const float *vals;
 };
 
-template <int NP, int EPI>
+template <int NP, int EPI, int ACC>
 __global__ __launch_bounds__(NT, 2) void split_gemm_kernel(gemm_args G) {
     constexpr int PIECES = (RGA + RGB) * NP;     // 1 KB blocks of a step
     constexpr int LPW = PIECES / (NT / kWave);   // loads per wave and step
@@ -255,16 +384,19 @@ __global__ __launch_bounds__(NT, 2) void split_gemm_kernel(gemm_args G) {
     }
     static_assert(RGA + RGB == 8, "one lane per group");
 
-    floatx16 acc[TM][TN];
+    floatx16 acc[TM][TN], small[TM][TN], top[TM][TN];  // (sets that ACC does not use vanish)
+    auto each = [&](auto f) {
 #pragma unroll
-    for (int a = 0; a < TM; ++a)
+        for (int a = 0; a < TM; ++a)
 #pragma unroll
-        for (int b = 0; b < TN; ++b)
+            for (int b = 0; b < TN; ++b)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.f;
+                for (int r = 0; r < 16; ++r) f(a, b, r);
+    };
+    each([&](int a, int b, int r) { acc[a][b][r] = small[a][b][r] = top[a][b][r] = 0.f; });
 
     const int lr = lane & 31, lh = lane >> 5;
-    if (!odd) {
+    if (!odd) {  // (the same in every wave: no wave waits for one that left)
         const int oa = wgm * (NP * kBlockBytes) + lane * 16;
         const int ob = (RGA + wgn) * (NP * kBlockBytes) + lane * 16;
         auto compute = [&](const char *cur) {
@@ -284,19 +416,29 @@ __global__ __launch_bounds__(NT, 2) void split_gemm_kernel(gemm_args G) {
 #pragma unroll
                     for (int b = 0; b < TN; ++b) acc[a][b] = mfma16(af[qa][a], bf[qb][b], acc[a][b]);
             };
+            auto small_term = [&](int qa, int qb) {
+                if constexpr (ACC == kAccOne) {
+                    term(qa, qb);
+                } else {
+#pragma unroll
+                    for (int a = 0; a < TM; ++a)
+#pragma unroll
+                        for (int b = 0; b < TN; ++b) small[a][b] = mfma16(af[qa][a], bf[qb][b], small[a][b]);
+                }
+            };
             if constexpr (NP == 2) {
                 // the two small terms first, then hi . hi
-                term(1, 0);
-                term(0, 1);
+                small_term(1, 0);
+                small_term(0, 1);
                 term(0, 0);
             } else {
                 // in the order the fragments arrive
                 term(0, 0);
-                term(1, 0);
-                term(0, 1);
-                term(1, 1);
-                term(2, 0);
-                term(0, 2);
+                small_term(1, 0);
+                small_term(0, 1);
+                small_term(1, 1);
+                small_term(2, 0);
+                small_term(0, 2);
             }
         };
         // step c: its blocks have landed everywhere (the loads of step c + 1 may
@@ -319,7 +461,31 @@ __global__ __launch_bounds__(NT, 2) void split_gemm_kernel(gemm_args G) {
             step(c, S0, l2);
             if (c + 1 < steps) step(c + 1, S1, l0);
             if (c + 2 < steps) step(c + 2, S2, l1);
+            if constexpr (ACC == kAccTree)
+                if (c % kTreeSteps == kTreeSteps - 3)
+                    each([&](int a, int b, int r) {
+                        top[a][b][r] += acc[a][b][r];
+                        acc[a][b][r] = 0.f;
+                    });
         }
+        if constexpr (ACC == kAccTree) each([&](int a, int b, int r) { acc[a][b][r] += top[a][b][r]; });
+        if constexpr (ACC != kAccOne) each([&](int a, int b, int r) { acc[a][b][r] += small[a][b][r]; });
+    } else if constexpr (EPI == kEpiSpmm) {
+        // not exact in parts: the stored entries of A alone (a zero of the
+        // packed copy would turn an infinity of B into NaN), a thread per column
+        const int k0 = c0 * kStep, k1 = min(G.Kr, (c0 + steps) * kStep);
+        float *C = G.C + (int64_t)blockIdx.y * G.M * G.ldc;
+        const int col = n0 + (threadIdx.x & (BN - 1));
+        if (col < G.Nn)
+            for (int row = m0 + threadIdx.x / BN; row < min(m0 + BM, G.M); row += NT / BN) {
+                float sum = 0.f;
+                for (int p = G.ptr[row]; p < G.ptr[row + 1]; ++p) {
+                    const int k = G.idx[p];
+                    if (k >= k0 && k < k1) sum = fmaf(G.vals[p], G.b32[k * G.ldb + col], sum);
+                }
+                C[(int64_t)row * G.ldc + col] = sum;
+            }
+        return;
     } else {
         // not exact in parts: the fp32 instruction, lane half h of a pair of indices
         const int k0 = c0 * kStep, k1 = min(G.Kr, (c0 + steps) * kStep);
@@ -360,6 +526,19 @@ __global__ __launch_bounds__(NT, 2) void split_gemm_kernel(gemm_args G) {
     }
     // D layout of the 32x32 MFMA: lane l, register r holds
     // row 8*(r/4) + 4*(l/32) + r%4, column l%32 of the 32x32 tile.
+    if constexpr (EPI == kEpiMask) {
+        // the entries of a row's 32-column word are consecutive in the CSR
+        __syncthreads();
+        int2 *stage = reinterpret_cast<int2 *>(S0);
+        prox_stage<BM, BN, NT>(G.P, G.M, m0, n0, stage);
+        const unsigned below = (1u << lr) - 1u;
+        each([&](int a, int b, int r) {
+            const int2 mp = stage[((wgm + a) * 32 + 8 * (r >> 2) + 4 * lh + (r & 3)) * (BN / 32) + wgn + b];
+            const unsigned m = (unsigned)mp.x;
+            if ((m >> lr) & 1u) G.C[mp.y + __popc(m & below)] = acc[a][b][r];
+        });
+        return;
+    }
     float *C = G.C + (int64_t)blockIdx.y * G.M * G.ldc;
 #pragma unroll
     for (int a = 0; a < TM; ++a)
@@ -382,10 +561,12 @@ hipError_t launch_pack(const pack_src &a, const pack_src &b, int kr, hipStream_t
     return hipGetLastError();
 }
 
-template <int NP, int EPI>
-hipError_t launch_tiles(const gemm_args &G, int splits, hipStream_t s) {
+template <int NP, int EPI, int ACC>
+hipError_t launch_tiles(gemm_args G, int splits, hipStream_t s) {
+    G.tiles_m = (int)ceil_div(G.M, BM);
+    G.tiles_n = (int)ceil_div(G.Nn, BN);
     dim3 grid((unsigned)(ceil_div((int64_t)G.tiles_m * G.tiles_n, 8) * 8), (unsigned)splits);
-    split_gemm_kernel<NP, EPI><<<grid, NT, 0, s>>>(G);
+    split_gemm_kernel<NP, EPI, ACC><<<grid, NT, 0, s>>>(G);
     return hipGetLastError();
 }
 
@@ -404,15 +585,14 @@ hipError_t wgrad(int N, int K, int B, const float *dY, int64_t ldy, const float 
     if (e != hipSuccess) return e;
     G.M = N; G.Nn = K; G.Kr = B;
     G.a32 = dY; G.lda = ldy; G.b32 = X; G.ldb = ldx;
-    G.tiles_m = (int)ceil_div(N, BM); G.tiles_n = (int)ceil_div(K, BN);
     G.split_steps = G.A.steps;
     G.C = C; G.ldc = ldc; G.P = P;
     const wgrad_split w = wgrad_plan(N, K, B);
-    if (w.splits == 1) return launch_tiles<NP, EPI>(G, 1, s);
+    if (w.splits == 1) return launch_tiles<NP, EPI, kAccOne>(G, 1, s);
     float *parts = reinterpret_cast<float *>(p);
     G.split_steps = w.chunk / kStep;
     G.C = parts; G.ldc = K;
-    e = launch_tiles<NP, kEpiStore>(G, w.splits, s);
+    e = launch_tiles<NP, kEpiStore, kAccOne>(G, w.splits, s);
     if (e != hipSuccess) return e;
     return launch_wgrad_reduce(N, K, w.splits, parts, C, ldc, s);
 }
@@ -458,6 +638,105 @@ hipError_t launch_split_wgrad_prox(int N, int K, int B, int precision, const flo
                                    int64_t ldx, float *Z, int64_t ldz, const prox_epi &P, void *ws, hipStream_t s) {
     return precision == kPrecF32 ? wgrad<3, kEpiProx>(N, K, B, dY, ldy, X, ldx, Z, ldz, P, ws, s)
                                  : wgrad<2, kEpiProx>(N, K, B, dY, ldy, X, ldx, Z, ldz, P, ws, s);
+}
+
+// gv = dY . X^T on W's pattern: the whole product, its epilogue writing the
+// stored entries.  Taken where the modelled time is shorter than the entry-wise
+// kernels' (both models in us, fitted to calls on the chip): theirs is nnz * B
+// products at 6.6 per ps (dense patterns 12, rows not 16-byte aligned 3) or an
+// entry's fixed cost, this
+// one's the packing, N * K * B products at tile granularity and the bitmap index.
+// Measured at 4096 x 4096 x 512, entry-wise -> whole: 5 % stored 81 -> 105, 10 %
+// 135 -> 106, 20 % 259 -> 111, 50 % 369 -> 128; 4096 x 9216 x 1024 at 9 % 693 ->
+// 393; 1000 x 1000 x 256 at 20 % 22 -> 29.
+size_t packed_sddmm_bytes(int N, int K, int64_t nnz, int B) {
+    if (B < 32 || B > (1 << 22) || N == 0 || K == 0 || wgrad_plan(N, K, B).splits > 1) return 0;
+    const double np = (double)ceil_div(N, BM) * BM, kp = (double)ceil_div(K, BN) * BN, n = (double)nnz;
+    const double whole = 24 + 10.0 * ((double)N + K) * B / 5e6 + 12 * np * kp * B / 1.25e9 + n / 250e3;
+    const double rate = B % 4 ? 3e6 : (3 * n > (double)N * K ? 12e6 : 6.6e6);  // products per us
+    const double products = n * B / rate, fixed = n / 23e3;
+    if (whole > 0.95 * (14 + (products > fixed ? products : fixed))) return 0;
+    return (size_t)(packed_bytes(N, B, 3) + flag_bytes(N, B) + packed_bytes(K, B, 3) + flag_bytes(K, B)) +
+           2 * (size_t)ceil_div(word_counts_bytes(N, K), 256) * 256;
+}
+
+hipError_t launch_packed_sddmm(int N, int K, const int *ptr, const int *idx, const float *dY, int64_t ldy,
+                               const float *X, int64_t ldx, int B, float *gv, void *ws, hipStream_t s) {
+    char *p = static_cast<char *>(ws);
+    gemm_args G{};
+    G.A = carve_packed(p, N, B, 3);
+    G.B = carve_packed(p, K, B, 3);
+    unsigned *mask = reinterpret_cast<unsigned *>(p);
+    int *pos = reinterpret_cast<int *>(p + ceil_div(word_counts_bytes(N, K), 256) * 256);
+    hipError_t e = launch_bitmap(N, K, ptr, idx, mask, pos, s);
+    if (e == hipSuccess)
+        e = launch_pack<3>(pack_src{dY, ldy, N, ldy % 4 == 0 && aligned16(dY), G.A},
+                           pack_src{X, ldx, K, ldx % 4 == 0 && aligned16(X), G.B}, B, s);
+    if (e != hipSuccess) return e;
+    G.M = N; G.Nn = K; G.Kr = B;
+    G.a32 = dY; G.lda = ldy; G.b32 = X; G.ldb = ldx;
+    G.split_steps = G.A.steps;
+    G.C = gv;
+    G.P.mask = mask; G.P.pos = pos; G.P.kw = (int)ceil_div(K, 32);
+    return launch_tiles<3, kEpiMask, kAccTree>(G, 1, s);
+}
+
+// Y = W . X with W's zeros written out: N * K * B products on the matrix cores
+// instead of nnz * B on the vector units.  Taken where the modelled time is
+// shorter than the sparse kernels' (both in us, fitted to calls on the chip):
+// the tiled kernel costs 60 us of planning and tile passes and 1 us per 12 M
+// products, the row kernel (under 1.7e8 products, or rows that are not 16-byte
+// aligned) 1 us per 4.5 M or 2.7 M; this one packs 6 bytes per weight and 10 per
+// activation, multiplies whole tiles and adds split sums.  Measured, sparse ->
+// packed: 4096 x 4096 x 512 at 5 % stored 108 -> 105, 10 % 126 -> 107, 20 % 197 ->
+// 114, 50 % 316 -> 128; 4096 x 9216 x 1024 at 9 % 357 -> 401 (W^T 299 -> 445);
+// 2049 x 3001 x 333 at 30 % 225 -> 59; 2000 x 700 x 1000 at 25 % 66 -> 39.
+namespace {
+wgrad_split spmm_splits(int N, int K, int B) {  // ranges of whole 256-index blocks, about 512 workgroups
+    const int64_t tiles = ceil_div(N, BM) * ceil_div(B, BN), kb = ceil_div(K, kPackK);
+    int64_t s = tiles >= 384 ? 1 : ceil_div(512, tiles);
+    s = s < kb ? s : kb;
+    const int64_t per = ceil_div(kb, s > 0 ? s : 1);
+    return wgrad_split{(int)ceil_div(kb, per), (int)per * kPackK};
+}
+}  // namespace
+
+size_t packed_spmm_bytes(int N, int K, int64_t nnz, int B) {
+    if (N == 0 || K == 0 || B < 32 || K > (1 << 22)) return 0;
+    const wgrad_split w = spmm_splits(N, K, B);
+    const double np = (double)ceil_div(N, BM) * BM, bp = (double)ceil_div(B, BN) * BN, nk = (double)N * K;
+    const double mfma = 12 * np * K * bp / 1.36e9, stream = 6 * nk / 3.5e6;
+    const double packed_us = 28 + 0.85 * ((6 * nk + 10.0 * K * B) / 4.8e6 + (mfma > stream ? mfma : stream) +
+                                          (w.splits > 1 ? 8.0 * w.splits * N * B / 6.9e6 : 0));
+    const double products = (double)nnz * B;
+    const double sparse_us = B % 4 ? 5 + products / 2.7e6
+                                   : (products < 1.7e8 ? 5 + products / 4.5e6 : 60 + products / 12e6);
+    if (packed_us > 0.95 * sparse_us) return 0;
+    return (size_t)(packed_bytes(N, K, 3) + flag_bytes(N, K) + packed_bytes(B, K, 3) + flag_bytes(B, K)) +
+           (w.splits > 1 ? sizeof(float) * (size_t)w.splits * N * B : 0);
+}
+
+hipError_t launch_packed_spmm(int N, int K, const int *ptr, const int *idx, const float *vals, const float *X,
+                              int64_t ldx, int B, float *Y, int64_t ldy, void *ws, hipStream_t s) {
+    char *p = static_cast<char *>(ws);
+    gemm_args G{};
+    G.A = carve_packed(p, N, K, 3);
+    G.B = carve_packed(p, B, K, 3);
+    dim3 grid((unsigned)(G.A.groups + G.B.groups), (unsigned)G.A.kblocks);
+    pack_spmm_kernel<<<grid, 256, 0, s>>>(N, ptr, idx, vals, G.A, X, ldx, K, B, G.B);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    const wgrad_split w = spmm_splits(N, K, B);
+    G.M = N; G.Nn = B; G.Kr = K;
+    G.b32 = X; G.ldb = ldx;
+    G.ptr = ptr; G.idx = idx; G.vals = vals;
+    G.split_steps = w.chunk / kStep;
+    float *parts = reinterpret_cast<float *>(p);
+    G.C = w.splits > 1 ? parts : Y;
+    G.ldc = w.splits > 1 ? B : ldy;
+    e = launch_tiles<3, kEpiSpmm, kAccSmall>(G, w.splits, s);
+    if (e != hipSuccess || w.splits == 1) return e;
+    return launch_wgrad_reduce(N, B, w.splits, parts, Y, ldy, s);
 }
 
 }  // namespace l1csr

@@ -1,0 +1,97 @@
+"""GPU: products over dense patterns on packed operands (csr_spmm_fwd, csr_spmm_bwd_t
+and sddmm_masked_wgrad with the packed workspace) against 64-bit references: tile and
+step edges, power-law and empty rows, split reductions, operands outside the parts'
+range, and the same bits from the planned calls."""
+import numpy as np
+import pytest
+
+import paper_1905_07931_amd as L1
+from paper_1905_07931_amd import synth
+from _helpers import bits_equal, h, t
+
+pytestmark = pytest.mark.gpu
+
+
+def layer(N, K, B, density, seed=0, pattern="uniform", empty=True):
+    rng = np.random.default_rng(seed)
+    if pattern == "zipf":
+        rp, ci = synth.zipf_pattern(rng, N, K, int(density * N * K))
+    else:
+        mask = rng.random((N, K)) < density
+        if empty:
+            mask[N // 3] = False
+            mask[:, K // 2] = False
+            mask[N - 1] = True
+        rp = np.concatenate([[0], np.cumsum(mask.sum(1))]).astype(np.int32)
+        ci = np.nonzero(mask)[1].astype(np.int32)
+    v = (rng.standard_normal(len(ci)) * 0.1).astype(np.float32)
+    dense = np.zeros((N, K))
+    dense[np.repeat(np.arange(N), np.diff(rp)), ci] = v
+    X, dY = rng.random((K, B)).astype(np.float32), rng.standard_normal((N, B)).astype(np.float32)
+    return L1.CSR.from_host(rp, ci, v, K), dense, rp, ci, X, dY
+
+
+def bound(terms):
+    # the terms left out of a product (2^-22), then a rounding per summed term
+    return 2.0 ** -22 + (terms / 16 + 96) * 2.0 ** -24
+
+
+SHAPES = [(1024, 1024, 384, 0.4, "uniform"), (1025, 1281, 333, 0.3, "uniform"), (1537, 1000, 1001, 0.25, "zipf"),
+          (2049, 2305, 130, 0.3, "uniform"), (300, 4097, 515, 0.5, "uniform")]
+
+
+@pytest.mark.parametrize("N,K,B,d,pattern", SHAPES)
+def test_packed_products(N, K, B, d, pattern):
+    W, dense, rp, ci, X, dY = layer(N, K, B, d, seed=N + B, pattern=pattern)
+    assert L1.workspace_bytes(L1.OP_SPMM_PACKED, N, K, W.nnz, B) > 0
+    assert L1.workspace_bytes(L1.OP_SPMM_PACKED, K, N, W.nnz, B) > 0
+    Xd, dYd = t(X), t(dY)
+    Y = L1.csr_spmm_fwd(W, Xd)
+    assert (np.abs(h(Y) - dense @ X) <= bound(6 * K) * (np.abs(dense) @ np.abs(X))).all()
+    csc = L1.csc_build(W)
+    dX = L1.csr_spmm_bwd_t(W, dYd, csc)
+    assert (np.abs(h(dX) - dense.T @ dY) <= bound(6 * N) * (np.abs(dense).T @ np.abs(dY))).all()
+    # again, planned, and into padded rows: the same bits
+    import torch
+    assert bits_equal(h(L1.csr_spmm_planned(W, Xd, L1.csr_spmm_plan(W, B))), h(Y))
+    assert bits_equal(h(L1.csr_spmm_bwd_t_planned(W, dYd, csc, L1.csr_spmm_bwd_t_plan(W, csc, B))), h(dX))
+    wide = torch.full((N, B + 3), 7.0, device="cuda")
+    L1.csr_spmm_fwd(W, Xd, wide[:, :B])
+    assert bits_equal(h(wide[:, :B].contiguous()), h(Y)) and bool((wide[:, B:] == 7.0).all())
+
+
+@pytest.mark.parametrize("N,K,B,d,pattern", [(1024, 2048, 256, 0.4, "uniform"), (2049, 3001, 97, 0.3, "uniform"),
+                                             (2177, 2050, 333, 0.25, "zipf")])
+def test_packed_masked_gradient(N, K, B, d, pattern):
+    W, dense, rp, ci, X, dY = layer(N, K, B, d, seed=B, pattern=pattern)
+    assert L1.workspace_bytes(L1.OP_SDDMM_PACKED, N, K, W.nnz, B) > 0
+    import torch
+    gv = torch.full((W.nnz + 5,), 3.0, device="cuda")  # entries past the pattern stay
+    L1.sddmm_masked_wgrad(W, t(dY), t(X), gv)
+    rows = np.repeat(np.arange(N), np.diff(rp))
+    ref = (dY.astype(np.float64) @ X.astype(np.float64).T)[rows, ci]
+    m = (np.abs(dY).astype(np.float64) @ np.abs(X).astype(np.float64).T)[rows, ci]
+    assert (np.abs(h(gv)[:W.nnz] - ref) <= bound(6 * B) * m).all()
+    assert bool((gv[W.nnz:] == 3.0).all())
+
+
+def test_packed_products_odd_values():
+    # values no three bf16 parts hold: the stored entries alone are summed, so an
+    # infinity meets only the rows that store its column
+    N, K, B = 1024, 1100, 500
+    W, dense, rp, ci, X, dY = layer(N, K, B, 0.4, seed=9)
+    assert L1.workspace_bytes(L1.OP_SPMM_PACKED, N, K, W.nnz, B) > 0
+    X[17, 5], X[1000, 299], X[40, 130] = np.inf, np.nan, 3e38
+    X[:, 200] *= np.float32(2.0 ** -115)
+    got = h(L1.csr_spmm_fwd(W, t(X))).astype(np.float64)
+    with np.errstate(invalid="ignore", over="ignore"):
+        ref = np.zeros((N, B), np.float64)
+        for i in range(N):
+            s = slice(rp[i], rp[i + 1])
+            ref[i] = (dense[i, ci[s]][:, None] * X[ci[s]].astype(np.float64)).sum(axis=0)
+        ref = ref.astype(np.float32)
+    assert np.array_equal(np.isnan(got), np.isnan(ref))
+    assert np.array_equal(got[np.isinf(ref)], ref[np.isinf(ref)])
+    ok = np.isfinite(ref)
+    m = np.abs(dense) @ np.where(np.isfinite(X), np.abs(X.astype(np.float64)), 0)
+    assert (np.abs(got[ok] - ref[ok]) <= 1e-4 * m[ok] + 2.0 ** -149 * K).all()
