@@ -52,6 +52,17 @@ struct vec_t<1> {
     static __device__ __forceinline__ void vmax(T &a, T x) { a = x > a ? x : a; }
 };
 template <>
+struct vec_t<2> {
+    typedef float2 T;
+    static __device__ __forceinline__ T load(const float *p) { return *reinterpret_cast<const float2 *>(p); }
+    static __device__ __forceinline__ void store(float *p, T v) { *reinterpret_cast<float2 *>(p) = v; }
+    static __device__ __forceinline__ void fma(T &a, float w, T x) {
+        a.x = fmaf(w, x.x, a.x);
+        a.y = fmaf(w, x.y, a.y);
+    }
+    static __device__ __forceinline__ T zero() { return make_float2(0.f, 0.f); }
+};
+template <>
 struct vec_t<4> {
     typedef float4 T;
     static __device__ __forceinline__ T load(const float *p) { return *reinterpret_cast<const float4 *>(p); }
@@ -214,6 +225,156 @@ __global__ __launch_bounds__(kThreads) void conv_bwd_kernel(geom_t g, int B, con
     }
 }
 
+constexpr int wave_positions(bool bwd) { return bwd ? 1 : 2; }
+
+// Both products for batches that fill a wave's lanes: a wave takes PB
+// consecutive output positions of a channel and 64 * VEC batch columns, so an
+// entry's input row is the same for the whole wave.  The index arithmetic runs
+// with an entry per lane, 64 at a time (the thread-per-output kernels above
+// repeat it in every thread, 4 divisions an entry in the backward one), and a
+// ballot drops the entries that fall outside the map; the rows and values of
+// the others are then read from their lanes as scalars, and the loads of NB
+// entries at PB positions are in flight together (an entry outside the map for
+// one of the positions loads row 0 and is skipped).  Entries are summed in the order of
+// the kernels above, so the bits are theirs.  Bound by the gathers through L1 and
+// L2 (1 KB per entry and position) and, where a channel has few entries, by the
+// stores.  conv2 of LeNet-5 at batch 256, thread-per-output -> this kernel: 17.7
+// -> 12.8 us forward, 56.6 -> 15.8 backward; at 1024 33.2 -> 27.6 and 117 -> 47; its
+// conv1 forward at 1024 34.7 -> 22.8.  Two positions and four entries a time
+// forward, one and eight backward (its neighbours' valid entries differ): conv1
+// forward with one and eight 30.1, conv2 backward with two and eight 21.8.
+template <int VEC, bool BWD>
+__global__ __launch_bounds__(kThreads) void conv_wave_kernel(geom_t g, int B, int chunks,
+                                                             const int *__restrict__ ptr,
+                                                             const int *__restrict__ idx,
+                                                             const float *__restrict__ vals,
+                                                             const float *__restrict__ in, int64_t ldi,
+                                                             float *__restrict__ out, int64_t ldo, int tasks) {
+    typedef vec_t<VEC> V;
+    constexpr int kPB = wave_positions(BWD), kNB = BWD ? 8 : 4;
+    __shared__ int map_s[kStage];  // first row of the entry's input map
+    __shared__ int khw_s[kStage];
+    __shared__ float w_s[kStage];
+    __shared__ int cp_s[BWD ? kMaxKK + 1 : 1];
+    const int ch = blockIdx.x, kk = g.KH * g.KW;
+    const int lane = threadIdx.x & 63, wave = uniform(threadIdx.x >> 6);
+    int s, e;
+    if constexpr (BWD) {  // the column pointers of this channel's KH*KW filter columns (kk <= kMaxKK)
+        for (int c = threadIdx.x; c <= kk; c += kThreads) cp_s[c] = ptr[ch * kk + c];
+        __syncthreads();
+        s = uniform(cp_s[0]);
+        e = uniform(cp_s[kk]);
+    } else {
+        s = ptr[ch];
+        e = ptr[ch + 1];
+    }
+    auto stage = [&](int p0, int n) {
+        __syncthreads();  // the previous entries are consumed
+        for (int i = threadIdx.x; i < n; i += kThreads) {
+            const int q = p0 + i;
+            int fc;  // filter position kh * KW + kw
+            if constexpr (BWD) {
+                int lo = 0, hi = kk - 1;  // last c with cp_s[c] <= q
+                while (lo < hi) {
+                    const int mid = (lo + hi + 1) >> 1;
+                    if (cp_s[mid] <= q) lo = mid; else hi = mid - 1;
+                }
+                fc = lo;
+                map_s[i] = idx[q] * g.OH * g.OW;
+            } else {
+                const int col = idx[q], ci = col / kk;
+                fc = col - ci * kk;
+                map_s[i] = ci * g.H * g.W;
+            }
+            const int kh = fc / g.KW;
+            khw_s[i] = (kh << 16) | (fc - kh * g.KW);
+            w_s[i] = vals[q];
+        }
+        __syncthreads();
+    };
+    const bool one_pass = e - s <= kStage;
+    if (one_pass) stage(s, e - s);
+    const int ow_ = BWD ? g.W : g.OW, npos = ow_ * (BWD ? g.H : g.OH);
+    // (a uniform trip count: every wave of the workgroup stages)
+    for (int t0 = blockIdx.y * (kThreads / kWave); t0 < tasks; t0 += gridDim.y * (kThreads / kWave)) {
+        const int t = t0 + wave;
+        const bool live = t < tasks;
+        const int pg = t / chunks, b = (t - pg * chunks) * (kWave * VEC) + lane * VEC;
+        const bool active = live && b < B;
+        const int bl = active ? b : 0;
+        int oh[kPB], ow[kPB];
+        typename V::T acc[kPB];
+#pragma unroll
+        for (int j = 0; j < kPB; ++j) {
+            const int pos = pg * kPB + j;
+            oh[j] = pos / ow_;
+            ow[j] = pos - oh[j] * ow_;
+            acc[j] = V::zero();
+        }
+        for (int p0 = s; p0 < e; p0 += kStage) {
+            const int n = min(kStage, e - p0);
+            if (!one_pass) stage(p0, n);
+            if (!live) continue;
+            for (int e0 = 0; e0 < n; e0 += kWave) {
+                const int i = e0 + lane < n ? e0 + lane : n - 1;
+                const int kh = khw_s[i] >> 16, kw = khw_s[i] & 0xffff, map = map_s[i];
+                const float w = w_s[i];
+                int row[kPB];  // this lane's entry: its input row for position j, -1 outside the map
+                uint64_t todo = 0;
+#pragma unroll
+                for (int j = 0; j < kPB; ++j) {
+                    bool ok = e0 + lane < n && pg * kPB + j < npos;
+                    int r, c;
+                    if constexpr (BWD) {
+                        const int th = oh[j] + g.PH - kh, tw = ow[j] + g.PW - kw;  // oh*SH, ow*SW
+                        r = th;
+                        c = tw;
+                        if (g.SH > 1 || g.SW > 1) {
+                            r = th / g.SH;
+                            c = tw / g.SW;
+                            ok = ok && r * g.SH == th && c * g.SW == tw;
+                        }
+                        ok = ok && th >= 0 && tw >= 0 && r < g.OH && c < g.OW;
+                        row[j] = ok ? map + r * g.OW + c : -1;
+                    } else {
+                        r = oh[j] * g.SH - g.PH + kh;
+                        c = ow[j] * g.SW - g.PW + kw;
+                        ok = ok && r >= 0 && r < g.H && c >= 0 && c < g.W;
+                        row[j] = ok ? map + r * g.W + c : -1;
+                    }
+                    todo |= wave_ballot(ok);
+                }
+                while (todo) {
+                    typename V::T x[kNB][kPB];
+                    int rr[kNB][kPB];
+                    float ww[kNB];
+#pragma unroll
+                    for (int u = 0; u < kNB; ++u) {
+                        const int src = todo ? __builtin_ctzll(todo) : 0;
+                        const bool have = todo != 0;
+                        todo &= todo - 1;
+                        ww[u] = lane_bcast(w, src);
+#pragma unroll
+                        for (int j = 0; j < kPB; ++j) {
+                            rr[u][j] = have ? lane_bcast(row[j], src) : -1;
+                            x[u][j] = V::load(in + (rr[u][j] >= 0 ? rr[u][j] : 0) * ldi + bl);
+                        }
+                    }
+#pragma unroll
+                    for (int u = 0; u < kNB; ++u)
+#pragma unroll
+                        for (int j = 0; j < kPB; ++j)
+                            if (rr[u][j] >= 0) V::fma(acc[j], ww[u], x[u][j]);
+                }
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < kPB; ++j)
+            if (active && pg * kPB + j < npos)
+                V::store(out + ((int64_t)ch * npos + pg * kPB + j) * ldo + b, acc[j]);
+    }
+}
+
 // im2col: row r = (ci, kh, kw) of the lowered operand, flattened columns
 // f = pos*B + b; VEC consecutive f per thread (one position).
 template <int VEC>
@@ -272,6 +433,41 @@ int64_t slice_blocks(int64_t slices, int64_t channels) {
     return slices < 65535 ? (slices < 1 ? 1 : slices) : 65535;
 }
 
+// Floats per lane of the wave kernel, 0 for the thread-per-output kernels: the
+// widest vector the alignment allows that keeps three quarters of the lanes
+// busy, else single floats where that keeps more than half of them busy.
+// Forward, vectors of four against four a thread in the other kernel, or single
+// floats against single floats: with narrower vectors than the other kernel's
+// it was slower (128 -> 40 channels 20 x 20, batch 128: 212 -> 263 us).  Backward
+// the other kernel's index arithmetic costs more than that (527 -> 301), up to a
+// batch of 40 in 64 lanes (158 -> 198).
+int wave_vec(bool bwd, int B, int64_t lda, const void *a, int64_t ldb, const void *b) {
+    const bool v4 = vec4_ok(B, lda, a, ldb, b);
+    for (int v = 4; v >= 1; v /= 2) {
+        if (v > 1 && (B % v || lda % v || ldb % v || (uintptr_t)a % (4 * v) || (uintptr_t)b % (4 * v))) continue;
+        const double used = (double)B / (double)(ceil_div(B, kWave * v) * kWave * v);
+        if (used >= 0.75 || (v == 1 && used >= 0.55 && B > kWave)) return bwd || v == 4 || !v4 ? v : 0;
+    }
+    return 0;
+}
+
+template <bool BWD>
+hipError_t launch_wave(int vec, const geom_t &g, int channels, int B, const int *ptr, const int *idx, const float *vals,
+                       const float *in, int64_t ldi, float *out, int64_t ldo, hipStream_t s) {
+    const int64_t npos = BWD ? (int64_t)g.H * g.W : (int64_t)g.OH * g.OW;
+    const int chunks = (int)ceil_div(B, kWave * vec);
+    const int64_t tasks = ceil_div(npos, wave_positions(BWD)) * chunks;
+    if (tasks > INT32_MAX - 65535 * 4 || channels > kMaxGridX) return hipErrorInvalidConfiguration;
+    const dim3 grid((unsigned)channels, (unsigned)slice_blocks(ceil_div(tasks, kThreads / kWave), channels));
+    if (vec == 4)
+        conv_wave_kernel<4, BWD><<<grid, kThreads, 0, s>>>(g, B, chunks, ptr, idx, vals, in, ldi, out, ldo, (int)tasks);
+    else if (vec == 2)
+        conv_wave_kernel<2, BWD><<<grid, kThreads, 0, s>>>(g, B, chunks, ptr, idx, vals, in, ldi, out, ldo, (int)tasks);
+    else
+        conv_wave_kernel<1, BWD><<<grid, kThreads, 0, s>>>(g, B, chunks, ptr, idx, vals, in, ldi, out, ldo, (int)tasks);
+    return hipGetLastError();
+}
+
 }  // namespace
 
 bool conv_out_dims(const conv_geom &g, int *OH, int *OW) {
@@ -292,6 +488,8 @@ hipError_t launch_conv_fwd(const conv_geom &cg, int N, int B, const int *ptr, co
     const geom_t g = to_geom(cg);
     const int64_t F = (int64_t)g.OH * g.OW * B;
     if (N == 0 || F == 0) return hipSuccess;
+    if (const int vec = wave_vec(false, B, ldx, X, ldy, Y))
+        return launch_wave<false>(vec, g, N, B, ptr, idx, vals, X, ldx, Y, ldy, s);
     const bool v4 = vec4_ok(B, ldx, X, ldy, Y);
     const int64_t sl = slices_of(F, v4 ? 4 : 1);
     if (sl > INT32_MAX || N > kMaxGridX) return hipErrorInvalidConfiguration;
@@ -310,6 +508,8 @@ hipError_t launch_conv_bwd_data(const conv_geom &cg, int N, int B, const int *co
     const int64_t F = (int64_t)g.H * g.W * B;
     if (F == 0) return hipSuccess;
     (void)N;
+    if (const int vec = wave_vec(true, B, ldy, dY, ldx, dX))
+        return launch_wave<true>(vec, g, g.C, B, col_ptr, row_idx, vals_t, dY, ldy, dX, ldx, s);
     const bool v4 = vec4_ok(B, ldy, dY, ldx, dX);
     const int64_t sl = slices_of(F, v4 ? 4 : 1);
     if (sl > INT32_MAX || g.C > kMaxGridX) return hipErrorInvalidConfiguration;
