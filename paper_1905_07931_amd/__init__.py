@@ -138,9 +138,15 @@ def _spmm_bytes(n_rows, n_cols, nnz, B):
 # marshalling helpers
 # ---------------------------------------------------------------------------
 
+_torch_module = None
+
+
 def _torch():
-    import torch
-    return torch
+    global _torch_module
+    if _torch_module is None:
+        import torch
+        _torch_module = torch
+    return _torch_module
 
 
 def _check(rc, name):
@@ -149,7 +155,7 @@ def _check(rc, name):
 
 
 def _p(t):
-    return None if t is None else C.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 class _HostWord:
@@ -214,7 +220,7 @@ def _nnz_word(out):
 
 def _nnz_dev(out):
     w = _nnz_word(out)
-    return None if w is None else C.c_void_p(w.dev)
+    return None if w is None else w.dev
 
 
 def _set_nnz(out, need, stream):
@@ -243,14 +249,21 @@ def _set_nnz(out, need, stream):
     out._pending = (w, ev)
 
 
+def _raw_stream(device_index):
+    """The handle of a device's current stream, without a Stream object around it."""
+    return _torch()._C._cuda_getCurrentRawStream(device_index)
+
+
 def _stream(stream=None):
-    torch = _torch()
-    s = torch.cuda.current_stream() if stream is None else stream
-    return C.c_void_p(s.cuda_stream)
+    if stream is not None:
+        return stream.cuda_stream
+    return _raw_stream(_torch().cuda.current_device())
 
 
 def _dev(t, dtype, name):
-    torch = _torch()
+    torch = _torch_module or _torch()
+    if isinstance(t, torch.Tensor) and t.is_cuda and t.dtype is dtype:
+        return t
     if not isinstance(t, torch.Tensor):
         raise TypeError(f"{name} must be a torch.Tensor")
     if t.device.type != "cuda":
@@ -262,22 +275,22 @@ def _dev(t, dtype, name):
 
 def _vec(t, dtype, name):
     _dev(t, dtype, name)
-    if t.dim() != 1 or (t.numel() > 1 and t.stride(0) != 1):
+    if t.dim() != 1 or (t.stride()[0] != 1 and t.numel() > 1):
         raise ValueError(f"{name} must be a contiguous 1-D tensor")
     return t
 
 
 def _mat(t, name):
     """A [rows][ld] float32 matrix with unit column stride; returns (rows, cols, ld)."""
-    torch = _torch()
-    _dev(t, torch.float32, name)
-    if t.dim() != 2:
+    _dev(t, (_torch_module or _torch()).float32, name)
+    shape = t.shape
+    if len(shape) != 2:
         raise ValueError(f"{name} must be 2-D")
-    rows, cols = t.shape
-    if cols > 1 and t.stride(1) != 1:
+    rows, cols = shape
+    ld, unit = t.stride()
+    if unit != 1 and cols > 1:
         raise ValueError(f"{name} must have a contiguous last dimension")
-    ld = t.stride(0) if rows > 1 else max(cols, 1)
-    return rows, cols, ld
+    return rows, cols, ld if rows > 1 else max(cols, 1)
 
 
 _ws_cache: dict = {}
@@ -290,12 +303,12 @@ def _workspace(nbytes, device, stream=None):
     reuses it only in that stream's order once it is replaced."""
     if nbytes == 0:
         return None, 0
-    torch = _torch()
-    s = torch.cuda.current_stream(device) if stream is None else stream
-    key = (device.index, s.cuda_stream)
+    index = device.index
+    key = (index, _raw_stream(index) if stream is None else stream.cuda_stream)
     buf = _ws_cache.get(key)
     if buf is None or buf.numel() < nbytes:
-        with torch.cuda.stream(s):
+        torch = _torch()
+        with torch.cuda.stream(torch.cuda.current_stream(device) if stream is None else stream):
             buf = torch.empty(nbytes, dtype=torch.uint8, device=device)
         _ws_cache[key] = buf
     return buf, nbytes
@@ -919,7 +932,13 @@ class ConvGeom:
         return self.C * self.KH * self.KW
 
     def _arr(self):
-        return (C.c_int32 * 9)(self.C, self.H, self.W, self.KH, self.KW, self.SH, self.SW, self.PH, self.PW)
+        return _geom_array(self.C, self.H, self.W, self.KH, self.KW, self.SH, self.SW, self.PH, self.PW)
+
+
+@functools.lru_cache(maxsize=256)
+def _geom_array(*sizes):
+    """The calls' geometry argument (only ever read) for these sizes."""
+    return (C.c_int32 * 9)(*sizes)
 
 
 def csr_conv_fwd(g: ConvGeom, W: CSR, X, Y=None, stream=None):
