@@ -117,8 +117,8 @@ __global__ __launch_bounds__(kCscThreads) void csc_emit_kernel(int n_rows, int n
                                                                int *__restrict__ perm,
                                                                float *__restrict__ vals_t) {
     constexpr int NW = kCscThreads / kWave, G = kWaveRows / kWave;
-    __shared__ int start[NW + 1][32];  // [j][c]: column c's entries of waves < j (row NW: block total)
-    __shared__ int64_t dst0[32];       // first output position of column c's entries of this block
+    __shared__ int start[NW + 1][kRunCols];  // [j][c]: column c's entries of waves < j (row NW: block total)
+    __shared__ int64_t dst0[kRunCols];       // first output position of column c's entries of this block
     __shared__ int run_row[kRunCols][kRunCap];
     __shared__ int run_p[kRunCols][kRunCap];
     int64_t item = blockIdx.x;
@@ -126,13 +126,18 @@ __global__ __launch_bounds__(kCscThreads) void csc_emit_kernel(int n_rows, int n
         const int64_t total = (int64_t)gridDim.x, per = total / 8;
         if (item < per * 8) item = (item % 8) * per + item / 8;
     }
-    const int rb = (int)(item / kw), w = (int)(item - (int64_t)rb * kw);
+    const int kq = kw * (32 / kRunCols);
+    const int rb = (int)(item / kq), wq = (int)(item - (int64_t)rb * kq);
+    const int w = wq / (32 / kRunCols), c0 = (wq - w * (32 / kRunCols)) * kRunCols;  // word, first column inside it
     const int r0 = rb * kRowBlock, r1 = min(n_rows, r0 + kRowBlock);
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int nc = min(32, n_cols - 32 * w);
+    const int nc = min(kRunCols, n_cols - 32 * w - c0);  // columns of this workgroup (<= 0 past the last)
+    if (nc <= 0) return;
     const int64_t o = (int64_t)w * n_rows;
-    if (threadIdx.x < nc)
-        dst0[threadIdx.x] = (int64_t)col_ptr[32 * w + threadIdx.x] + cnt[(int64_t)rb * n_cols + 32 * w + threadIdx.x];
+    if (threadIdx.x < nc) {
+        const int c = 32 * w + c0 + threadIdx.x;
+        dst0[threadIdx.x] = (int64_t)col_ptr[c] + (cnt ? cnt[(int64_t)rb * n_cols + c] : 0);
+    }
     unsigned m[G];
     int ps[G];
 #pragma unroll
@@ -143,15 +148,15 @@ __global__ __launch_bounds__(kCscThreads) void csc_emit_kernel(int n_rows, int n
     }
     int mine = 0;
 #pragma unroll
-    for (int c = 0; c < 32; ++c) {
+    for (int c = 0; c < kRunCols; ++c) {
         int n = 0;
 #pragma unroll
-        for (int g = 0; g < G; ++g) n += __popcll(__ballot((m[g] >> c) & 1u));
+        for (int g = 0; g < G; ++g) n += __popcll(__ballot((m[g] >> (c0 + c)) & 1u));
         mine = lane == c ? n : mine;
     }
-    if (lane < 32) start[wave][lane] = mine;
+    if (lane < kRunCols) start[wave][lane] = mine;
     __syncthreads();
-    if (threadIdx.x < 32) {  // exclusive scan over the waves (relative to the block's run)
+    if (threadIdx.x < kRunCols) {  // exclusive scan over the waves (relative to the block's run)
         int run = 0;
 #pragma unroll
         for (int j = 0; j < NW; ++j) {
@@ -162,66 +167,62 @@ __global__ __launch_bounds__(kCscThreads) void csc_emit_kernel(int n_rows, int n
         start[NW][threadIdx.x] = run;
     }
     __syncthreads();
-    for (int c0 = 0; c0 < nc; c0 += kRunCols) {
 #pragma unroll
-        for (int cc = 0; cc < kRunCols; ++cc) {
-            const int c = c0 + cc;
-            if (c >= nc) break;  // uniform
-            const unsigned below = (1u << c) - 1u;
-            int q0 = start[wave][c];
+    for (int cc = 0; cc < kRunCols; ++cc) {
+        if (cc >= nc) break;  // uniform
+        const unsigned below = (1u << (c0 + cc)) - 1u;
+        int q0 = start[wave][cc];
 #pragma unroll
-            for (int g = 0; g < G; ++g) {
-                const bool set = (m[g] >> c) & 1u;
-                const uint64_t b = __ballot(set);
-                if (set) {
-                    const int q = q0 + popc_below(b);
-                    const int row = r0 + wave * kWaveRows + g * kWave + lane;
-                    const int p = ps[g] + __popc(m[g] & below);
-                    if (q < kRunCap) {
-                        run_row[cc][q] = row;
-                        run_p[cc][q] = p;
-                    } else {  // beyond the staged run: straight to the output
-                        const int64_t d = dst0[c] + q;
-                        row_idx[d] = row;
-                        perm[d] = p;
-                        vals_t[d] = vals[p];
-                    }
+        for (int g = 0; g < G; ++g) {
+            const bool set = (m[g] >> (c0 + cc)) & 1u;
+            const uint64_t b = __ballot(set);
+            if (set) {
+                const int q = q0 + popc_below(b);
+                const int row = r0 + wave * kWaveRows + g * kWave + lane;
+                const int p = ps[g] + __popc(m[g] & below);
+                if (q < kRunCap) {
+                    run_row[cc][q] = row;
+                    run_p[cc][q] = p;
+                } else {  // beyond the staged run: straight to the output
+                    const int64_t d = dst0[cc] + q;
+                    row_idx[d] = row;
+                    perm[d] = p;
+                    vals_t[d] = vals[p];
                 }
-                q0 += __popcll(b);
             }
+            q0 += __popcll(b);
         }
-        __syncthreads();
-        // the staged runs of the chunk's columns back to back: entry i of the
-        // sequence is entry i - roff[cc] of column cc's run
-        int roff[kRunCols + 1];
-        roff[0] = 0;
+    }
+    __syncthreads();
+    // the staged runs of the chunk's columns back to back: entry i of the
+    // sequence is entry i - roff[cc] of column cc's run
+    int roff[kRunCols + 1];
+    roff[0] = 0;
 #pragma unroll
-        for (int cc = 0; cc < kRunCols; ++cc)
-            roff[cc + 1] = roff[cc] + (c0 + cc < nc ? min(kRunCap, start[NW][c0 + cc]) : 0);
-        int qc[kRunPer], pv[kRunPer];
-        float vv[kRunPer];
+    for (int cc = 0; cc < kRunCols; ++cc)
+        roff[cc + 1] = roff[cc] + (cc < nc ? min(kRunCap, start[NW][cc]) : 0);
+    int qc[kRunPer], pv[kRunPer];
+    float vv[kRunPer];
 #pragma unroll
-        for (int u = 0; u < kRunPer; ++u) {
-            const int i = threadIdx.x + u * kCscThreads;
-            int cc = 0;
+    for (int u = 0; u < kRunPer; ++u) {
+        const int i = threadIdx.x + u * kCscThreads;
+        int cc = 0;
 #pragma unroll
-            for (int j = 1; j < kRunCols; ++j) cc += i >= roff[j] ? 1 : 0;
-            qc[u] = i < roff[kRunCols] ? (cc << 16) | (i - roff[cc]) : -1;
-            if (qc[u] >= 0) {
-                pv[u] = run_p[cc][i - roff[cc]];
-                vv[u] = vals[pv[u]];
-            }
+        for (int j = 1; j < kRunCols; ++j) cc += i >= roff[j] ? 1 : 0;
+        qc[u] = i < roff[kRunCols] ? (cc << 16) | (i - roff[cc]) : -1;
+        if (qc[u] >= 0) {
+            pv[u] = run_p[cc][i - roff[cc]];
+            vv[u] = vals[pv[u]];
         }
+    }
 #pragma unroll
-        for (int u = 0; u < kRunPer; ++u) {
-            if (qc[u] < 0) continue;
-            const int cc = qc[u] >> 16, q = qc[u] & 0xffff;
-            const int64_t d = dst0[c0 + cc] + q;
-            row_idx[d] = run_row[cc][q];
-            perm[d] = pv[u];
-            vals_t[d] = vv[u];
-        }
-        __syncthreads();  // the runs are refilled by the next columns
+    for (int u = 0; u < kRunPer; ++u) {
+        if (qc[u] < 0) continue;
+        const int cc = qc[u] >> 16, q = qc[u] & 0xffff;
+        const int64_t d = dst0[cc] + q;
+        row_idx[d] = run_row[cc][q];
+        perm[d] = pv[u];
+        vals_t[d] = vv[u];
     }
 }
 
@@ -252,7 +253,7 @@ csc_layout layout(int n_rows, int n_cols) {
 }  // namespace
 
 bool csc_grid_fits(int n_rows, int n_cols) {
-    return ceil_div(n_cols, 32) * ceil_div(n_rows, kRowBlock) <= INT32_MAX && ceil_div(n_rows, kRowBlock) <= 65535;
+    return ceil_div(n_cols, 32) * ceil_div(n_rows, kRowBlock) <= INT32_MAX / (32 / kRunCols) && ceil_div(n_rows, kRowBlock) <= 65535;
 }
 
 size_t csc_workspace_bytes(int n_rows, int n_cols, int64_t nnz) {
@@ -278,15 +279,19 @@ hipError_t launch_csc_build(int n_rows, int n_cols, int64_t nnz, const int *ptr,
         mask = m;
         pos = p;
     }
+    // up to 1024 rows are one row block: its counts are the columns' totals
+    const bool one = l.n_blocks == 1;
     dim3 grid(l.kw, l.n_blocks);
-    csc_count_kernel<<<grid, kCscThreads, 0, s>>>(n_rows, n_cols, mask, cnt);
+    csc_count_kernel<<<grid, kCscThreads, 0, s>>>(n_rows, n_cols, mask, one ? tot : cnt);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    csc_colscan_kernel<<<(unsigned)ceil_div(n_cols, 256), 256, 0, s>>>(l.n_blocks, n_cols, cnt, tot);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
+    if (!one) {
+        csc_colscan_kernel<<<(unsigned)ceil_div(n_cols, 256), 256, 0, s>>>(l.n_blocks, n_cols, cnt, tot);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+    }
     if ((e = launch_exclusive_scan(tot, col_ptr, n_cols, nullptr, s)) != hipSuccess) return e;
     if (nnz == 0) return hipSuccess;
-    csc_emit_kernel<<<(unsigned)((int64_t)l.kw * l.n_blocks), kCscThreads, 0, s>>>(
-        n_rows, n_cols, l.kw, mask, pos, vals, cnt, col_ptr, row_idx, perm, vals_t);
+    csc_emit_kernel<<<(unsigned)((int64_t)l.kw * l.n_blocks * (32 / kRunCols)), kCscThreads, 0, s>>>(
+        n_rows, n_cols, l.kw, mask, pos, vals, one ? nullptr : cnt, col_ptr, row_idx, perm, vals_t);
     return hipGetLastError();
 }
 
