@@ -123,7 +123,9 @@ int l1csr_host_free_mapped(void *host);
  * the kernel).  ws (nullable) enables the LDS-tiled kernel and must then hold
  * l1csr_workspace_bytes(L1CSR_OP_SPMM, n_rows, n_cols, nnz, B) bytes; without
  * it a row-per-wave kernel runs.  Summation order (fp32 fused multiply-adds):
- * the row-per-wave kernel sums each Y entry in ascending p order; the tiled
+ * the row-per-wave kernel sums each Y entry in ascending p order (rows of more
+ * than 256 entries: four consecutive parts, each in ascending p order, added in
+ * that order, for up to 32768 rows); the tiled
  * kernel sums a row in ascending p order too unless it cuts the row into k
  * strided pieces (long rows: piece j takes p = row_ptr[i] + j, + j + k, ...),
  * each summed in ascending p order and the k partial sums then added in piece

@@ -974,32 +974,13 @@ __global__ __launch_bounds__(256) void fixup_kernel(int n_rows, const int *__res
 // rows kernel: one wave per (row, batch chunk), X from the cache hierarchy
 // ---------------------------------------------------------------------------
 
-constexpr int kRowsPerBlock = 4;
-
-template <int VEC>
-__global__ __launch_bounds__(256) void spmm_rows_kernel(int n_rows, const int *__restrict__ ptr,
-                                                        const int *__restrict__ idx,
-                                                        const float *__restrict__ vals,
-                                                        const float *__restrict__ X, int64_t ldx,
-                                                        int B, float *__restrict__ Y, int64_t ldy,
-                                                        int nrb) {
-    // blocks of one XCD take a contiguous run of batch chunks, so the rows that
-    // share an X row segment read it through the same L2
-    int rb, ch;
-    map_block(blockIdx.x, gridDim.x, nrb, rb, ch);
-    const int row = uniform(rb * kRowsPerBlock + (threadIdx.x >> 6));
-    if (row >= n_rows) return;
+// acc += the entries [start, end) of one row times their X rows, at this lane's
+// VEC columns from b on, U X row segments in flight
+template <int VEC, int U>
+__device__ __forceinline__ void row_sum(int start, int end, const int *__restrict__ idx,
+                                        const float *__restrict__ vals, const float *__restrict__ X, int64_t ldx,
+                                        int b, bool active, float (&acc)[VEC]) {
     const int lane = threadIdx.x & 63;
-    const int b = (ch * kWave + lane) * VEC;
-    const bool active = b < B;
-    const int start = uniform(ptr[row]);
-    const int end = uniform(ptr[row + 1]);
-    constexpr int U = 8;  // X row segments in flight per wave
-
-    float acc[VEC];
-#pragma unroll
-    for (int e = 0; e < VEC; ++e) acc[e] = 0.f;
-
     for (int base = start; base < end; base += kWave) {
         const int n = min(kWave, end - base);
         int c = 0;
@@ -1008,31 +989,133 @@ __global__ __launch_bounds__(256) void spmm_rows_kernel(int n_rows, const int *_
             c = idx[base + lane];
             v = vals[base + lane];
         }
+        if (!active) continue;
         int j = 0;
         for (; j + U <= n; j += U) {
             float x[U][VEC];
-            if (active) {
 #pragma unroll
-                for (int u = 0; u < U; ++u) load_vec<VEC>(X + (int64_t)lane_bcast(c, j + u) * ldx + b, x[u]);
+            for (int u = 0; u < U; ++u) load_vec<VEC>(X + (int64_t)lane_bcast(c, j + u) * ldx + b, x[u]);
 #pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    const float vu = lane_bcast(v, j + u);
+            for (int u = 0; u < U; ++u) {
+                const float vu = lane_bcast(v, j + u);
 #pragma unroll
-                    for (int e = 0; e < VEC; ++e) acc[e] = fmaf(vu, x[u][e], acc[e]);
-                }
+                for (int e = 0; e < VEC; ++e) acc[e] = fmaf(vu, x[u][e], acc[e]);
             }
         }
         for (; j < n; ++j) {
             const int cj = lane_bcast(c, j);
             const float vj = lane_bcast(v, j);
-            if (active) {
-                float x0[VEC];
-                load_vec<VEC>(X + (int64_t)cj * ldx + b, x0);
+            float x0[VEC];
+            load_vec<VEC>(X + (int64_t)cj * ldx + b, x0);
 #pragma unroll
-                for (int e = 0; e < VEC; ++e) acc[e] = fmaf(vj, x0[e], acc[e]);
-            }
+            for (int e = 0; e < VEC; ++e) acc[e] = fmaf(vj, x0[e], acc[e]);
         }
     }
+}
+
+// A wave per row and 64 * VEC columns.  Rows of more than kLongRow entries, which
+// power-law patterns have, would hold one wave (and one compute unit's path to
+// X) for as long as all others together: they are left to the grid's first
+// `extra` workgroups, which find them by a pass over the row pointers and take
+// (long row, 64 columns) items, a consecutive quarter of the entries per wave
+// with 32 loads in flight, the quarters added in order.  Where no row is long
+// they end after that pass (768 workgroups: 16.9 -> 17.3 us at 4096 x 4096 x 512
+// with 1 % uniform; power-law rows: 680 -> 176 us at 1000 x 9000 x 512 and 561 -> 134 at
+// 4096 x 9216 x 64, 43 -> 16 at 300 x 784 x 256).  Eight waves
+// per SIMD have to fit: with 64 registers and more the uniform layers lose 10 %.
+constexpr int kRowsPerBlock = 4;
+constexpr int kLongRow = 256;
+constexpr int kLongList = 2048;       // long rows held in LDS at a time
+constexpr int kLongBlocks = 768;
+constexpr int kLongMaxRows = 1 << 15;  // rows a workgroup scans at most
+
+__device__ void long_rows(int n_rows, const int *__restrict__ ptr, const int *__restrict__ idx,
+                          const float *__restrict__ vals, const float *__restrict__ X, int64_t ldx, int B,
+                          float *__restrict__ Y, int64_t ldy, int extra) {
+    __shared__ int list[kLongList];
+    __shared__ int wtot[kRowsPerBlock];
+    __shared__ float part[kRowsPerBlock][kWave];
+    const int lane = threadIdx.x & 63, wave = uniform(threadIdx.x >> 6);
+    bool any = false;
+    for (int r = threadIdx.x; r < n_rows; r += 4 * 256) {
+        int a[4], e[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int q = min(r + u * 256, n_rows - 1);
+            a[u] = ptr[q];
+            e[u] = ptr[q + 1];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) any |= e[u] - a[u] > kLongRow;
+    }
+    if (!__syncthreads_or(any)) return;
+    const int per = (n_rows + 255) / 256, r0 = threadIdx.x * per, r1 = min(n_rows, r0 + per);
+    int mine = 0;  // long rows among this thread's consecutive ones
+    for (int r = r0; r < r1; ++r) mine += ptr[r + 1] - ptr[r] > kLongRow;
+    const int incl = wave_incl_scan(mine);
+    if (lane == kWave - 1) wtot[wave] = incl;
+    __syncthreads();
+    int total = 0, first = incl - mine;
+#pragma unroll
+    for (int w = 0; w < kRowsPerBlock; ++w) {
+        first += w < wave ? wtot[w] : 0;
+        total += wtot[w];
+    }
+    const int nsub = (B + kWave - 1) / kWave;
+    for (int l0 = 0; l0 < total; l0 += kLongList) {
+        __syncthreads();  // the previous list is consumed
+        int q = first;
+        if (mine > 0)
+            for (int r = r0; r < r1; ++r)
+                if (ptr[r + 1] - ptr[r] > kLongRow) {
+                    if (q >= l0 && q < l0 + kLongList) list[q - l0] = r;
+                    ++q;
+                }
+        __syncthreads();
+        const int64_t items = (int64_t)min(kLongList, total - l0) * nsub;
+        for (int64_t it = blockIdx.x; it < items; it += extra) {
+            // consecutive workgroups (XCDs) on different columns of one row
+            const int row = list[it / nsub], b = (int)(it % nsub) * kWave + lane;
+            const int start = uniform(ptr[row]), len = uniform(ptr[row + 1]) - start;
+            float acc[1] = {0.f};
+            row_sum<1, 16>(start + (int)((int64_t)len * wave / kRowsPerBlock),
+                           start + (int)((int64_t)len * (wave + 1) / kRowsPerBlock), idx, vals, X, ldx, b, b < B, acc);
+            part[wave][lane] = acc[0];
+            __syncthreads();
+            if (wave == 0 && b < B)
+                Y[(int64_t)row * ldy + b] = part[0][lane] + part[1][lane] + part[2][lane] + part[3][lane];
+            __syncthreads();
+        }
+    }
+}
+
+template <int VEC>
+__global__ __launch_bounds__(256, 8) void spmm_rows_kernel(int n_rows, const int *__restrict__ ptr,
+                                                        const int *__restrict__ idx,
+                                                        const float *__restrict__ vals,
+                                                        const float *__restrict__ X, int64_t ldx,
+                                                        int B, float *__restrict__ Y, int64_t ldy,
+                                                        int nrb, int extra) {
+    if ((int)blockIdx.x < extra) {
+        long_rows(n_rows, ptr, idx, vals, X, ldx, B, Y, ldy, extra);
+        return;
+    }
+    // blocks of one XCD take a contiguous run of batch chunks, so the rows that
+    // share an X row segment read it through the same L2
+    int rb, ch;
+    map_block(blockIdx.x - extra, gridDim.x - extra, nrb, rb, ch);
+    const int row = uniform(rb * kRowsPerBlock + (threadIdx.x >> 6));
+    if (row >= n_rows) return;
+    const int lane = threadIdx.x & 63;
+    const int b = (ch * kWave + lane) * VEC;
+    const bool active = b < B;
+    const int start = uniform(ptr[row]);
+    const int end = uniform(ptr[row + 1]);
+    if (extra > 0 && end - start > kLongRow) return;
+    float acc[VEC];
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) acc[e] = 0.f;
+    row_sum<VEC, 8>(start, end, idx, vals, X, ldx, b, active, acc);
     if (active) store_vec<VEC>(Y + (int64_t)row * ldy + b, acc);
 }
 
@@ -1269,17 +1352,24 @@ hipError_t exec_any(const spmm_plan &pl, int n_rows, int n_cols, const int *ptr,
 }
 
 // the row-per-wave kernel (no workspace)
-hipError_t launch_rows(int n_rows, const int *ptr, const int *idx, const float *vals, const float *X, int64_t ldx,
+hipError_t launch_rows(int n_rows, int n_cols, const int *ptr, const int *idx, const float *vals, const float *X, int64_t ldx,
                        int B, float *Y, int64_t ldy, int vec, hipStream_t s) {
+    // vectors no wider than fill the lanes: 4096 x 4096 x 32 at 5 % 36.3 us with
+    // four floats on 8 lanes, 23.0 with one on 32; x 64 at 3 % 20.1 and 15.8
+    if (B <= kWave)
+        vec = 1;
+    else if (B <= 2 * kWave && vec > 2)
+        vec = 2;
     const int64_t nrb = ceil_div(n_rows, kRowsPerBlock), nch = ceil_div(B, kWave * vec);
-    if (nrb * nch > INT32_MAX) return hipErrorInvalidConfiguration;
-    const unsigned grid = (unsigned)(nrb * nch);
+    if (nrb * nch > INT32_MAX - kLongBlocks) return hipErrorInvalidConfiguration;
+    const int extra = n_cols > kLongRow && n_rows <= kLongMaxRows ? kLongBlocks : 0;
+    const unsigned grid = (unsigned)(nrb * nch) + extra;
     if (vec == 4)
-        spmm_rows_kernel<4><<<grid, 256, 0, s>>>(n_rows, ptr, idx, vals, X, ldx, B, Y, ldy, (int)nrb);
+        spmm_rows_kernel<4><<<grid, 256, 0, s>>>(n_rows, ptr, idx, vals, X, ldx, B, Y, ldy, (int)nrb, extra);
     else if (vec == 2)
-        spmm_rows_kernel<2><<<grid, 256, 0, s>>>(n_rows, ptr, idx, vals, X, ldx, B, Y, ldy, (int)nrb);
+        spmm_rows_kernel<2><<<grid, 256, 0, s>>>(n_rows, ptr, idx, vals, X, ldx, B, Y, ldy, (int)nrb, extra);
     else
-        spmm_rows_kernel<1><<<grid, 256, 0, s>>>(n_rows, ptr, idx, vals, X, ldx, B, Y, ldy, (int)nrb);
+        spmm_rows_kernel<1><<<grid, 256, 0, s>>>(n_rows, ptr, idx, vals, X, ldx, B, Y, ldy, (int)nrb, extra);
     return hipGetLastError();
 }
 
@@ -1320,7 +1410,7 @@ hipError_t launch_spmm(int n_rows, int n_cols, int64_t nnz, const int *ptr, cons
         if (e != hipSuccess) return e;
         return exec_any(pl, n_rows, n_cols, ptr, X, ldx, B, Y, ldy, ws, s);
     }
-    return launch_rows(n_rows, ptr, idx, vals, X, ldx, B, Y, ldy, vec, s);
+    return launch_rows(n_rows, n_cols, ptr, idx, vals, X, ldx, B, Y, ldy, vec, s);
 }
 
 hipError_t launch_spmm_plan(int n_rows, int n_cols, int64_t nnz, const int *ptr, const int *idx, const float *vals,
@@ -1337,7 +1427,7 @@ hipError_t launch_spmm_planned(int n_rows, int n_cols, int64_t nnz, const int *p
     const int vec = spmm_vec(X, ldx, B, Y, ldy);
     const spmm_plan pl = make_plan(n_rows, n_cols, nnz, B, plan != nullptr && vec == 4);
     if (pl.tiled) return exec_any(pl, n_rows, n_cols, ptr, X, ldx, B, Y, ldy, plan, s);
-    return launch_rows(n_rows, ptr, idx, vals, X, ldx, B, Y, ldy, vec, s);
+    return launch_rows(n_rows, n_cols, ptr, idx, vals, X, ldx, B, Y, ldy, vec, s);
 }
 
 hipError_t launch_spmm_scatter_atomic(int n_rows, int n_cols, const int *ptr, const int *idx,

@@ -1,0 +1,60 @@
+"""GPU: the row kernel's long rows (more than 256 entries, taken by workgroups of
+their own) around that length, with more of them than one LDS list holds, among
+empty rows, past the row count that a workgroup scans, at batches on both sides of
+each vector width, against 64-bit references and run to run."""
+import numpy as np
+import pytest
+
+import paper_1905_07931_amd as L1
+from _helpers import bits_equal, h, t
+
+pytestmark = pytest.mark.gpu
+
+
+def check(lengths, K, B, seed):
+    rng = np.random.default_rng(seed)
+    lengths = np.asarray(lengths)
+    rp = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int32)
+    ci = np.concatenate([np.sort(rng.choice(K, n, replace=False)) for n in lengths] or [[]]).astype(np.int32)
+    v = rng.standard_normal(len(ci)).astype(np.float32)
+    X = rng.random((K, B)).astype(np.float32)
+    N = len(lengths)
+    W = L1.CSR.from_host(rp, ci, v, K)
+    Xd = t(X)
+    import ctypes as C
+    import torch
+    Y = torch.full((N, B + 1), 5.0, device="cuda")  # without a workspace: the row kernel
+    rc = L1.lib().csr_spmm_fwd(N, K, W.nnz, W.row_ptr.data_ptr(), W.col_idx.data_ptr(), W.vals.data_ptr(), Xd.data_ptr(),
+                               B, B, Y.data_ptr(), B + 1, None, 0, C.c_void_p(torch.cuda.current_stream().cuda_stream))
+    assert rc == L1.OK
+    got = h(Y)
+    assert (got[:, B] == 5.0).all()
+    rows = np.repeat(np.arange(N), lengths)
+    ref, m = np.zeros((N, B)), np.zeros((N, B))
+    np.add.at(ref, rows, v[:, None].astype(np.float64) * X[ci])
+    np.add.at(m, rows, np.abs(v)[:, None].astype(np.float64) * X[ci])
+    bound = (lengths[:, None] + 4) * 2.0 ** -24 * m
+    assert (np.abs(got[:, :B] - ref) <= bound).all()
+    Z = torch.empty((N, B + 1), device="cuda")
+    L1.lib().csr_spmm_fwd(N, K, W.nnz, W.row_ptr.data_ptr(), W.col_idx.data_ptr(), W.vals.data_ptr(), Xd.data_ptr(), B, B,
+                          Z.data_ptr(), B + 1, None, 0, C.c_void_p(torch.cuda.current_stream().cuda_stream))
+    assert bits_equal(h(Z)[:, :B].copy(), got[:, :B].copy())
+
+
+@pytest.mark.parametrize("B", [1, 33, 64, 65, 128, 132, 260])
+def test_lengths_around_the_split(B):
+    check([0, 255, 256, 257, 1, 300, 0, 1000, 64, 8, 9, 320, 259], 1000, B, B)
+
+
+def test_more_long_rows_than_a_list():
+    check([257] * 2100 + [3] * 5, 300, 7, 1)
+
+
+def test_one_long_row_among_many():
+    check([0] * 1500 + [2000] + [1] * 1500, 2000, 96, 2)
+
+
+def test_past_the_scanned_rows():
+    n = np.zeros(32769, np.int64)
+    n[[0, 7, 32768]] = [300, 1, 270]
+    check(n, 300, 3, 3)
