@@ -91,7 +91,8 @@ enum l1csr_op {
     L1CSR_OP_WGRAD_PROX = 9,   /* dense_wgrad_prox, fp32 (other precisions need none) */
     L1CSR_OP_WGRAD_PACKED = 10, /* dense_wgrad / dense_wgrad_prox with packed operands (nnz unused) */
     L1CSR_OP_SDDMM_PACKED = 11, /* sddmm_masked_wgrad over a dense pattern, packed operands */
-    L1CSR_OP_SPMM_PACKED = 12   /* csr_spmm_fwd / csr_spmm_bwd_t over a dense pattern, packed operands */
+    L1CSR_OP_SPMM_PACKED = 12,  /* csr_spmm_fwd / csr_spmm_bwd_t over a dense pattern, packed operands */
+    L1CSR_OP_PROX_DENSE = 13    /* prox_adaptive_recompress, dense result kept (nnz, B unused) */
 };
 
 /* Human-readable name of a status code (static string, never NULL). */
@@ -458,17 +459,19 @@ int prox_adaptive_step(int mode, int solver, int32_t n_rows, int32_t n_cols, int
 
 /*
  * prox_adaptive_step (dense mode) followed by csr_recompress (t = 0) in one
- * call, without materialising Z: the l1-phase update of Algorithm 1 or 2 from
+ * call: the l1-phase update of Algorithm 1 or 2 from
  * the CSR weights W, the dense gradient G and the dense states m, v straight
  * to the new CSR W'.  m and v are updated in place exactly as by
  * prox_adaptive_step; the output is bit-identical to the two calls.
  * row_ptr_out, col_idx_out, vals_out, capacity, d_nnz_out and h_nnz_required
  * behave as in prox_l1_recompress; when the call returns L1CSR_ECAPACITY it
- * has left m and v unchanged.  With capacity >= n_rows*n_cols (no wait) G and
- * the states are read in a counting pass that stores m', v', and m', v' (ADAM)
- * or G, v' (RMSProp) are read again by the filling pass.  The output arrays
- * must not overlap W's arrays, G, m, v or one another (L1CSR_EINVAL).  ws as
- * l1csr_workspace_bytes(L1CSR_OP_PROX_RECOMPRESS, n_rows, n_cols, nnz, 0).
+ * has left m and v unchanged.  ws must hold
+ * l1csr_workspace_bytes(L1CSR_OP_PROX_RECOMPRESS, n_rows, n_cols, nnz, 0); with
+ * capacity >= n_rows*n_cols (no wait) and L1CSR_OP_PROX_DENSE's bytes one pass
+ * over G and the states leaves Z there for the compaction, with fewer bytes G
+ * and the states are read in a counting pass that stores m', v', and m', v'
+ * (ADAM) or G, v' (RMSProp) again by the filling pass (same bits).  The output
+ * arrays must not overlap W's arrays, G, m, v or one another (L1CSR_EINVAL).
  */
 int prox_adaptive_recompress(int solver, int32_t n_rows, int32_t n_cols, int64_t nnz,
                              const int32_t *row_ptr, const int32_t *col_idx, const float *vals,

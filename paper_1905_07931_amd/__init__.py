@@ -40,6 +40,7 @@ OP_WGRAD_PROX = 9
 OP_WGRAD_PACKED = 10
 OP_SDDMM_PACKED = 11
 OP_SPMM_PACKED = 12
+OP_PROX_DENSE = 13
 
 
 class L1CSRError(RuntimeError):
@@ -891,7 +892,10 @@ def prox_adaptive_recompress(W: CSR, G, st: AdaptiveState, eta, lam, capacity=No
                   torch.empty(max(cap, 1), dtype=torch.int32, device=dev),
                   torch.empty(max(cap, 1), dtype=torch.float32, device=dev), None)
     cap = min(out.col_idx.numel(), out.vals.numel()) if capacity is None else int(capacity)
-    ws, wsb = _workspace(workspace_bytes(OP_PROX_RECOMPRESS, N, K, nnz, 0), dev, stream)
+    need_ws = workspace_bytes(OP_PROX_RECOMPRESS, N, K, nnz, 0)
+    if cap >= N * K:
+        need_ws = max(need_ws, workspace_bytes(OP_PROX_DENSE, N, K, 0, 0))
+    ws, wsb = _workspace(need_ws, dev, stream)
     need = C.c_int64(-1)
     _check(lib().prox_adaptive_recompress(st.solver, N, K, nnz, _p(W.row_ptr), _p(W.col_idx),
                                           _p(W.vals), _p(G), ldg, _p(m), _p(st.v), lds, float(eta),

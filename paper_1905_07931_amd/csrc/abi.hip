@@ -143,6 +143,17 @@ int prox_recompress_check(int32_t n_rows, int32_t n_cols, int64_t nnz, const int
     return L1CSR_OK;
 }
 
+// Z and its word counts are in dw: W' by the counted compaction (room for every weight)
+int compact_dense(int32_t n_rows, int32_t n_cols, const prox_dense_ws &dw, int32_t *row_ptr_out, int32_t *col_idx_out,
+                  float *vals_out, int64_t capacity, int32_t *d_nnz_out, hipStream_t stream) {
+    hipError_t e = launch_counted_sums(n_rows, n_cols, dw.words, dw.sums, stream);
+    const bool prefix_here = counted_prefix_in_compact(n_rows);
+    if (e == hipSuccess && !prefix_here) e = launch_counted_row_ptr(n_rows, dw.sums, row_ptr_out, stream);
+    if (e != hipSuccess) return L1CSR_EHIP;
+    return hip_status(launch_counted_compact(n_rows, n_cols, dw.Z, dw.ldz, dw.words, dw.sums, prefix_here, row_ptr_out,
+                                             col_idx_out, vals_out, capacity, d_nnz_out, stream));
+}
+
 // the launches of prox_l1_recompress on checked arguments, with ws holding
 // prox_recompress_workspace_bytes(n_rows, n_cols) bytes
 int prox_recompress_run(int32_t n_rows, int32_t n_cols, int64_t nnz, const int32_t *row_ptr,
@@ -277,6 +288,7 @@ size_t l1csr_workspace_bytes(int op, int32_t n_rows, int32_t n_cols, int64_t nnz
         }
         case L1CSR_OP_SDDMM_PACKED: return round_up(packed_sddmm_bytes(n_rows, n_cols, nnz, B));
         case L1CSR_OP_SPMM_PACKED: return round_up(packed_spmm_bytes(n_rows, n_cols, nnz, B));
+        case L1CSR_OP_PROX_DENSE: return round_up(prox_dense_carve(n_rows, n_cols, nullptr).bytes);
         case L1CSR_OP_SOFTMAX_XENT: return round_up(sizeof(float) * (size_t)(ceil_div(B, 256) + 1));
         default: return 0;
     }
@@ -687,6 +699,15 @@ int prox_adaptive_recompress(int solver, int32_t n_rows, int32_t n_cols, int64_t
     // fill pass recomputes from them; otherwise the state is only written once
     // the output is known to fit
     const bool roomy = capacity >= total;
+    const prox_dense_ws dw = prox_dense_carve(n_rows, n_cols, ws);
+    if (roomy && total > 0 && ws_bytes >= dw.bytes) {
+        if (h_nnz_required) *h_nnz_required = -1;
+        if (launch_adaptive_slabs(kStageWords, n_rows, n_cols, row_ptr, col_idx, vals, G, ldg, M, v, lds, P, pw.seg,
+                                  dw.words, nullptr, nullptr, nullptr, 0, nullptr, nullptr, dw.Z, dw.ldz, nullptr,
+                                  stream) != hipSuccess)
+            return L1CSR_EHIP;
+        return compact_dense(n_rows, n_cols, dw, row_ptr_out, col_idx_out, vals_out, capacity, d_nnz_out, stream);
+    }
     hipError_t e = launch_adaptive_slabs(roomy ? kStageCountWrite : kStageCountKeep, n_rows, n_cols,
                                          row_ptr, col_idx, vals, G, ldg, M, v, lds, P, pw.seg,
                                          pw.counts, nullptr, nullptr, nullptr, 0, nullptr, nullptr,

@@ -173,6 +173,16 @@ hipError_t launch_prox_fill(int n_rows, int n_cols, const int *seg, const int *i
                             const int *off, int *col_out, float *val_out, int64_t capacity,
                             int *row_ptr, int *nnz_out, hipStream_t s);
 
+// the workspace of an adaptive update that keeps Z: prox_carve()'s part first,
+// then Z with its row stride, the word counts and the compaction's sums
+struct prox_dense_ws {
+    float *Z;
+    int64_t ldz;
+    int *words, *sums;
+    size_t bytes;
+};
+prox_dense_ws prox_dense_carve(int n_rows, int n_cols, void *ws);
+
 // prox_adaptive.hip --------------------------------------------------------
 // Prox-RMSProp / Prox-ADAM parameters, prepared on the host in double
 constexpr int kSolverRms = 1;
@@ -190,10 +200,12 @@ enum {
     kStageCountKeep = 1,    // count only (state untouched)
     kStageFillStored = 2,   // compact, recomputing from the stored m', v'
     kStageFillWrite = 3,    // compact and store m', v'
-    kStageDense = 4         // write Z and row counts, store m', v'
+    kStageDense = 4,        // write Z and row counts, store m', v'
+    kStageWords = 5         // write Z and its word counts (into counts), store m', v'
 };
-// seg and counts are the prox_carve() parts; the count and dense stages also
-// compute seg.  Arguments a stage does not use may be null.
+// seg and counts are the prox_carve() parts (kStageWords: counts is the word
+// counts); the count, dense and words stages also compute seg.  Arguments a
+// stage does not use may be null.
 hipError_t launch_adaptive_slabs(int stage, int n_rows, int n_cols, const int *ptr, const int *idx,
                                  const float *vals, const float *G, int64_t ldg, float *M, float *V,
                                  int64_t lds, const adaptive_params &P, int *seg, int *counts,

@@ -339,4 +339,20 @@ hipError_t launch_prox_fill(int n_rows, int n_cols, const int *seg, const int *i
     return hipGetLastError();
 }
 
+prox_dense_ws prox_dense_carve(int n_rows, int n_cols, void *ws) {
+    auto al = [](size_t x) { return (x + 255) & ~(size_t)255; };
+    char *b = static_cast<char *>(ws);
+    prox_dense_ws w{};
+    size_t o = al(prox_recompress_workspace_bytes(n_rows, n_cols));
+    w.ldz = ceil_div(n_cols, 4) * 4;
+    w.Z = reinterpret_cast<float *>(b + o);
+    o = al(o + sizeof(float) * (size_t)n_rows * (size_t)w.ldz);
+    w.words = reinterpret_cast<int *>(b + o);
+    o = al(o + word_counts_bytes(n_rows, n_cols));
+    w.sums = reinterpret_cast<int *>(b + o);
+    o += sizeof(int) * counted_ws_ints(n_rows);
+    w.bytes = o;
+    return w;
+}
+
 }  // namespace l1csr

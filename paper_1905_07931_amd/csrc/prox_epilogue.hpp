@@ -30,6 +30,17 @@ __device__ __forceinline__ float soft_threshold(float w, float g, double eta, do
     return (float)(z - c) + 0.0f;
 }
 
+// The nonzeros of every 32-column word of one row, from a wave whose lanes hold
+// four consecutive columns each (lane 0 at a multiple of 256): keep[j] of column
+// k + j.  Eight lanes are a word; the first of them stores its count.
+__device__ __forceinline__ void store_word_counts(const bool (&keep)[4], int k, int n_cols, int *words) {
+    const int sh = (threadIdx.x & 63) & ~7;
+    int n = 0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) n += __popc((unsigned)(wave_ballot(keep[j]) >> sh) & 0xffu);
+    if ((threadIdx.x & 7) == 0 && k < n_cols) words[k >> 5] = n;
+}
+
 // kernel argument of a GEMM with the prox epilogue
 struct prox_epi {
     const unsigned *mask;  // [kw][M] (word-major)
