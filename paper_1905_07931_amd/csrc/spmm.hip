@@ -1013,7 +1013,7 @@ __device__ __forceinline__ void row_sum(int start, int end, const int *__restric
     }
 }
 
-// A wave per row and 64 * VEC columns.  Rows of more than kLongRow entries, which
+// A wave per row and 64 * VEC columns.  Rows of more than `longest` entries (long_row()), which
 // power-law patterns have, would hold one wave (and one compute unit's path to
 // X) for as long as all others together: they are left to the grid's first
 // `extra` workgroups, which find them by a pass over the row pointers and take
@@ -1031,7 +1031,7 @@ constexpr int kLongMaxRows = 1 << 15;  // rows a workgroup scans at most
 
 __device__ void long_rows(int n_rows, const int *__restrict__ ptr, const int *__restrict__ idx,
                           const float *__restrict__ vals, const float *__restrict__ X, int64_t ldx, int B,
-                          float *__restrict__ Y, int64_t ldy, int extra) {
+                          float *__restrict__ Y, int64_t ldy, int extra, int longest) {
     __shared__ int list[kLongList];
     __shared__ int wtot[kRowsPerBlock];
     __shared__ float part[kRowsPerBlock][kWave];
@@ -1046,12 +1046,12 @@ __device__ void long_rows(int n_rows, const int *__restrict__ ptr, const int *__
             e[u] = ptr[q + 1];
         }
 #pragma unroll
-        for (int u = 0; u < 4; ++u) any |= e[u] - a[u] > kLongRow;
+        for (int u = 0; u < 4; ++u) any |= e[u] - a[u] > longest;
     }
     if (!__syncthreads_or(any)) return;
     const int per = (n_rows + 255) / 256, r0 = threadIdx.x * per, r1 = min(n_rows, r0 + per);
     int mine = 0;  // long rows among this thread's consecutive ones
-    for (int r = r0; r < r1; ++r) mine += ptr[r + 1] - ptr[r] > kLongRow;
+    for (int r = r0; r < r1; ++r) mine += ptr[r + 1] - ptr[r] > longest;
     const int incl = wave_incl_scan(mine);
     if (lane == kWave - 1) wtot[wave] = incl;
     __syncthreads();
@@ -1067,7 +1067,7 @@ __device__ void long_rows(int n_rows, const int *__restrict__ ptr, const int *__
         int q = first;
         if (mine > 0)
             for (int r = r0; r < r1; ++r)
-                if (ptr[r + 1] - ptr[r] > kLongRow) {
+                if (ptr[r + 1] - ptr[r] > longest) {
                     if (q >= l0 && q < l0 + kLongList) list[q - l0] = r;
                     ++q;
                 }
@@ -1095,9 +1095,9 @@ __global__ __launch_bounds__(256, 8) void spmm_rows_kernel(int n_rows, const int
                                                         const float *__restrict__ vals,
                                                         const float *__restrict__ X, int64_t ldx,
                                                         int B, float *__restrict__ Y, int64_t ldy,
-                                                        int nrb, int extra) {
+                                                        int nrb, int extra, int longest) {
     if ((int)blockIdx.x < extra) {
-        long_rows(n_rows, ptr, idx, vals, X, ldx, B, Y, ldy, extra);
+        long_rows(n_rows, ptr, idx, vals, X, ldx, B, Y, ldy, extra, longest);
         return;
     }
     // blocks of one XCD take a contiguous run of batch chunks, so the rows that
@@ -1111,7 +1111,7 @@ __global__ __launch_bounds__(256, 8) void spmm_rows_kernel(int n_rows, const int
     const bool active = b < B;
     const int start = uniform(ptr[row]);
     const int end = uniform(ptr[row + 1]);
-    if (extra > 0 && end - start > kLongRow) return;
+    if (extra > 0 && end - start > longest) return;
     float acc[VEC];
 #pragma unroll
     for (int e = 0; e < VEC; ++e) acc[e] = 0.f;
@@ -1351,8 +1351,25 @@ hipError_t exec_any(const spmm_plan &pl, int n_rows, int n_cols, const int *ptr,
     return exec_tiled<2, false>(pl, n_rows, n_cols, ptr, X, ldx, B, Y, ldy, ws, s);
 }
 
+// The entries beyond which a row is long.  A row's wave takes 0.056 us an entry (one
+// chain of loads, eight in flight); long rows share the chip at about 2.4 M
+// products per us, the waves of a full grid reach 4.7 M.  So layers of few rows
+// (waves that hold columns for less than 0.056 us per entry and row: n_rows * columns
+// under 140,000) take all rows near the mean length as long ones, others only
+// those that outlast their layer's uniform row by half.  256 entries for all ->
+// this rule, us: uniform 1733 x 3370 x 224 at 10 % 65.8 -> 27.2, 1024 x 3000 x 256
+// at 12 % 41.8 -> 22.6, power-law rows 1000 x 9000 x 200 at 4 % 162 -> 127, 4096 x
+// 4096 x 32 at 13 % 145 -> 92; kept: uniform 512 x 4096 x 128 18.3 (29.1 with one
+// wave a row), 128 x 2000 x 64 at 50 % 14.8 (43.7).
+int long_row(int64_t n_rows, int64_t nnz, int B) {
+    const int64_t mean = nnz / (n_rows > 0 ? n_rows : 1);
+    const bool few = n_rows * (ceil_div(B, kWave) * kWave) < 140000;
+    const int64_t n = few ? mean * 3 / 4 : mean * 3 / 2;
+    return (int)(n < kLongRow ? kLongRow : (n < INT32_MAX ? n : INT32_MAX));
+}
+
 // the row-per-wave kernel (no workspace)
-hipError_t launch_rows(int n_rows, int n_cols, const int *ptr, const int *idx, const float *vals, const float *X, int64_t ldx,
+hipError_t launch_rows(int n_rows, int n_cols, int64_t nnz, const int *ptr, const int *idx, const float *vals, const float *X, int64_t ldx,
                        int B, float *Y, int64_t ldy, int vec, hipStream_t s) {
     // vectors no wider than fill the lanes: 4096 x 4096 x 32 at 5 % 36.3 us with
     // four floats on 8 lanes, 23.0 with one on 32; x 64 at 3 % 20.1 and 15.8
@@ -1362,14 +1379,15 @@ hipError_t launch_rows(int n_rows, int n_cols, const int *ptr, const int *idx, c
         vec = 2;
     const int64_t nrb = ceil_div(n_rows, kRowsPerBlock), nch = ceil_div(B, kWave * vec);
     if (nrb * nch > INT32_MAX - kLongBlocks) return hipErrorInvalidConfiguration;
-    const int extra = n_cols > kLongRow && n_rows <= kLongMaxRows ? kLongBlocks : 0;
+    const int longest = long_row(n_rows, nnz, B);
+    const int extra = n_cols > longest && n_rows <= kLongMaxRows ? kLongBlocks : 0;
     const unsigned grid = (unsigned)(nrb * nch) + extra;
     if (vec == 4)
-        spmm_rows_kernel<4><<<grid, 256, 0, s>>>(n_rows, ptr, idx, vals, X, ldx, B, Y, ldy, (int)nrb, extra);
+        spmm_rows_kernel<4><<<grid, 256, 0, s>>>(n_rows, ptr, idx, vals, X, ldx, B, Y, ldy, (int)nrb, extra, longest);
     else if (vec == 2)
-        spmm_rows_kernel<2><<<grid, 256, 0, s>>>(n_rows, ptr, idx, vals, X, ldx, B, Y, ldy, (int)nrb, extra);
+        spmm_rows_kernel<2><<<grid, 256, 0, s>>>(n_rows, ptr, idx, vals, X, ldx, B, Y, ldy, (int)nrb, extra, longest);
     else
-        spmm_rows_kernel<1><<<grid, 256, 0, s>>>(n_rows, ptr, idx, vals, X, ldx, B, Y, ldy, (int)nrb, extra);
+        spmm_rows_kernel<1><<<grid, 256, 0, s>>>(n_rows, ptr, idx, vals, X, ldx, B, Y, ldy, (int)nrb, extra, longest);
     return hipGetLastError();
 }
 
@@ -1410,7 +1428,7 @@ hipError_t launch_spmm(int n_rows, int n_cols, int64_t nnz, const int *ptr, cons
         if (e != hipSuccess) return e;
         return exec_any(pl, n_rows, n_cols, ptr, X, ldx, B, Y, ldy, ws, s);
     }
-    return launch_rows(n_rows, n_cols, ptr, idx, vals, X, ldx, B, Y, ldy, vec, s);
+    return launch_rows(n_rows, n_cols, nnz, ptr, idx, vals, X, ldx, B, Y, ldy, vec, s);
 }
 
 hipError_t launch_spmm_plan(int n_rows, int n_cols, int64_t nnz, const int *ptr, const int *idx, const float *vals,
@@ -1427,7 +1445,7 @@ hipError_t launch_spmm_planned(int n_rows, int n_cols, int64_t nnz, const int *p
     const int vec = spmm_vec(X, ldx, B, Y, ldy);
     const spmm_plan pl = make_plan(n_rows, n_cols, nnz, B, plan != nullptr && vec == 4);
     if (pl.tiled) return exec_any(pl, n_rows, n_cols, ptr, X, ldx, B, Y, ldy, plan, s);
-    return launch_rows(n_rows, n_cols, ptr, idx, vals, X, ldx, B, Y, ldy, vec, s);
+    return launch_rows(n_rows, n_cols, nnz, ptr, idx, vals, X, ldx, B, Y, ldy, vec, s);
 }
 
 hipError_t launch_spmm_scatter_atomic(int n_rows, int n_cols, const int *ptr, const int *idx,

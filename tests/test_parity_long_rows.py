@@ -58,3 +58,14 @@ def test_past_the_scanned_rows():
     n = np.zeros(32769, np.int64)
     n[[0, 7, 32768]] = [300, 1, 270]
     check(n, 300, 3, 3)
+
+
+@pytest.mark.parametrize("B", [64, 100])
+def test_even_rows_keep_a_wave(B):
+    # many rows of some 300 entries: only the one past their mean by half is split
+    check([300] * 1500 + [440, 0, 455, 1000, 256, 257] + [290] * 900, 1000, B, B)
+
+
+def test_few_rows_around_their_mean():
+    # 12 rows, mean 400: the line lies at 300 entries
+    check([299, 300, 301, 257, 400, 480, 500, 460, 440, 463, 500, 400], 600, 40, 6)
