@@ -286,8 +286,15 @@ size_t l1csr_workspace_bytes(int op, int32_t n_rows, int32_t n_cols, int64_t nnz
                          x3 = split_wgrad_bytes(n_rows, n_cols, B, L1CSR_BF16X3);
             return round_up(f > x3 ? f : x3);
         }
-        case L1CSR_OP_SDDMM_PACKED: return round_up(packed_sddmm_bytes(n_rows, n_cols, nnz, B));
-        case L1CSR_OP_SPMM_PACKED: return round_up(packed_spmm_bytes(n_rows, n_cols, nnz, B));
+        // (no less than the calls ask for without the packed path)
+        case L1CSR_OP_SDDMM_PACKED: {
+            const size_t p = packed_sddmm_bytes(n_rows, n_cols, nnz, B), q = sddmm_workspace_bytes(n_rows, n_cols, nnz, B);
+            return round_up(p > 0 && p < q ? q : p);
+        }
+        case L1CSR_OP_SPMM_PACKED: {
+            const size_t p = packed_spmm_bytes(n_rows, n_cols, nnz, B), q = spmm_workspace_bytes(n_rows, n_cols, nnz, B);
+            return round_up(p > 0 && p < q ? q : p);
+        }
         case L1CSR_OP_PROX_DENSE: return round_up(prox_dense_carve(n_rows, n_cols, nullptr).bytes);
         case L1CSR_OP_SOFTMAX_XENT: return round_up(sizeof(float) * (size_t)(ceil_div(B, 256) + 1));
         default: return 0;
@@ -302,7 +309,7 @@ int csr_spmm_fwd(int32_t n_rows, int32_t n_cols, int64_t nnz, const int32_t *row
     if (ws != nullptr && ws_bytes < spmm_workspace_bytes(n_rows, n_cols, nnz, B)) return L1CSR_EINVAL;
     if (ceil_div(B, kWave) > kMaxGridY) return L1CSR_EUNSUPPORTED;
     const size_t packed = packed_spmm_bytes(n_rows, n_cols, nnz, B);
-    if (packed > 0 && ws != nullptr && ws_bytes >= packed)
+    if (packed_room(packed, ws, ws_bytes))
         return hip_status(launch_packed_spmm(n_rows, n_cols, row_ptr, col_idx, vals, X, ldx, B, Y, ldy, ws, stream));
     return hip_status(launch_spmm(n_rows, n_cols, nnz, row_ptr, col_idx, vals, X, ldx, B, Y, ldy, ws,
                                   stream));
@@ -374,7 +381,7 @@ int csr_spmm_bwd_t(int32_t n_rows, int32_t n_cols, int64_t nnz, const int32_t *r
     if (bad_dense(dY, n_rows, B, ldy) || bad_dense(dX, n_cols, B, ldx)) return L1CSR_EINVAL;
     if (ceil_div(B, kWave) > kMaxGridY) return L1CSR_EUNSUPPORTED;
     const size_t packed = use_csc ? packed_spmm_bytes(n_cols, n_rows, nnz, B) : 0;
-    if (packed > 0 && ws != nullptr && ws_bytes >= packed)
+    if (packed_room(packed, ws, ws_bytes))
         return hip_status(launch_packed_spmm(n_cols, n_rows, col_ptr, row_idx, vals_t, dY, ldy, B, dX, ldx, ws, stream));
     if (use_csc)  // the forward product of the transposed matrix
         return hip_status(launch_spmm(n_cols, n_rows, nnz, col_ptr, row_idx, vals_t, dY, ldy, B, dX,
@@ -396,7 +403,7 @@ int dense_wgrad(int32_t N, int32_t K, int32_t B, const float *dY, int64_t ldy, c
     if (precision == L1CSR_BF16)
         return hip_status(launch_wgrad_bf16(N, K, B, dY, ldy, X, ldx, dW, ldw, stream));
     const size_t packed = split_wgrad_bytes(N, K, B, precision);
-    if (packed > 0 && ws != nullptr && ws_bytes >= packed)
+    if (packed_room(packed, ws, ws_bytes))
         return hip_status(launch_split_wgrad(N, K, B, precision, dY, ldy, X, ldx, dW, ldw, ws, stream));
     if (precision == L1CSR_BF16X3)
         return hip_status(launch_wgrad_bf16x3(N, K, B, dY, ldy, X, ldx, dW, ldw, stream));
@@ -415,7 +422,7 @@ int sddmm_masked_wgrad(int32_t n_rows, int32_t n_cols, int64_t nnz, const int32_
     if (need > 0 && (ws == nullptr || ws_bytes < need)) return L1CSR_EINVAL;
     if (ceil_div(B, kWave) > kMaxGridY) return L1CSR_EUNSUPPORTED;
     const size_t packed = packed_sddmm_bytes(n_rows, n_cols, nnz, B);
-    if (packed > 0 && ws != nullptr && ws_bytes >= packed)
+    if (packed_room(packed, ws, ws_bytes))
         return hip_status(launch_packed_sddmm(n_rows, n_cols, row_ptr, col_idx, dY, ldy, X, ldx, B, gv, ws, stream));
     return hip_status(
         launch_sddmm(n_rows, n_cols, nnz, row_ptr, col_idx, dY, ldy, X, ldx, B, gv, ws, stream));
@@ -700,7 +707,7 @@ int prox_adaptive_recompress(int solver, int32_t n_rows, int32_t n_cols, int64_t
     // the output is known to fit
     const bool roomy = capacity >= total;
     const prox_dense_ws dw = prox_dense_carve(n_rows, n_cols, ws);
-    if (roomy && total > 0 && ws_bytes >= dw.bytes) {
+    if (roomy && total > 0 && packed_room(dw.bytes, ws, ws_bytes)) {
         if (h_nnz_required) *h_nnz_required = -1;
         if (launch_adaptive_slabs(kStageWords, n_rows, n_cols, row_ptr, col_idx, vals, G, ldg, M, v, lds, P, pw.seg,
                                   dw.words, nullptr, nullptr, nullptr, 0, nullptr, nullptr, dw.Z, dw.ldz, nullptr,

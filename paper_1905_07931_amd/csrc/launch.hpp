@@ -80,6 +80,11 @@ int wgrad_f32_prox_slab(int N, int K, int B);
 int wgrad_bf16x3_prox_slab(int N, int K, int B);
 // dense_wgrad precision codes (the ABI's l1csr_precision)
 constexpr int kPrecF32 = 0, kPrecBF16 = 1, kPrecBF16X3 = 2;
+// ws holds an optional path's `need` bytes (0: not taken), at the 16-byte
+// alignment of its wide stores; callers with less keep the other kernels
+inline bool packed_room(size_t need, const void *ws, size_t ws_bytes) {
+    return need > 0 && ws != nullptr && ws_bytes >= need && aligned16(ws);
+}
 // dW = parts[0] + parts[1] + ... (N x K each), in that order
 hipError_t launch_wgrad_reduce(int N, int K, int splits, const float *parts, float *dW, int64_t ldw, hipStream_t s);
 // split_gemm.hip: dW (or Z) with the operands packed as bf16 parts into ws

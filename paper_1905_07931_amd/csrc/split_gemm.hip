@@ -9,7 +9,7 @@
 // fp32.  What is left out (mid lo, lo mid, lo lo) is at most 2^-23 of |a b|, of
 // random sign.  16 products are summed per instruction instead of 2, so there
 // are fewer roundings than in the fp32 instruction's sum: at 4096 x 9216 x
-// 1024 the result is 4.9e-7 off the 64-bit one (2-norm), 5.7e-7 with
+// 1024 the result is 1.8e-7 off the 64-bit one (2-norm), 5.7e-7 with
 // v_mfma_f32_32x32x2_f32.  The bf16 pipe is 16x the fp32 one, so six products
 // have 2.7x its peak.  Two parts (hi, lo) with three terms are the BF16X3
 // arithmetic (2^-16 left out).
@@ -234,7 +234,7 @@ __global__ __launch_bounds__(256) void pack_spmm_kernel(int n_rows, const int *_
         }
 #pragma unroll
         for (int u = 0; u < 4; ++u)
-            if (c[u] >= 0) tile[r * kCsrStride + c[u]] = v[u];
+            if ((unsigned)c[u] < (unsigned)kPackK) tile[r * kCsrStride + c[u]] = v[u];  // (columns ascend in a row)
     }
     __syncthreads();
 #pragma unroll
@@ -300,8 +300,9 @@ enum {
 //   that, and the large terms moved to a third set every six
 //   steps (its chain and theirs are then both short)         8.6e-8 / 7.5e-8
 // The sums that a kernel replaces set which one it needs: a row of fp32 matrix
-// instructions 5.7e-7 / 4.1e-7 (the dense gradient: one set), a sequential fp32
-// row sum 3-5e-7 (the sparse products: two), a tree over 64 lanes 8.5e-8 (the
+// instructions 5.7e-7 / 4.1e-7 (the dense gradient: two sets, since a product
+// that the fp32 tiles split into two ranges may be whole here; two parts: one,
+// their 2^-16 decides), a sequential fp32 row sum 3-5e-7 (the sparse products: two), a tree over 64 lanes 8.5e-8 (the
 // masked gradient: three).  The second set is free (353 and 354 us at 4096 x
 // 9216 x 1024), the third costs 3 %.
 enum { kAccOne = 1, kAccSmall = 2, kAccTree = 3 };
@@ -570,8 +571,28 @@ hipError_t launch_tiles(gemm_args G, int splits, hipStream_t s) {
     return hipGetLastError();
 }
 
+// Ranges of the reduction: as many as give every CU one workgroup (of >= 256
+// indices each).  From 129 tiles on a product is whole: partial results that are
+// written, added and, without the fused epilogue, read again by the prox cost
+// more than the second workgroup on a CU gives.  us for dense_wgrad, prox,
+// with the 512 workgroups that the fp32 tiles want -> 256: 503 x 7856 x 736 58.9
+// -> 50.6, 73.0 -> 58.6; 1200 x 3000 x 1000 64.8 -> 54.2, 79.8 -> 62.7; BF16X3 1500 x
+// 2000 x 600 31.7 -> 28.0, 45.3 -> 37.1; 1024 x 1024 x 1024 29.4 -> 30.4, 34.8 -> 35.1.
+wgrad_split split_plan(int N, int K, int B) {
+    wgrad_split p{1, B};
+    const int64_t tiles = ceil_div(N, BM) * ceil_div(K, BN);
+    int64_t s = tiles > 0 ? 256 / tiles : 1;
+    s = s < B / 256 ? s : B / 256;
+    s = s < 64 ? s : 64;
+    if (s < 2) return p;
+    const int64_t chunk = ceil_div(ceil_div(B, s), 2 * kStep) * 2 * kStep;
+    p.splits = (int)ceil_div(B, chunk);
+    p.chunk = (int)chunk;
+    return p;
+}
+
 // dY . X^T with the operands packed into ws; a product of few tiles splits its
-// reduction by wgrad_plan() into partial results behind the packed operands,
+// reduction by split_plan() into partial results behind the packed operands,
 // which wgrad_reduce_kernel adds in order
 template <int NP, int EPI>
 hipError_t wgrad(int N, int K, int B, const float *dY, int64_t ldy, const float *X, int64_t ldx, float *C,
@@ -587,12 +608,15 @@ hipError_t wgrad(int N, int K, int B, const float *dY, int64_t ldy, const float 
     G.a32 = dY; G.lda = ldy; G.b32 = X; G.ldb = ldx;
     G.split_steps = G.A.steps;
     G.C = C; G.ldc = ldc; G.P = P;
-    const wgrad_split w = wgrad_plan(N, K, B);
-    if (w.splits == 1) return launch_tiles<NP, EPI, kAccOne>(G, 1, s);
+    // three parts: the small terms apart, which makes a whole sum at least as
+    // exact as the fp32 instruction's over half as many indices
+    constexpr int ACC = NP == 3 ? kAccSmall : kAccOne;
+    const wgrad_split w = split_plan(N, K, B);
+    if (w.splits == 1) return launch_tiles<NP, EPI, ACC>(G, 1, s);
     float *parts = reinterpret_cast<float *>(p);
     G.split_steps = w.chunk / kStep;
     G.C = parts; G.ldc = K;
-    e = launch_tiles<NP, kEpiStore, kAccOne>(G, w.splits, s);
+    e = launch_tiles<NP, kEpiStore, ACC>(G, w.splits, s);
     if (e != hipSuccess) return e;
     return launch_wgrad_reduce(N, K, w.splits, parts, C, ldc, s);
 }
@@ -621,11 +645,12 @@ size_t split_wgrad_bytes(int N, int K, int B, int precision) {
     }
     if (B > (1 << 22)) return 0;  // 32-bit offsets inside a group
     const int np = f32 ? 3 : 2;
+    // (split_plan() makes no more ranges than wgrad_plan())
     return (size_t)(packed_bytes(N, B, np) + flag_bytes(N, B) + packed_bytes(K, B, np) + flag_bytes(K, B)) +
            wgrad_workspace_bytes(N, K, B);
 }
 
-bool split_wgrad_prox_fused(int N, int K, int B) { return wgrad_plan(N, K, B).splits == 1; }
+bool split_wgrad_prox_fused(int N, int K, int B) { return split_plan(N, K, B).splits == 1; }
 
 hipError_t launch_split_wgrad(int N, int K, int B, int precision, const float *dY, int64_t ldy, const float *X,
                               int64_t ldx, float *dW, int64_t ldw, void *ws, hipStream_t s) {
@@ -643,19 +668,22 @@ hipError_t launch_split_wgrad_prox(int N, int K, int B, int precision, const flo
 // gv = dY . X^T on W's pattern: the whole product, its epilogue writing the
 // stored entries.  Taken where the modelled time is shorter than the entry-wise
 // kernels' (both models in us, fitted to calls on the chip): theirs is nnz * B
-// products at 6.6 per ps (dense patterns 12, rows not 16-byte aligned 3) or an
+// products at 6.6 per ps (dense patterns 12, rows not 16-byte aligned 3.5) or an
 // entry's fixed cost, this
-// one's the packing, N * K * B products at tile granularity and the bitmap index.
+// one's the packing, N * K * B products at tile granularity (few tiles: the steps
+// of one, 0.55 us each) and the bitmap index.
 // Measured at 4096 x 4096 x 512, entry-wise -> whole: 5 % stored 81 -> 105, 10 %
 // 135 -> 106, 20 % 259 -> 111, 50 % 369 -> 128; 4096 x 9216 x 1024 at 9 % 693 ->
-// 393; 1000 x 1000 x 256 at 20 % 22 -> 29.
+// 393; 503 x 7856 x 736 at 20 % 143 -> 68, 1738 x 1321 x 531 77 -> 45 (10 % 40 -> 44);
+// 1000 x 1000 x 256 at 20 % 22 -> 29, 1024 x 1024 x 1024 43 -> 57.
 size_t packed_sddmm_bytes(int N, int K, int64_t nnz, int B) {
-    if (B < 32 || B > (1 << 22) || N == 0 || K == 0 || wgrad_plan(N, K, B).splits > 1) return 0;
+    if (B < 32 || B > (1 << 22) || N == 0 || K == 0) return 0;
     const double np = (double)ceil_div(N, BM) * BM, kp = (double)ceil_div(K, BN) * BN, n = (double)nnz;
-    const double whole = 24 + 10.0 * ((double)N + K) * B / 5e6 + 12 * np * kp * B / 1.25e9 + n / 250e3;
-    const double rate = B % 4 ? 3e6 : (3 * n > (double)N * K ? 12e6 : 6.6e6);  // products per us
+    const double mfma = 12 * np * kp * B / 1.25e9, chain = 0.55 * ceil_div(B, kStep);
+    const double whole = 24 + 10.0 * ((double)N + K) * B / 5e6 + (mfma > chain ? mfma : chain) + n / 250e3;
+    const double rate = B % 4 ? 3.5e6 : (3 * n > (double)N * K ? 12e6 : 6.6e6);  // products per us
     const double products = n * B / rate, fixed = n / 23e3;
-    if (whole > 0.95 * (14 + (products > fixed ? products : fixed))) return 0;
+    if (whole > 0.88 * (14 + (products > fixed ? products : fixed))) return 0;
     return (size_t)(packed_bytes(N, B, 3) + flag_bytes(N, B) + packed_bytes(K, B, 3) + flag_bytes(K, B)) +
            2 * (size_t)ceil_div(word_counts_bytes(N, K), 256) * 256;
 }

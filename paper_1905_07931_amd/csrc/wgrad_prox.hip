@@ -435,7 +435,7 @@ hipError_t launch_wgrad_prox(int N, int K, int B, const float *dY, int64_t ldy, 
     P.kw = (int)ceil_div(K, 32);
     P.counts = counts;
     const size_t packed = split_wgrad_bytes(N, K, B, precision);
-    const bool split = packed > 0 && ws != nullptr && ws_bytes >= packed;
+    const bool split = packed_room(packed, ws, ws_bytes);
     if (split && split_wgrad_prox_fused(N, K, B))
         return launch_split_wgrad_prox(N, K, B, precision, dY, ldy, X, ldx, Z, ldz, P, ws, s);
     if (!split && precision == kPrecF32 && wgrad_f32_prox_slab(N, K, B) > 0)

@@ -61,7 +61,7 @@ def test_packed_products(N, K, B, d, pattern):
 
 
 @pytest.mark.parametrize("N,K,B,d,pattern", [(1024, 2048, 256, 0.4, "uniform"), (2049, 3001, 97, 0.3, "uniform"),
-                                             (2177, 2050, 333, 0.25, "zipf")])
+                                             (2177, 2050, 333, 0.25, "zipf"), (600, 1300, 530, 0.4, "uniform")])
 def test_packed_masked_gradient(N, K, B, d, pattern):
     W, dense, rp, ci, X, dY = layer(N, K, B, d, seed=B, pattern=pattern)
     assert L1.workspace_bytes(L1.OP_SDDMM_PACKED, N, K, W.nnz, B) > 0

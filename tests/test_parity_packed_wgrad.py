@@ -26,10 +26,12 @@ def bound(B, prec):
 
 
 # one tile exactly, one row / column / index past tiles and steps, less than a
-# tile, a partial last band of tile rows, split reductions (< 256 tiles, B >= 512)
+# tile, a partial last band of tile rows, split reductions (B >= 512) of 24, 2 and,
+# on both sides of the last split, 128 and 129 tiles
 @pytest.mark.parametrize("N,K,B,pad", [(128, 128, 160, 0), (129, 257, 161, 0), (127, 1, 175, 3), (1, 300, 320, 0),
                                        (1153, 2177, 333, 0), (2049, 2100, 97, 1), (300, 1000, 1024, 0),
-                                       (65, 129, 4097, 2), (1100, 1300, 777, 0)])
+                                       (65, 129, 4097, 2), (1100, 1300, 777, 0),
+                                       (1024, 2048, 515, 0), (300, 5500, 516, 1)])
 @pytest.mark.parametrize("prec", [L1.F32, L1.BF16X3])
 def test_packed_wgrad(N, K, B, pad, prec):
     dYh, Xh = operands(N, K, B, seed=N + K + B, pad=pad)
@@ -91,7 +93,7 @@ def test_packed_wgrad_nonfinite(prec):
     assert (np.abs(got[ok] - ref[ok].astype(np.float64)) <= 1e-4 * m[ok]).all()
 
 
-@pytest.mark.parametrize("N,K,B", [(1153, 2177, 333), (300, 1000, 1024)])
+@pytest.mark.parametrize("N,K,B", [(1153, 2177, 333), (300, 1000, 1024), (300, 5500, 516)])
 @pytest.mark.parametrize("prec", [L1.F32, L1.BF16X3])
 def test_packed_prox_equals_the_calls(N, K, B, prec):
     # the fused update and dense_wgrad + prox_l1_recompress: the same bits
