@@ -21,6 +21,7 @@
 // per-range sums go to scratch and a second pass adds them in range order.
 #include "common.hpp"
 #include "launch.hpp"
+#include "seg.hpp"
 
 namespace l1csr {
 
@@ -67,41 +68,56 @@ __device__ __forceinline__ void load_vec(const float *p, float (&v)[VEC]) {
     }
 }
 
-// Extra pieces (row, j), j = 1 .. k_row - 1 with k_row = ceil(len / lsplit),
-// listed in row order; their number goes to *ext_n.  One workgroup walks the
-// rows in tiles with a carried offset.
-__global__ __launch_bounds__(1024) void sddmm_extra_kernel(int n_rows, const int *__restrict__ ptr,
-                                                           int lsplit, int2 *__restrict__ ext,
-                                                           int *__restrict__ ext_n) {
-    __shared__ int wave_tot[16];
-    __shared__ int carry_s;
+// What the gather needs besides the CSR, in one launch.  Workgroup 0: the extra
+// pieces (row, j), j = 1 .. k_row - 1 with k_row = ceil(len / lsplit), listed in
+// row order, their number in *ext_n; it walks the rows with a carried offset,
+// ROWS consecutive ones a thread: four, so that 4096 rows take one round, or one
+// up to 1024 rows (a thread then lists one row's pieces: 500 x 800 x 300 at 10 %
+// 15.4 us a call, 16.3 with four).  The others, if R > 1: the rows' column-range
+// bounds, a row per wave.  Both are latency, 4.8 and 5.7 us one after another,
+// 4.6 together: the debiasing step at 4096 x 4096 x 512 and 1 % 73.1 -> 68.9, the
+// call at 2958 x 1017 x 960 and 5 % 39.3 -> 35.1.
+constexpr int kPrepThreads = 1024;
+
+template <int ROWS>
+__global__ __launch_bounds__(kPrepThreads) void sddmm_prep_kernel(int n_rows, const int *__restrict__ ptr,
+                                                                  const int *__restrict__ idx, int lsplit,
+                                                                  int2 *__restrict__ ext, int *__restrict__ ext_n,
+                                                                  int R, int shift, int *__restrict__ seg) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    if (tid == 0) carry_s = 0;
-    __syncthreads();
-    for (int base = 0; base < n_rows; base += 1024) {
-        const int i = base + tid;
-        int e = 0;
-        if (i < n_rows) {
-            const int len = ptr[i + 1] - ptr[i];
-            e = len > lsplit ? (len + lsplit - 1) / lsplit - 1 : 0;
-        }
-        const int incl = wave_incl_scan(e);
-        if (lane == 63) wave_tot[wave] = incl;
-        __syncthreads();
-        if (wave == 0) {
-            const int t = lane < 16 ? wave_tot[lane] : 0;
-            const int ti = wave_incl_scan(t);
-            if (lane < 16) wave_tot[lane] = ti - t;
-        }
-        __syncthreads();
-        const int carry = carry_s;
-        const int off = carry + wave_tot[wave] + incl - e;
-        for (int j = 0; j < e; ++j) ext[off + j] = make_int2(i, j + 1);
-        __syncthreads();
-        if (tid == 1023) carry_s = off + e;
-        __syncthreads();
+    if (blockIdx.x > 0) {
+        const int row = uniform(((int)blockIdx.x - 1) * (kPrepThreads / kWave) + wave);
+        if (row < n_rows) seg_row(row, R, shift, ptr, idx, seg);
+        return;
     }
-    if (tid == 0) *ext_n = carry_s;
+    __shared__ int wave_tot[2][kPrepThreads / kWave];  // (two: the next rows' totals while these are read)
+    int carry = 0, buf = 0;
+    for (int base = 0; base < n_rows; base += kPrepThreads * ROWS, buf ^= 1) {
+        const int i0 = base + tid * ROWS;
+        int at[ROWS + 1], e[ROWS], mine = 0;
+#pragma unroll
+        for (int u = 0; u <= ROWS; ++u) at[u] = ptr[min(i0 + u, n_rows)];  // rows past the last are empty
+#pragma unroll
+        for (int u = 0; u < ROWS; ++u) {
+            const int len = at[u + 1] - at[u];
+            e[u] = len > lsplit ? (len + lsplit - 1) / lsplit - 1 : 0;
+            mine += e[u];
+        }
+        const int incl = wave_incl_scan(mine);
+        if (lane == kWave - 1) wave_tot[buf][wave] = incl;
+        __syncthreads();
+        int off = carry + incl - mine;
+#pragma unroll
+        for (int w = 0; w < kPrepThreads / kWave; ++w) {
+            const int t = wave_tot[buf][w];
+            off += w < wave ? t : 0;
+            carry += t;
+        }
+#pragma unroll
+        for (int u = 0; u < ROWS; ++u)
+            for (int j = 0; j < e[u]; ++j) ext[off++] = make_int2(i0 + u, j + 1);
+    }
+    if (tid == 0) *ext_n = carry;
 }
 
 // The entries of one item in steps of G: loads of all G entries issued
@@ -584,10 +600,14 @@ hipError_t launch_sddmm(int n_rows, int n_cols, int64_t nnz, const int *ptr, con
     const bool v4 = (B % 4 == 0) && (ldx % 4 == 0) && (ldy % 4 == 0) && aligned16(X) && aligned16(dY);
     const gplan pl = make_plan(n_rows, n_cols, nnz, B, v4);
     const gwork w = carve(pl, n_rows, nnz, ws);
-    if (pl.R > 1 && (e = launch_seg(n_rows, pl.R, pl.shift, ptr, idx, w.seg, s)) != hipSuccess) return e;
     if (pl.extras) {
-        sddmm_extra_kernel<<<1, 1024, 0, s>>>(n_rows, ptr, pl.lsplit, w.ext, w.ext_n);
+        const int64_t seg_blocks = pl.R > 1 ? ceil_div(n_rows, kPrepThreads / kWave) : 0;
+        const auto prep = n_rows <= kPrepThreads ? sddmm_prep_kernel<1> : sddmm_prep_kernel<4>;
+        prep<<<(unsigned)(1 + seg_blocks), kPrepThreads, 0, s>>>(n_rows, ptr, idx, pl.lsplit, w.ext, w.ext_n, pl.R,
+                                                               pl.shift, w.seg);
         if ((e = hipGetLastError()) != hipSuccess) return e;
+    } else if (pl.R > 1 && (e = launch_seg(n_rows, pl.R, pl.shift, ptr, idx, w.seg, s)) != hipSuccess) {
+        return e;
     }
     float *out = pl.nbr > 1 ? w.part : gv;
     if (pl.block) {
