@@ -720,9 +720,16 @@ hipError_t launch_packed_sddmm(int N, int K, const int *ptr, const int *idx, con
 // 114, 50 % 316 -> 128; 4096 x 9216 x 1024 at 9 % 357 -> 401 (W^T 299 -> 445);
 // 2049 x 3001 x 333 at 30 % 225 -> 59; 2000 x 700 x 1000 at 25 % 66 -> 39.
 namespace {
-wgrad_split spmm_splits(int N, int K, int B) {  // ranges of whole 256-index blocks, about 512 workgroups
+// Ranges of whole 256-index blocks, about 512 workgroups; ranges of a single block
+// only for the first 256 of them (a partial sum costs as much as some 200 indices:
+// 6544 x 522 x 832 67 -> 53 us whole, 1000 x 4000 x 300 48.5 -> 44.6 with 8 ranges for
+// 16, 2048 x 2048 x 512 46.4 -> 43.6; 2000 x 700 x 1000 39.3 -> 41.8.  256 workgroups
+// for all: 3000 x 3000 x 700 111 -> 130, 4096 x 4096 x 512 at 10 % 117 -> 126)
+wgrad_split spmm_splits(int N, int K, int B) {
     const int64_t tiles = ceil_div(N, BM) * ceil_div(B, BN), kb = ceil_div(K, kPackK);
     int64_t s = tiles >= 384 ? 1 : ceil_div(512, tiles);
+    const int64_t two = kb / 2, fill = ceil_div(256, tiles), most = two > fill ? two : fill;
+    s = s < most ? s : most;
     s = s < kb ? s : kb;
     const int64_t per = ceil_div(kb, s > 0 ? s : 1);
     return wgrad_split{(int)ceil_div(kb, per), (int)per * kPackK};
