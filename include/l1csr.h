@@ -136,8 +136,8 @@ int l1csr_host_free_mapped(void *host);
  * bytes (0: not taken at these sizes) a product over a dense pattern packs W,
  * zeros written out, and X as bf16 parts into ws and runs on the matrix cores
  * as dense_wgrad's packed products do (all 24 significand bits, fp32 sums by
- * 16 columns; ranges of columns summed apart and added in order).  Where a
- * value's parts would over- or underflow the stored entries are summed in
+ * 16 columns; ranges of columns summed apart and added in order).  Where an
+ * operand is NaN, infinite or beyond 2^28 the stored entries are summed in
  * ascending p order instead.
  */
 int csr_spmm_fwd(int32_t n_rows, int32_t n_cols, int64_t nnz,
@@ -249,8 +249,8 @@ int csr_spmm_bwd_t(int32_t n_rows, int32_t n_cols, int64_t nnz,
  * first, split into bf16 parts: F32 into three that hold all 24 significand
  * bits, six exact products per pair (those left out are at most 2^-23 of it)
  * and fp32 sums, so the result is as close to the exact one as the fp32
- * instruction's.  Operands whose parts would over- or underflow (NaN,
- * infinities, beyond 2^60, rows all below 2^-100) take the fp32 instruction.
+ * instruction's, down to the smallest subnormal and whatever the values beside
+ * it.  NaN, infinities and operands beyond 2^28 take the fp32 instruction.
  */
 int dense_wgrad(int32_t N, int32_t K, int32_t B,
                 const float *dY, int64_t ldy, const float *X, int64_t ldx,

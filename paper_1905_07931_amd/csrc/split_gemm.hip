@@ -14,11 +14,14 @@
 // have 2.7x its peak.  Two parts (hi, lo) with three terms are the BF16X3
 // arithmetic (2^-16 left out).
 //
-// The exactness of the parts holds for |x| in [2^-100, 2^60] (no part under- or
-// overflows) and for zeros.  The pack kernel flags every (32-row group,
-// 256-index block) that holds a NaN, an infinity, an |x| above 2^60 or a row
-// whose values there are all below 2^-100; tiles that touch a flagged group
-// run the fp32 matrix-core instruction on the operands themselves.
+// The parts are those of 2^24 x, and a sum is scaled back by 2^-48 (both exact,
+// but for a result that is itself subnormal): the last bit of the smallest fp32
+// number, 2^-149, then lies at 2^-125, so no part underflows, whatever stands
+// beside it.  The parts hold every |x| up to 2^28, with which no sum of 2^22
+// products overflows (2^126).  The pack kernel flags every (32-row group,
+// 256-index block) that holds a NaN, an infinity or an |x| above 2^28; tiles that
+// touch a flagged group run the fp32 matrix-core instruction on the operands
+// themselves.
 //
 // What bounds it: the matrix pipe, and through it the power limit.  With every
 // CU's matrix pipe 71 % busy the shader clock falls to 1.64 GHz (2.38 GHz under
@@ -41,7 +44,8 @@ constexpr int kGroup = 32;         // rows of a packed group
 constexpr int kStep = 16;          // reduction indices of a packed block
 constexpr int kBlockBytes = 1024;  // one part of a (group, step): 64 lanes x 16 bytes
 constexpr int kPackK = 256;        // reduction indices of a pack workgroup (one flag)
-constexpr float kPartMax = 0x1p60f, kPartMin = 0x1p-100f;
+constexpr float kPartMax = 0x1p28f, kPartScale = 0x1p24f;
+constexpr float kSumScale = 1.f / (kPartScale * kPartScale);
 
 // A packed operand: [group][step][part][lane][8] bf16.  Lane l of a block holds
 // row l % 32 of the group and reduction indices 8 (l / 32) .. + 7 of the step,
@@ -77,7 +81,7 @@ template <int NP>
 __device__ __forceinline__ void split8(const float (&x)[8], bf16x8 (&p)[NP]) {
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-        float r = x[e];
+        float r = x[e] * kPartScale;
 #pragma unroll
         for (int q = 0; q < NP; ++q) {
             const __bf16 h = (__bf16)r;
@@ -105,8 +109,7 @@ __device__ __forceinline__ void store_flag(unsigned *rowmax, unsigned mx, int *f
     __syncthreads();
     if (threadIdx.x < kWave) {
         const unsigned m = rowmax[lane & 31];
-        const bool odd = m > __float_as_uint(kPartMax) || (m != 0u && m < __float_as_uint(kPartMin));
-        const uint64_t any = __ballot(odd);
+        const uint64_t any = __ballot(m > __float_as_uint(kPartMax));
         if (lane == 0) *flag = any != 0ull;
     }
 }
@@ -469,8 +472,12 @@ __global__ __launch_bounds__(NT, 2) void split_gemm_kernel(gemm_args G) {
                         acc[a][b][r] = 0.f;
                     });
         }
-        if constexpr (ACC == kAccTree) each([&](int a, int b, int r) { acc[a][b][r] += top[a][b][r]; });
-        if constexpr (ACC != kAccOne) each([&](int a, int b, int r) { acc[a][b][r] += small[a][b][r]; });
+        each([&](int a, int b, int r) {
+            float sum = acc[a][b][r];
+            if constexpr (ACC == kAccTree) sum += top[a][b][r];
+            if constexpr (ACC != kAccOne) sum += small[a][b][r];
+            acc[a][b][r] = sum * kSumScale;
+        });
     } else if constexpr (EPI == kEpiSpmm) {
         // not exact in parts: the stored entries of A alone (a zero of the
         // packed copy would turn an infinity of B into NaN), a thread per column

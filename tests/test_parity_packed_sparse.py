@@ -95,3 +95,25 @@ def test_packed_products_odd_values():
     ok = np.isfinite(ref)
     m = np.abs(dense) @ np.where(np.isfinite(X), np.abs(X.astype(np.float64)), 0)
     assert (np.abs(got[ok] - ref[ok]) <= 1e-4 * m[ok] + 2.0 ** -149 * K).all()
+
+
+def test_packed_products_small_beside_large():
+    # rows of normal values that meet zeros alone, beside others of 2^-80 to 2^-145
+    N, K, B = 1024, 2048, 256
+    W, dense, rp, ci, X, dY = layer(N, K, B, 0.4, seed=11)
+    assert L1.workspace_bytes(L1.OP_SPMM_PACKED, N, K, W.nnz, B) > 0
+    assert L1.workspace_bytes(L1.OP_SDDMM_PACKED, N, K, W.nnz, B) > 0
+    small = np.exp2(-np.linspace(80, 145, N)).astype(np.float32)
+    rows = np.repeat(np.arange(N), np.diff(rp))
+    W.vals.copy_(t(np.where(ci % 2 == 1, small[rows], np.float32(1)) * h(W.vals)))
+    dense[rows, ci] = h(W.vals)
+    Xf = (X * np.float32(2.0 ** 27)).astype(np.float32)
+    Xf[0::2] = 0
+    got, x = h(L1.csr_spmm_fwd(W, t(Xf))).astype(np.float64), Xf.astype(np.float64)
+    assert (np.abs(got - dense @ x) <= bound(6 * K) * (np.abs(dense) @ x)).all()
+    dY[:, 1::2] *= small[:, None]
+    Xg = (X * np.float32(2.0 ** 27)).astype(np.float32)
+    Xg[:, 0::2] = 0
+    gv = h(L1.sddmm_masked_wgrad(W, t(dY), t(Xg))).astype(np.float64)[:W.nnz]
+    a, x = dY.astype(np.float64), Xg.astype(np.float64)
+    assert (np.abs(gv - (a @ x.T)[rows, ci]) <= bound(6 * B) * (np.abs(a) @ x.T)[rows, ci]).all()

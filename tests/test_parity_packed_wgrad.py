@@ -74,6 +74,20 @@ def test_packed_wgrad_scales(scale_a, scale_x):
 
 
 @pytest.mark.parametrize("prec", [L1.F32, L1.BF16X3])
+def test_packed_wgrad_small_beside_large(prec):
+    # every row of dY holds normal values and others some 2^-80 to 2^-145 (down to subnormals
+    # of a few bits) that alone meet nonzeros of X: the error stays relative to their products
+    N, K, B = 130, 260, 322
+    dYh, Xh = operands(N, K, B, seed=8)
+    dYh[:, 1::2] *= np.exp2(-np.linspace(80, 145, N))[:, None].astype(np.float32)
+    Xh[:, 0::2] = 0
+    Xh[:, 1::2] *= np.float32(2.0 ** 27)
+    got = h(L1.dense_wgrad(t(dYh), t(Xh), precision=prec)).astype(np.float64)
+    a, x = dYh.astype(np.float64), Xh.astype(np.float64)
+    assert (np.abs(got - a @ x.T) <= bound(B, prec) * (np.abs(a) @ np.abs(x).T)).all()
+
+
+@pytest.mark.parametrize("prec", [L1.F32, L1.BF16X3])
 def test_packed_wgrad_nonfinite(prec):
     # infinities and NaN reach exactly the entries that multiply them
     N, K, B = 260, 390, 322
