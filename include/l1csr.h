@@ -136,9 +136,10 @@ int l1csr_host_free_mapped(void *host);
  * bytes (0: not taken at these sizes) a product over a dense pattern packs W,
  * zeros written out, and X as bf16 parts into ws and runs on the matrix cores
  * as dense_wgrad's packed products do (all 24 significand bits, fp32 sums by
- * 16 columns; ranges of columns summed apart and added in order).  Where an
- * operand is NaN, infinite or beyond 2^28 the stored entries are summed in
- * ascending p order instead.
+ * 16 columns; ranges of columns summed apart and added in order).  Blocks of 32
+ * rows (of X: 32 batch columns) by 256 columns of W that hold a NaN, an infinity
+ * or a value beyond 2^28 are summed apart, the stored entries alone in ascending
+ * p order, and added block by block.
  */
 int csr_spmm_fwd(int32_t n_rows, int32_t n_cols, int64_t nnz,
                  const int32_t *row_ptr, const int32_t *col_idx, const float *vals,
@@ -250,7 +251,8 @@ int csr_spmm_bwd_t(int32_t n_rows, int32_t n_cols, int64_t nnz,
  * bits, six exact products per pair (those left out are at most 2^-23 of it)
  * and fp32 sums, so the result is as close to the exact one as the fp32
  * instruction's, down to the smallest subnormal and whatever the values beside
- * it.  NaN, infinities and operands beyond 2^28 take the fp32 instruction.
+ * it.  Blocks of 32 rows by 256 batch indices that hold a NaN, an infinity or a
+ * value beyond 2^28 are multiplied by the fp32 instruction and added.
  */
 int dense_wgrad(int32_t N, int32_t K, int32_t B,
                 const float *dY, int64_t ldy, const float *X, int64_t ldx,

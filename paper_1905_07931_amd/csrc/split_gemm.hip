@@ -19,9 +19,14 @@
 // number, 2^-149, then lies at 2^-125, so no part underflows, whatever stands
 // beside it.  The parts hold every |x| up to 2^28, with which no sum of 2^22
 // products overflows (2^126).  The pack kernel flags every (32-row group,
-// 256-index block) that holds a NaN, an infinity or an |x| above 2^28; tiles that
-// touch a flagged group run the fp32 matrix-core instruction on the operands
-// themselves.
+// 256-index block) that holds a NaN, an infinity or an |x| above 2^28 and leaves
+// its parts zero; a tile adds the products of its flagged blocks (both operands'
+// groups over those 256 indices) from the operands themselves, by the fp32
+// matrix-core instruction, or over a CSR operand entry by entry.  What that
+// costs, us per call for ordinary operands, one infinity in X and 2 % of X
+// infinite (a flag on every block): forward product 4096 x 4096 x 512 at 20 %
+// 128 / 197 / 1450 (7000 and 8200 with whole tiles
+// left to a thread per column), gradient 102 / 115 / 215; gradient 4096 x 9216 x 1024 399 / 410 / 821.
 //
 // What bounds it: the matrix pipe, and through it the power limit.  With every
 // CU's matrix pipe 71 % busy the shader clock falls to 1.64 GHz (2.38 GHz under
@@ -102,16 +107,21 @@ __device__ __forceinline__ void pack8(const float (&x)[8], unsigned &mx, char *d
     for (int q = 0; q < NP; ++q) *reinterpret_cast<bf16x8 *>(d + q * kBlockBytes) = p[q];
 }
 
-// rowmax: the 32 rows' magnitudes in LDS (zeroed, a barrier behind it); ends the workgroup's pack
-__device__ __forceinline__ void store_flag(unsigned *rowmax, unsigned mx, int *flag) {
+// Ends the workgroup's pack of block kb of group g: stores its flag and zeroes the
+// parts of a flagged block.  rowmax: the 32 rows' magnitudes in LDS (zeroed, a
+// barrier behind it).
+template <int NP>
+__device__ __forceinline__ void store_flag(unsigned *rowmax, unsigned mx, const packed &o, int g, int kb) {
     const int lane = threadIdx.x & 63;
     atomicMax(&rowmax[lane & 31], mx);
-    __syncthreads();
-    if (threadIdx.x < kWave) {
-        const unsigned m = rowmax[lane & 31];
-        const uint64_t any = __ballot(m > __float_as_uint(kPartMax));
-        if (lane == 0) *flag = any != 0ull;
-    }
+    __syncthreads();  // (the waves' parts are stored)
+    if (threadIdx.x >= kWave) return;
+    const bool odd = __ballot(rowmax[lane & 31] > __float_as_uint(kPartMax)) != 0ull;
+    if (lane == 0) o.flags[g * o.kblocks + kb] = odd;
+    if (!odd) return;
+    const int s0 = kb * (kPackK / kStep), n = min(kPackK / kStep, o.steps - s0) * NP;
+    char *d = o.data + ((int64_t)g * o.steps + s0) * (NP * kBlockBytes) + lane * 16;
+    for (int q = 0; q < n; ++q) *reinterpret_cast<bf16x8 *>(d + q * kBlockBytes) = bf16x8{};
 }
 
 // one operand of a pack launch: rows of a row-major fp32 matrix, the reduction
@@ -157,7 +167,7 @@ __global__ __launch_bounds__(256) void pack_rows_kernel(pack_src s0, pack_src s1
         }
         pack8<NP>(x, mx, s.out.data + ((int64_t)g * s.out.steps + st) * (NP * kBlockBytes) + lane * 16);
     }
-    store_flag(rowmax, mx, &s.out.flags[g * s.out.kblocks + blockIdx.y]);
+    store_flag<NP>(rowmax, mx, s.out, g, blockIdx.y);
 }
 
 // Both operands of a sparse product in one launch: a CSR matrix (the first
@@ -195,7 +205,7 @@ __global__ __launch_bounds__(256) void pack_spmm_kernel(int n_rows, const int *_
             for (int e = 0; e < 8; ++e) x[e] = col < cols && k + e < Kr ? X[(int64_t)(k + e) * ldx + col] : 0.f;
             pack8<3>(x, mx, B.data + ((int64_t)g * B.steps + st) * (3 * kBlockBytes) + lane * 16);
         }
-        store_flag(rowmax, mx, &B.flags[g * B.kblocks + kb]);
+        store_flag<3>(rowmax, mx, B, g, kb);
         return;
     }
     const int g = blockIdx.x;
@@ -250,7 +260,7 @@ __global__ __launch_bounds__(256) void pack_spmm_kernel(int n_rows, const int *_
         const float x[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
         pack8<3>(x, mx, A.data + ((int64_t)g * A.steps + st) * (3 * kBlockBytes) + lane * 16);
     }
-    store_flag(rowmax, mx, &A.flags[g * A.kblocks + kb]);
+    store_flag<3>(rowmax, mx, A, g, kb);
 }
 
 __device__ __forceinline__ floatx16 mfma16(bf16x8 a, bf16x8 b, floatx16 c) {
@@ -314,8 +324,9 @@ constexpr int kTreeSteps = 6;  // a multiple of the three steps in LDS
 struct gemm_args {
     int M, Nn, Kr;                // sizes (Kr: all reduction indices)
     packed A, B;
-    const float *a32, *b32;       // the operands themselves, for flagged groups
+    const float *a32, *b32;       // the operands themselves, for flagged blocks
     int64_t lda, ldb;
+    int a_v4, b_v4;               // their rows are 16-byte aligned
     int tiles_m, tiles_n;
     int split_steps;              // steps per split (blockIdx.y); the splits' C are M * ldc apart
     float *C;
@@ -374,10 +385,10 @@ __global__ __launch_bounds__(NT, 2) void split_gemm_kernel(gemm_args G) {
 #pragma unroll
         for (int j = 0; j < LPW; ++j) dma16(src[j], off, dst + j * (NT / kWave) * kBlockBytes);
     };
-    // flagged groups of the tile (the same answer in every wave)
+    // flagged blocks of the tile (the same answer in every wave)
+    const int kb0 = c0 / (kPackK / kStep), kb1 = (c0 + steps + kPackK / kStep - 1) / (kPackK / kStep);
     bool odd = false;
     {
-        const int kb0 = c0 / (kPackK / kStep), kb1 = (c0 + steps + kPackK / kStep - 1) / (kPackK / kStep);
         for (int kb = kb0 + (lane >> 3); kb < kb1; kb += 8) {
             const int g = lane & 7;
             const int *f = g < RGA ? G.A.flags + (int64_t)min(tm * RGA + g, G.A.groups - 1) * G.A.kblocks
@@ -400,7 +411,7 @@ __global__ __launch_bounds__(NT, 2) void split_gemm_kernel(gemm_args G) {
     each([&](int a, int b, int r) { acc[a][b][r] = small[a][b][r] = top[a][b][r] = 0.f; });
 
     const int lr = lane & 31, lh = lane >> 5;
-    if (!odd) {  // (the same in every wave: no wave waits for one that left)
+    {
         const int oa = wgm * (NP * kBlockBytes) + lane * 16;
         const int ob = (RGA + wgn) * (NP * kBlockBytes) + lane * 16;
         auto compute = [&](const char *cur) {
@@ -478,43 +489,48 @@ __global__ __launch_bounds__(NT, 2) void split_gemm_kernel(gemm_args G) {
             if constexpr (ACC != kAccOne) sum += small[a][b][r];
             acc[a][b][r] = sum * kSumScale;
         });
-    } else if constexpr (EPI == kEpiSpmm) {
-        // not exact in parts: the stored entries of A alone (a zero of the
-        // packed copy would turn an infinity of B into NaN), a thread per column
-        const int k0 = c0 * kStep, k1 = min(G.Kr, (c0 + steps) * kStep);
-        float *C = G.C + (int64_t)blockIdx.y * G.M * G.ldc;
-        const int col = n0 + (threadIdx.x & (BN - 1));
-        if (col < G.Nn)
-            for (int row = m0 + threadIdx.x / BN; row < min(m0 + BM, G.M); row += NT / BN) {
-                float sum = 0.f;
-                for (int p = G.ptr[row]; p < G.ptr[row + 1]; ++p) {
-                    const int k = G.idx[p];
-                    if (k >= k0 && k < k1) sum = fmaf(G.vals[p], G.b32[k * G.ldb + col], sum);
-                }
-                C[(int64_t)row * G.ldc + col] = sum;
-            }
-        return;
-    } else {
-        // not exact in parts: the fp32 instruction, lane half h of a pair of indices
-        const int k0 = c0 * kStep, k1 = min(G.Kr, (c0 + steps) * kStep);
-        for (int k = k0; k < k1; k += 2) {
-            const int kk = k + lh;
-            float av[TM], bv[TN];
-#pragma unroll
-            for (int a = 0; a < TM; ++a) {
-                const int row = m0 + (wgm + a) * 32 + lr;
-                av[a] = row < G.M && kk < k1 ? G.a32[row * G.lda + kk] : 0.f;
-            }
-#pragma unroll
-            for (int b = 0; b < TN; ++b) {
-                const int row = n0 + (wgn + b) * 32 + lr;
-                bv[b] = row < G.Nn && kk < k1 ? G.b32[row * G.ldb + kk] : 0.f;
-            }
+    }
+    if constexpr (EPI != kEpiSpmm) {
+        // the flagged blocks: the fp32 instruction, lane half h at indices 4 h .. + 3 of 8
+        for (int kb = odd ? kb0 : kb1; kb < kb1; ++kb) {
+            int fa[TM], fb[TN], any = 0;
 #pragma unroll
             for (int a = 0; a < TM; ++a)
+                any |= fa[a] = uniform(G.A.flags[(int64_t)min(tm * RGA + wgm + a, G.A.groups - 1) * G.A.kblocks + kb]);
+#pragma unroll
+            for (int b = 0; b < TN; ++b)
+                any |= fb[b] = uniform(G.B.flags[(int64_t)min(tn * RGB + wgn + b, G.B.groups - 1) * G.B.kblocks + kb]);
+            if (!any) continue;
+            const int k1 = min(G.Kr, min(c0 + steps, (kb + 1) * (kPackK / kStep)) * kStep);
+            auto load4 = [&](const float *p, int64_t ld, int row, int rows, int v4, int k, float (&x)[4]) {
+                const float *r = p + row * ld + k;
+                if (v4 && row < rows && k + 3 < k1) {
+                    const float4 v = *reinterpret_cast<const float4 *>(r);
+                    x[0] = v.x; x[1] = v.y; x[2] = v.z; x[3] = v.w;
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) x[e] = row < rows && k + e < k1 ? r[e] : 0.f;
+                }
+            };
+#pragma unroll 2
+            for (int k = max(c0, kb * (kPackK / kStep)) * kStep; k < k1; k += 8) {
+                float av[TM][4], bv[TN][4];
+#pragma unroll
+                for (int a = 0; a < TM; ++a)
+                    load4(G.a32, G.lda, m0 + (wgm + a) * 32 + lr, G.M, G.a_v4, k + 4 * lh, av[a]);
 #pragma unroll
                 for (int b = 0; b < TN; ++b)
-                    acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[a], bv[b], acc[a][b], 0, 0, 0);
+                    load4(G.b32, G.ldb, n0 + (wgn + b) * 32 + lr, G.Nn, G.b_v4, k + 4 * lh, bv[b]);
+#pragma unroll
+                for (int a = 0; a < TM; ++a)
+#pragma unroll
+                    for (int b = 0; b < TN; ++b) {
+                        if (!(fa[a] | fb[b])) continue;
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[a][e], bv[b][e], acc[a][b], 0, 0, 0);
+                    }
+            }
         }
     }
     if constexpr (EPI == kEpiProx) {
@@ -560,6 +576,61 @@ __global__ __launch_bounds__(NT, 2) void split_gemm_kernel(gemm_args G) {
                 if (row < G.M) C[(int64_t)row * G.ldc + col] = acc[a][b][r];
             }
         }
+    if constexpr (EPI == kEpiSpmm) {
+        // the flagged blocks: the stored entries of A alone (a zero of the packed
+        // copy would turn an infinity of B into NaN), half a wave per row and 32 columns
+        if (!odd) return;
+        __syncthreads();  // the tile is stored, the LDS buffers are free
+        int2 *ends = reinterpret_cast<int2 *>(S0);  // each row's entries in the block
+        for (int kb = kb0; kb < kb1; ++kb) {
+            const int g = lane & 7;
+            const int *f = g < RGA ? G.A.flags + (int64_t)min(tm * RGA + g, G.A.groups - 1) * G.A.kblocks
+                                   : G.B.flags + (int64_t)min(tn * RGB + g - RGA, G.B.groups - 1) * G.B.kblocks;
+            const unsigned flagged = (unsigned)__ballot(f[kb] != 0) & 0xffu;  // A's groups, then B's
+            if (flagged == 0u) continue;  // (the same in every wave)
+            const int k0 = max(c0, kb * (kPackK / kStep)) * kStep;
+            const int k1 = min(G.Kr, min(c0 + steps, (kb + 1) * (kPackK / kStep)) * kStep);
+            __syncthreads();  // the previous block's bounds are consumed
+            for (int r = threadIdx.x; r < BM; r += NT) {
+                int2 e = make_int2(0, 0);
+                if (m0 + r < G.M) {
+                    const int end = G.ptr[m0 + r + 1];
+                    auto first_at = [&](int lo, int k) {
+                        int hi = end;
+                        while (lo < hi) {
+                            const int mid = lo + (hi - lo) / 2;
+                            if (G.idx[mid] < k) lo = mid + 1; else hi = mid;
+                        }
+                        return lo;
+                    };
+                    e.x = first_at(G.ptr[m0 + r], k0);
+                    e.y = first_at(e.x, k1);
+                }
+                ends[r] = e;
+            }
+            __syncthreads();
+            for (int it = wave * 2 + lh; it < BM * RGB; it += 2 * (NT / kWave)) {
+                const int r = it % BM, cg = it / BM, col = n0 + cg * 32 + lr;
+                if (!(((flagged >> (r >> 5)) | (flagged >> (RGA + cg))) & 1u) || col >= G.Nn) continue;
+                const int2 e = ends[r];
+                if (e.x == e.y) continue;
+                float sum = 0.f;
+                for (int p0 = e.x; p0 < e.y; p0 += 16) {
+                    float v[16], x[16];
+#pragma unroll
+                    for (int u = 0; u < 16; ++u) {
+                        const int p = min(p0 + u, e.y - 1);
+                        v[u] = G.vals[p];
+                        x[u] = G.b32[(int64_t)G.idx[p] * G.ldb + col];
+                    }
+#pragma unroll
+                    for (int u = 0; u < 16; ++u)
+                        if (p0 + u < e.y) sum = fmaf(v[u], x[u], sum);
+                }
+                C[(int64_t)(m0 + r) * G.ldc + col] += sum;
+            }
+        }
+    }
 }
 
 template <int NP>
@@ -608,8 +679,9 @@ hipError_t wgrad(int N, int K, int B, const float *dY, int64_t ldy, const float 
     gemm_args G{};
     G.A = carve_packed(p, N, B, NP);
     G.B = carve_packed(p, K, B, NP);
-    hipError_t e = launch_pack<NP>(pack_src{dY, ldy, N, ldy % 4 == 0 && aligned16(dY), G.A},
-                                   pack_src{X, ldx, K, ldx % 4 == 0 && aligned16(X), G.B}, B, s);
+    G.a_v4 = ldy % 4 == 0 && aligned16(dY); G.b_v4 = ldx % 4 == 0 && aligned16(X);
+    hipError_t e = launch_pack<NP>(pack_src{dY, ldy, N, G.a_v4, G.A},
+                                   pack_src{X, ldx, K, G.b_v4, G.B}, B, s);
     if (e != hipSuccess) return e;
     G.M = N; G.Nn = K; G.Kr = B;
     G.a32 = dY; G.lda = ldy; G.b32 = X; G.ldb = ldx;
@@ -703,10 +775,11 @@ hipError_t launch_packed_sddmm(int N, int K, const int *ptr, const int *idx, con
     G.B = carve_packed(p, K, B, 3);
     unsigned *mask = reinterpret_cast<unsigned *>(p);
     int *pos = reinterpret_cast<int *>(p + ceil_div(word_counts_bytes(N, K), 256) * 256);
+    G.a_v4 = ldy % 4 == 0 && aligned16(dY); G.b_v4 = ldx % 4 == 0 && aligned16(X);
     hipError_t e = launch_bitmap(N, K, ptr, idx, mask, pos, s);
     if (e == hipSuccess)
-        e = launch_pack<3>(pack_src{dY, ldy, N, ldy % 4 == 0 && aligned16(dY), G.A},
-                           pack_src{X, ldx, K, ldx % 4 == 0 && aligned16(X), G.B}, B, s);
+        e = launch_pack<3>(pack_src{dY, ldy, N, G.a_v4, G.A},
+                           pack_src{X, ldx, K, G.b_v4, G.B}, B, s);
     if (e != hipSuccess) return e;
     G.M = N; G.Nn = K; G.Kr = B;
     G.a32 = dY; G.lda = ldy; G.b32 = X; G.ldb = ldx;

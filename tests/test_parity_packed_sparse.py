@@ -117,3 +117,53 @@ def test_packed_products_small_beside_large():
     gv = h(L1.sddmm_masked_wgrad(W, t(dY), t(Xg))).astype(np.float64)[:W.nnz]
     a, x = dY.astype(np.float64), Xg.astype(np.float64)
     assert (np.abs(gv - (a @ x.T)[rows, ci]) <= bound(6 * B) * (np.abs(a) @ x.T)[rows, ci]).all()
+
+
+@pytest.mark.parametrize("N,K,B,d,pattern", [(1025, 1281, 333, 0.3, "uniform"), (300, 4097, 515, 0.5, "uniform"),
+                                             (2049, 2305, 130, 0.3, "uniform")])
+def test_packed_products_flagged_blocks(N, K, B, d, pattern):
+    # values that no parts hold, at the edges of groups and 256-index blocks, in the weights and
+    # in X: added once, over the stored entries alone, and the entries beside them as exact as ever
+    W, dense, rp, ci, X, dY = layer(N, K, B, d, seed=N, pattern=pattern)
+    assert L1.workspace_bytes(L1.OP_SPMM_PACKED, N, K, W.nnz, B) > 0
+    v = h(W.vals).copy()
+    v[rp[31]], v[rp[32]], v[rp[N] - 1], v[rp[N // 2] + 3] = 2.0 ** 30, -(2.0 ** 29), 2.0 ** 35, 2.0 ** 31
+    W.vals.copy_(t(v))
+    rows = np.repeat(np.arange(N), np.diff(rp))
+    dense[rows, ci] = v
+    for k, b in [(0, 0), (255, 31), (256, 32), (K - 1, B - 1), (K // 3, 127), (512, 128), (K // 2, 64)]:
+        X[k, b] = 2.0 ** 30
+    X[257, 5], X[K - 2, B // 2] = np.inf, -np.inf
+    x = np.where(np.isfinite(X), X, 0).astype(np.float64)
+    ref, m = dense @ x, np.abs(dense) @ np.abs(x)
+    for k, b in [(257, 5), (K - 2, B // 2)]:
+        st = dense[:, k] != 0
+        ref[st, b] = np.sign(dense[st, k]) * X[k, b]
+    got = h(L1.csr_spmm_fwd(W, t(X))).astype(np.float64)
+    ok = np.isfinite(ref)
+    assert not np.isnan(got).any() and np.array_equal(got[~ok], ref[~ok])
+    assert (np.abs(got[ok] - ref[ok]) <= (bound(6 * K) + K * 2.0 ** -24) * m[ok]).all()
+
+
+def test_flagged_blocks_cost_little():
+    # one infinity is the work of its own block: the call takes no multiple of its time
+    import torch
+    N, K, B = 4096, 4096, 512
+    W, _, _, _, X, _ = layer(N, K, B, 0.2, seed=1)
+    Xd, Y = t(X), torch.empty((N, B), device="cuda")
+
+    def us():
+        times = []
+        for _ in range(7):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            L1.csr_spmm_fwd(W, Xd, Y)
+            b.record()
+            torch.cuda.synchronize()
+            times.append(1e3 * a.elapsed_time(b))
+        return min(times)
+
+    us()
+    plain = us()
+    Xd[K // 2, B // 2] = float("inf")
+    assert us() < 6 * plain

@@ -107,6 +107,33 @@ def test_packed_wgrad_nonfinite(prec):
     assert (np.abs(got[ok] - ref[ok].astype(np.float64)) <= 1e-4 * m[ok]).all()
 
 
+@pytest.mark.parametrize("N,K,B,pad", [(129, 257, 161, 0), (300, 1000, 1024, 0), (65, 129, 4097, 2), (300, 5500, 516, 1)])
+def test_packed_wgrad_flagged_blocks(N, K, B, pad):
+    # values that no parts hold at the edges of groups and 256-index blocks: added once, and
+    # the entries beside them as exact as ever
+    if B < 320 or not L1.workspace_bytes(L1.OP_WGRAD_PACKED, N, K, 0, B):
+        precs = [L1.F32]
+    else:
+        precs = [L1.F32, L1.BF16X3]
+    dYh, Xh = operands(N, K, B, seed=N, pad=pad)
+    for i, b in [(0, 0), (31, min(255, B - 1)), (32, min(256, B - 1)), (N - 1, B - 1), (N // 2, B // 2)]:
+        dYh[i, b] = 2.0 ** 30
+    for k, b in [(K - 1, 0), (K // 2, B - 1), (32, B // 2), (127, 31), (128, 32)]:
+        Xh[k, b] = -(2.0 ** 40)
+    Xh[K // 3, 5], dYh[N // 3, 7] = np.inf, -np.inf
+    a, x = dYh[:, :B].astype(np.float64), Xh[:, :B].astype(np.float64)
+    fa, fx = np.where(np.isfinite(a), a, 0), np.where(np.isfinite(x), x, 0)
+    ref = fa @ fx.T
+    ref[:, K // 3] = np.sign(a[:, 5]) * np.inf
+    ref[N // 3, :] = -np.inf
+    ref[N // 3, K // 3] = -np.inf if a[N // 3, 5] < 0 else np.nan
+    for prec in precs:
+        got = h(L1.dense_wgrad(t(dYh)[:, :B], t(Xh)[:, :B], precision=prec)).astype(np.float64)
+        assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.array_equal(got[np.isinf(ref)], ref[np.isinf(ref)])
+        ok = np.isfinite(ref)
+        assert (np.abs(got[ok] - ref[ok]) <= (bound(B, prec) + 2 * B / 16 * 2.0 ** -24) * (np.abs(fa) @ np.abs(fx).T)[ok]).all()
+
+
 @pytest.mark.parametrize("N,K,B", [(1153, 2177, 333), (300, 1000, 1024), (300, 5500, 516)])
 @pytest.mark.parametrize("prec", [L1.F32, L1.BF16X3])
 def test_packed_prox_equals_the_calls(N, K, B, prec):
