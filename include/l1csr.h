@@ -130,10 +130,10 @@ int l1csr_host_free_mapped(void *host);
  * kernel sums a row in ascending p order too unless it cuts the row into k
  * strided pieces (long rows: piece j takes p = row_ptr[i] + j, + j + k, ...),
  * each summed in ascending p order and the k partial sums then added in piece
- * order.  Either order is fixed by the operands alone, so results are
- * reproducible run to run and under any schedule.
+ * order.  The order is fixed by the operands and by which of these workspaces
+ * ws_bytes holds, so results are reproducible run to run and under any schedule.
  * With l1csr_workspace_bytes(L1CSR_OP_SPMM_PACKED, n_rows, n_cols, nnz, B)
- * bytes (0: not taken at these sizes) a product over a dense pattern packs W,
+ * bytes (0: not taken at these sizes, else more than L1CSR_OP_SPMM's) a product over a dense pattern packs W,
  * zeros written out, and X as bf16 parts into ws and runs on the matrix cores
  * as dense_wgrad's packed products do (all 24 significand bits, fp32 sums by
  * 16 columns; ranges of columns summed apart and added in order).  Blocks of 32
@@ -153,7 +153,8 @@ int csr_spmm_fwd(int32_t n_rows, int32_t n_cols, int64_t nnz,
  * (row pieces, their deal to the waves, the pair stream holding W's column
  * offsets and values) into the caller's buffer plan; csr_spmm_planned then
  * computes Y = W . X from it, the same bits as csr_spmm_fwd with the same
- * arguments and a workspace of L1CSR_OP_SPMM's size.  Arguments as for csr_spmm_fwd; plan must hold
+ * arguments and a workspace of L1CSR_OP_SPMM's size (a larger one, where it holds
+ * L1CSR_OP_SPMM_PACKED's, gives the packed product's bits).  Arguments as for csr_spmm_fwd; plan must hold
  * l1csr_workspace_bytes(L1CSR_OP_SPMM, n_rows, n_cols, nnz, B) bytes (0: the
  * product does not take the tiled path, plan may be NULL and csr_spmm_plan
  * enqueues nothing).  Preconditions: both calls get the same n_rows, n_cols,
@@ -266,7 +267,7 @@ int dense_wgrad(int32_t N, int32_t K, int32_t B,
  *     gv[p] = sum_{b < B} dY[row(p)][b] * X[col_idx[p]][b],  0 <= p < nnz.
  * gv has nnz entries (host nnz = row_ptr[n_rows]).  ws must hold
  * l1csr_workspace_bytes(L1CSR_OP_SDDMM, n_rows, n_cols, nnz, B) bytes; with
- * those of L1CSR_OP_SDDMM_PACKED (0: not taken at these sizes) the gradient
+ * those of L1CSR_OP_SDDMM_PACKED (0: not taken at these sizes, else more) the gradient
  * over a dense pattern is the packed product's, sampled in its epilogue.
  */
 int sddmm_masked_wgrad(int32_t n_rows, int32_t n_cols, int64_t nnz,

@@ -286,15 +286,8 @@ size_t l1csr_workspace_bytes(int op, int32_t n_rows, int32_t n_cols, int64_t nnz
                          x3 = split_wgrad_bytes(n_rows, n_cols, B, L1CSR_BF16X3);
             return round_up(f > x3 ? f : x3);
         }
-        // (no less than the calls ask for without the packed path)
-        case L1CSR_OP_SDDMM_PACKED: {
-            const size_t p = packed_sddmm_bytes(n_rows, n_cols, nnz, B), q = sddmm_workspace_bytes(n_rows, n_cols, nnz, B);
-            return round_up(p > 0 && p < q ? q : p);
-        }
-        case L1CSR_OP_SPMM_PACKED: {
-            const size_t p = packed_spmm_bytes(n_rows, n_cols, nnz, B), q = spmm_workspace_bytes(n_rows, n_cols, nnz, B);
-            return round_up(p > 0 && p < q ? q : p);
-        }
+        case L1CSR_OP_SDDMM_PACKED: return round_up(packed_sddmm_bytes(n_rows, n_cols, nnz, B));
+        case L1CSR_OP_SPMM_PACKED: return round_up(packed_spmm_bytes(n_rows, n_cols, nnz, B));
         case L1CSR_OP_PROX_DENSE: return round_up(prox_dense_carve(n_rows, n_cols, nullptr).bytes);
         case L1CSR_OP_SOFTMAX_XENT: return round_up(sizeof(float) * (size_t)(ceil_div(B, 256) + 1));
         default: return 0;

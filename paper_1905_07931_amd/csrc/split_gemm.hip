@@ -744,6 +744,12 @@ hipError_t launch_split_wgrad_prox(int N, int K, int B, int precision, const flo
                                  : wgrad<2, kEpiProx>(N, K, B, dY, ldy, X, ldx, Z, ldz, P, ws, s);
 }
 
+namespace {
+// The workspace's size is what tells the two routes of a call apart, so a packed
+// route asks for more than the call's `plain` one, rounded up as that is given out.
+size_t above(size_t need, size_t plain) { return need > plain + 256 ? need : plain + 256; }
+}  // namespace
+
 // gv = dY . X^T on W's pattern: the whole product, its epilogue writing the
 // stored entries.  Taken where the modelled time is shorter than the entry-wise
 // kernels' (both models in us, fitted to calls on the chip): theirs is nnz * B
@@ -763,8 +769,9 @@ size_t packed_sddmm_bytes(int N, int K, int64_t nnz, int B) {
     const double rate = B % 4 ? 3.5e6 : (3 * n > (double)N * K ? 12e6 : 6.6e6);  // products per us
     const double products = n * B / rate, fixed = n / 23e3;
     if (whole > 0.88 * (14 + (products > fixed ? products : fixed))) return 0;
-    return (size_t)(packed_bytes(N, B, 3) + flag_bytes(N, B) + packed_bytes(K, B, 3) + flag_bytes(K, B)) +
-           2 * (size_t)ceil_div(word_counts_bytes(N, K), 256) * 256;
+    const size_t need = (size_t)(packed_bytes(N, B, 3) + flag_bytes(N, B) + packed_bytes(K, B, 3) + flag_bytes(K, B)) +
+                        2 * (size_t)ceil_div(word_counts_bytes(N, K), 256) * 256;
+    return above(need, sddmm_workspace_bytes(N, K, nnz, B));
 }
 
 hipError_t launch_packed_sddmm(int N, int K, const int *ptr, const int *idx, const float *dY, int64_t ldy,
@@ -827,8 +834,9 @@ size_t packed_spmm_bytes(int N, int K, int64_t nnz, int B) {
     const double sparse_us = B % 4 ? 5 + products / 2.7e6
                                    : (products < 1.7e8 ? 5 + products / 4.5e6 : 60 + products / 12e6);
     if (packed_us > 0.95 * sparse_us) return 0;
-    return (size_t)(packed_bytes(N, K, 3) + flag_bytes(N, K) + packed_bytes(B, K, 3) + flag_bytes(B, K)) +
-           (w.splits > 1 ? sizeof(float) * (size_t)w.splits * N * B : 0);
+    const size_t need = (size_t)(packed_bytes(N, K, 3) + flag_bytes(N, K) + packed_bytes(B, K, 3) + flag_bytes(B, K)) +
+                        (w.splits > 1 ? sizeof(float) * (size_t)w.splits * N * B : 0);
+    return above(need, spmm_workspace_bytes(N, K, nnz, B));
 }
 
 hipError_t launch_packed_spmm(int N, int K, const int *ptr, const int *idx, const float *vals, const float *X,

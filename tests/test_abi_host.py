@@ -435,3 +435,20 @@ def test_binding_and_torch_share_one_hip_runtime():
     assert r.returncode == 0, r.stderr
     runtimes = ast.literal_eval(r.stdout.strip().splitlines()[-1])
     assert len(runtimes) == 1, runtimes
+
+
+def test_packed_workspaces_exceed_the_plain_ones(lib):
+    # the size tells the routes apart: a buffer of the plain size never takes the packed one
+    import random
+    ws, rng, packed = lib.l1csr_workspace_bytes, random.Random(1), 0
+    shapes = [(2048, 2048, 0.9, 512), (4096, 4096, 0.9, 512), (8192, 4096, 0.7, 512), (2547, 204, 0.4, 1080)]
+    shapes += [(rng.randint(1, 9000), rng.randint(1, 9000), rng.random(), rng.randint(1, 1100)) for _ in range(3000)]
+    for N, K, d, B in shapes:
+        nnz = int(d * N * K)
+        for plain, pack in ((4, 12), (3, 11), (8, 10), (9, 10)):  # SPMM, SDDMM, DENSE_WGRAD, WGRAD_PROX
+            n = 0 if pack == 10 else nnz
+            p = ws(pack, N, K, n, B)
+            packed += p > 0
+            assert p == 0 or p > ws(plain, N, K, nnz, B), (plain, N, K, d, B)
+        assert ws(13, N, K, 0, 0) > ws(7, N, K, nnz, 0)  # PROX_DENSE, PROX_RECOMPRESS
+    assert packed > 1000

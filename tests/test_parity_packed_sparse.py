@@ -167,3 +167,20 @@ def test_flagged_blocks_cost_little():
     plain = us()
     Xd[K // 2, B // 2] = float("inf")
     assert us() < 6 * plain
+
+
+def test_plain_workspace_gives_the_planned_bits():
+    # nearly full: the packed operands fit the tiled kernel's workspace, which still takes that kernel
+    import torch
+    N, K, B = 2048, 2048, 512
+    W, dense, rp, ci, X, dY = layer(N, K, B, 0.9, seed=4)
+    n = L1.workspace_bytes(L1.OP_SPMM, N, K, W.nnz, B)
+    assert 0 < n < L1.workspace_bytes(L1.OP_SPMM_PACKED, N, K, W.nnz, B)
+    Xd, s = t(X), torch.cuda.current_stream().cuda_stream
+    ws = torch.empty(n, dtype=torch.uint8, device="cuda")
+    Y = [torch.empty((N, B), device="cuda") for _ in range(2)]
+    a = (N, K, W.nnz, W.row_ptr.data_ptr(), W.col_idx.data_ptr(), W.vals.data_ptr())
+    assert L1.lib().csr_spmm_fwd(*a, Xd.data_ptr(), B, B, Y[0].data_ptr(), B, ws.data_ptr(), n, s) == L1.OK
+    assert L1.lib().csr_spmm_plan(*a, B, ws.data_ptr(), n, s) == L1.OK
+    assert L1.lib().csr_spmm_planned(*a, Xd.data_ptr(), B, B, Y[1].data_ptr(), B, ws.data_ptr(), n, s) == L1.OK
+    assert bits_equal(h(Y[0]), h(Y[1]))
