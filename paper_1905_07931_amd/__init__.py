@@ -129,10 +129,10 @@ def workspace_bytes(op: int, n_rows: int, n_cols: int, nnz: int, B: int) -> int:
     return int(lib().l1csr_workspace_bytes(op, n_rows, n_cols, nnz, B))
 
 
-def _spmm_bytes(n_rows, n_cols, nnz, B):
-    """Workspace of a product of an n_rows x n_cols CSR (or CSC) operand."""
-    return max(workspace_bytes(OP_SPMM, n_rows, n_cols, nnz, B),
-               workspace_bytes(OP_SPMM_PACKED, n_rows, n_cols, nnz, B))
+def _two_sizes(plain_op, packed_op, n_rows, n_cols, nnz, B):
+    """The workspace of a call's packed route (its plain one where there is none) and the plain one."""
+    plain = workspace_bytes(plain_op, n_rows, n_cols, nnz, B)
+    return max(plain, workspace_bytes(packed_op, n_rows, n_cols, nnz, B)), plain
 
 
 # ---------------------------------------------------------------------------
@@ -295,23 +295,38 @@ def _mat(t, name):
 
 
 _ws_cache: dict = {}
+_WS_KEEP = 512 << 20  # the largest buffer kept for a stream
 
 
-def _workspace(nbytes, device, stream=None):
+def _empty_bytes(nbytes, device, stream):
+    """A buffer allocated with its stream current: the caching allocator reuses
+    it only in that stream's order once it is dropped."""
+    torch = _torch()
+    with torch.cuda.stream(torch.cuda.current_stream(device) if stream is None else stream):
+        return torch.empty(nbytes, dtype=torch.uint8, device=device)
+
+
+def _workspace(nbytes, device, stream=None, least=None, keep=True):
     """Scratch for one call, cached per (device, stream the call runs on): calls
     on one stream run in order and may share it, calls on two streams never do.
-    A buffer is allocated with its stream current, so the caching allocator
-    reuses it only in that stream's order once it is replaced."""
+    Beyond _WS_KEEP bytes, or without `keep`, the buffer is the call's own and
+    goes back to the caching allocator behind it.  A call that can do with
+    `least` bytes (its route without the packed operands) gets those where
+    memory for `nbytes` is short.  Returns (buffer or None, its bytes)."""
     if nbytes == 0:
         return None, 0
     index = device.index
     key = (index, _raw_stream(index) if stream is None else stream.cuda_stream)
-    buf = _ws_cache.get(key)
+    buf = _ws_cache.get(key) if keep else None
     if buf is None or buf.numel() < nbytes:
-        torch = _torch()
-        with torch.cuda.stream(torch.cuda.current_stream(device) if stream is None else stream):
-            buf = torch.empty(nbytes, dtype=torch.uint8, device=device)
-        _ws_cache[key] = buf
+        try:
+            buf = _empty_bytes(nbytes, device, stream)
+        except _torch().OutOfMemoryError:
+            if least is None or least >= nbytes:
+                raise
+            return _workspace(least, device, stream, keep=keep)
+        if keep and nbytes <= _WS_KEEP:
+            _ws_cache[key] = buf
     return buf, nbytes
 
 
@@ -433,7 +448,8 @@ def csr_spmm_fwd(W: CSR, X, Y=None, stream=None):
     N, By, ldy = _mat(Y, "Y")
     if N != W.n_rows or By != B:
         raise ValueError("Y must be [n_rows][B]")
-    ws, wsb = _workspace(_spmm_bytes(W.n_rows, W.n_cols, nnz, B), X.device, stream)
+    need, least = _two_sizes(OP_SPMM, OP_SPMM_PACKED, W.n_rows, W.n_cols, nnz, B)
+    ws, wsb = _workspace(need, X.device, stream, least)
     _check(lib().csr_spmm_fwd(W.n_rows, W.n_cols, nnz, _p(W.row_ptr), _p(W.col_idx), _p(W.vals),
                               _p(X), ldx, B, _p(Y), ldy, _p(ws), wsb, _stream(stream)),
            "csr_spmm_fwd")
@@ -497,7 +513,13 @@ def csr_spmm_planned(W: CSR, X, plan: SpmmPlan, Y=None, stream=None):
         raise ValueError("Y must be [n_rows][B]")
     pp, pb = _plan_args(plan, (W.n_rows, W.n_cols, nnz, B))
     if plan.packed:
-        return csr_spmm_fwd(W, X, Y, stream)
+        # the packed operands in a buffer of the call's own: like a plan it is shared with no
+        # other call, so a captured graph keeps it and another thread does not reach it
+        need, least = _two_sizes(OP_SPMM, OP_SPMM_PACKED, W.n_rows, W.n_cols, nnz, B)
+        ws, wsb = _workspace(need, X.device, stream, least, keep=False)
+        _check(lib().csr_spmm_fwd(W.n_rows, W.n_cols, nnz, _p(W.row_ptr), _p(W.col_idx), _p(W.vals), _p(X), ldx, B,
+                                  _p(Y), ldy, _p(ws), wsb, _stream(stream)), "csr_spmm_planned")
+        return Y
     _check(lib().csr_spmm_planned(W.n_rows, W.n_cols, nnz, _p(W.row_ptr), _p(W.col_idx), _p(W.vals), _p(X), ldx, B,
                                   _p(Y), ldy, pp, pb, _stream(stream)), "csr_spmm_planned")
     return Y
@@ -558,7 +580,8 @@ def csr_spmm_bwd_t(W: CSR, dY, csc: CSC | None = None, dX=None, stream=None):
     wsb = 0
     if csc is not None:
         cp, ri, vt = csc.col_ptr, csc.row_idx, csc.vals_t
-        ws, wsb = _workspace(_spmm_bytes(W.n_cols, W.n_rows, nnz, B), dY.device, stream)
+        need, least = _two_sizes(OP_SPMM, OP_SPMM_PACKED, W.n_cols, W.n_rows, nnz, B)
+        ws, wsb = _workspace(need, dY.device, stream, least)
     _check(lib().csr_spmm_bwd_t(W.n_rows, W.n_cols, nnz, _p(W.row_ptr), _p(W.col_idx), _p(W.vals),
                                 _p(cp), _p(ri), _p(vt), _p(dY), ldy, B, _p(dX), ldx, _p(ws), wsb,
                                 _stream(stream)), "csr_spmm_bwd_t")
@@ -580,8 +603,8 @@ def dense_wgrad(dY, X, dW=None, precision=F32, stream=None):
     Nw, Kw, ldw = _mat(dW, "dW")
     if (Nw, Kw) != (N, K):
         raise ValueError("dW must be [N][K]")
-    ws, wsb = _workspace(max(workspace_bytes(OP_DENSE_WGRAD, N, K, 0, B),
-                             0 if precision == BF16 else workspace_bytes(OP_WGRAD_PACKED, N, K, 0, B)), dY.device, stream)
+    need, least = _two_sizes(OP_DENSE_WGRAD, OP_WGRAD_PACKED, N, K, 0, B)
+    ws, wsb = _workspace(least if precision == BF16 else need, dY.device, stream, least)
     _check(lib().dense_wgrad(N, K, B, _p(dY), ldy, _p(X), ldx, _p(dW), ldw, int(precision), _p(ws), wsb,
                              _stream(stream)), "dense_wgrad")
     return dW
@@ -597,8 +620,8 @@ def sddmm_masked_wgrad(W: CSR, dY, X, gv=None, stream=None):
         raise ValueError("shape mismatch")
     if gv is None:
         gv = torch.empty(max(nnz, 1), dtype=torch.float32, device=dY.device)
-    ws, wsb = _workspace(max(workspace_bytes(OP_SDDMM, W.n_rows, W.n_cols, nnz, B),
-                             workspace_bytes(OP_SDDMM_PACKED, W.n_rows, W.n_cols, nnz, B)), dY.device, stream)
+    need, least = _two_sizes(OP_SDDMM, OP_SDDMM_PACKED, W.n_rows, W.n_cols, nnz, B)
+    ws, wsb = _workspace(need, dY.device, stream, least)
     _check(lib().sddmm_masked_wgrad(W.n_rows, W.n_cols, nnz, _p(W.row_ptr), _p(W.col_idx), _p(dY),
                                     ldy, _p(X), ldx, B, _p(gv), _p(ws), wsb, _stream(stream)),
            "sddmm_masked_wgrad")
@@ -711,8 +734,8 @@ def dense_wgrad_prox(W: CSR, dY, X, eta, lam, bitmap: Bitmap, Z=None, word_count
         raise ValueError("word_counts must be contiguous with N * ceil(K/32) entries")
     ws, wsb = (None, 0)
     if precision != BF16:
-        ws, wsb = _workspace(max(workspace_bytes(OP_WGRAD_PROX, N, K, nnz, B),
-                                 workspace_bytes(OP_WGRAD_PACKED, N, K, 0, B)), dev, stream)
+        least = workspace_bytes(OP_WGRAD_PROX, N, K, nnz, B)
+        ws, wsb = _workspace(max(least, workspace_bytes(OP_WGRAD_PACKED, N, K, 0, B)), dev, stream, least)
     _check(lib().dense_wgrad_prox(N, K, B, _p(dY), ldy, _p(X), ldx, int(precision), nnz, _p(W.row_ptr),
                                   _p(W.col_idx), _p(W.vals), _p(bitmap.mask), _p(bitmap.pos), float(eta), float(lam),
                                   _p(Z), ldz, _p(word_counts), _p(ws), wsb, _stream(stream)), "dense_wgrad_prox")
@@ -892,10 +915,10 @@ def prox_adaptive_recompress(W: CSR, G, st: AdaptiveState, eta, lam, capacity=No
                   torch.empty(max(cap, 1), dtype=torch.int32, device=dev),
                   torch.empty(max(cap, 1), dtype=torch.float32, device=dev), None)
     cap = min(out.col_idx.numel(), out.vals.numel()) if capacity is None else int(capacity)
-    need_ws = workspace_bytes(OP_PROX_RECOMPRESS, N, K, nnz, 0)
+    need_ws = least = workspace_bytes(OP_PROX_RECOMPRESS, N, K, nnz, 0)
     if cap >= N * K:
         need_ws = max(need_ws, workspace_bytes(OP_PROX_DENSE, N, K, 0, 0))
-    ws, wsb = _workspace(need_ws, dev, stream)
+    ws, wsb = _workspace(need_ws, dev, stream, least)
     need = C.c_int64(-1)
     _check(lib().prox_adaptive_recompress(st.solver, N, K, nnz, _p(W.row_ptr), _p(W.col_idx),
                                           _p(W.vals), _p(G), ldg, _p(m), _p(st.v), lds, float(eta),

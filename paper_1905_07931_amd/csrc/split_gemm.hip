@@ -702,6 +702,19 @@ hipError_t wgrad(int N, int K, int B, const float *dY, int64_t ldy, const float 
 
 }  // namespace
 
+namespace {
+// The workspace of a packed route whose operands take `need` bytes, in a call that
+// otherwise asks for `plain`.  The size is what tells the two routes apart, so it
+// exceeds the plain one, rounded up as that is given out; and a weight takes 6
+// bytes, stored or zero, so beyond 4 GiB (26,000 x 26,000 weights) the call keeps to
+// its stored entries (0: 65536 x 65536 at 20 % would take 26 GB beside 7 of W).
+constexpr size_t kPackedMost = (size_t)4 << 30;
+size_t packed_size(size_t need, size_t plain) {
+    const size_t n = need > plain + 256 ? need : plain + 256;
+    return n <= kPackedMost ? n : 0;
+}
+}  // namespace
+
 // Where the split product is taken (times in us, fp32 tiles -> split product,
 // dense_wgrad).  The packing launch costs 5-6 us, so the batch has to be long
 // enough for the faster products to win it back.  F32: 2048 x 2048 x 64 12.1 ->
@@ -725,8 +738,9 @@ size_t split_wgrad_bytes(int N, int K, int B, int precision) {
     if (B > (1 << 22)) return 0;  // 32-bit offsets inside a group
     const int np = f32 ? 3 : 2;
     // (split_plan() makes no more ranges than wgrad_plan())
-    return (size_t)(packed_bytes(N, B, np) + flag_bytes(N, B) + packed_bytes(K, B, np) + flag_bytes(K, B)) +
-           wgrad_workspace_bytes(N, K, B);
+    const size_t plain = wgrad_workspace_bytes(N, K, B);
+    return packed_size((size_t)(packed_bytes(N, B, np) + flag_bytes(N, B) + packed_bytes(K, B, np) + flag_bytes(K, B)) +
+                       plain, plain);
 }
 
 bool split_wgrad_prox_fused(int N, int K, int B) { return split_plan(N, K, B).splits == 1; }
@@ -743,12 +757,6 @@ hipError_t launch_split_wgrad_prox(int N, int K, int B, int precision, const flo
     return precision == kPrecF32 ? wgrad<3, kEpiProx>(N, K, B, dY, ldy, X, ldx, Z, ldz, P, ws, s)
                                  : wgrad<2, kEpiProx>(N, K, B, dY, ldy, X, ldx, Z, ldz, P, ws, s);
 }
-
-namespace {
-// The workspace's size is what tells the two routes of a call apart, so a packed
-// route asks for more than the call's `plain` one, rounded up as that is given out.
-size_t above(size_t need, size_t plain) { return need > plain + 256 ? need : plain + 256; }
-}  // namespace
 
 // gv = dY . X^T on W's pattern: the whole product, its epilogue writing the
 // stored entries.  Taken where the modelled time is shorter than the entry-wise
@@ -771,7 +779,7 @@ size_t packed_sddmm_bytes(int N, int K, int64_t nnz, int B) {
     if (whole > 0.88 * (14 + (products > fixed ? products : fixed))) return 0;
     const size_t need = (size_t)(packed_bytes(N, B, 3) + flag_bytes(N, B) + packed_bytes(K, B, 3) + flag_bytes(K, B)) +
                         2 * (size_t)ceil_div(word_counts_bytes(N, K), 256) * 256;
-    return above(need, sddmm_workspace_bytes(N, K, nnz, B));
+    return packed_size(need, sddmm_workspace_bytes(N, K, nnz, B));
 }
 
 hipError_t launch_packed_sddmm(int N, int K, const int *ptr, const int *idx, const float *dY, int64_t ldy,
@@ -836,7 +844,7 @@ size_t packed_spmm_bytes(int N, int K, int64_t nnz, int B) {
     if (packed_us > 0.95 * sparse_us) return 0;
     const size_t need = (size_t)(packed_bytes(N, K, 3) + flag_bytes(N, K) + packed_bytes(B, K, 3) + flag_bytes(B, K)) +
                         (w.splits > 1 ? sizeof(float) * (size_t)w.splits * N * B : 0);
-    return above(need, spmm_workspace_bytes(N, K, nnz, B));
+    return packed_size(need, spmm_workspace_bytes(N, K, nnz, B));
 }
 
 hipError_t launch_packed_spmm(int N, int K, const int *ptr, const int *idx, const float *vals, const float *X,

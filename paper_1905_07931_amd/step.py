@@ -165,7 +165,8 @@ def l1_step(W: CSR, X, dY, eta: float, lam: float, *, Y, dX, dW, csc: CSC, out: 
         plan = _bwd_plan(W, csc, dY.shape[1], side)
         call("csr_spmm_bwd_t_plan", side, lambda: csr_spmm_bwd_t_plan(W, csc, dY.shape[1], plan, stream=side))
         side.wait_stream(main)  # dY follows Y; the CSC and the plan are on side already
-        call("csr_spmm_bwd_t", side, lambda: csr_spmm_bwd_t_planned(W, dY, csc, plan, dX, stream=side))
+        call("csr_spmm_bwd_t", side, lambda: csr_spmm_bwd_t(W, dY, csc, dX, stream=side) if plan.packed else
+             csr_spmm_bwd_t_planned(W, dY, csc, plan, dX, stream=side))
     else:
         if fork:
             side.wait_stream(main)  # dY follows Y; the CSC is on side already

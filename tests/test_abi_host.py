@@ -452,3 +452,11 @@ def test_packed_workspaces_exceed_the_plain_ones(lib):
             assert p == 0 or p > ws(plain, N, K, nnz, B), (plain, N, K, d, B)
         assert ws(13, N, K, 0, 0) > ws(7, N, K, nnz, 0)  # PROX_DENSE, PROX_RECOMPRESS
     assert packed > 1000
+
+
+def test_packed_workspaces_have_a_ceiling(lib):
+    # 6 bytes per weight, stored or not: none beyond 4 GiB, where the plain routes run as before
+    ws = lib.l1csr_workspace_bytes
+    assert 0 < ws(12, 16384, 16384, 16384 * 16384 // 5, 512) <= 4 << 30
+    for pack in (10, 11, 12):
+        assert ws(pack, 65536, 30000, 65536 * 30000 // 5, 16384) == 0

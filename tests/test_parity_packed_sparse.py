@@ -184,3 +184,69 @@ def test_plain_workspace_gives_the_planned_bits():
     assert L1.lib().csr_spmm_plan(*a, B, ws.data_ptr(), n, s) == L1.OK
     assert L1.lib().csr_spmm_planned(*a, Xd.data_ptr(), B, B, Y[1].data_ptr(), B, ws.data_ptr(), n, s) == L1.OK
     assert bits_equal(h(Y[0]), h(Y[1]))
+
+
+def test_packed_workspace_is_given_back_and_can_be_refused(monkeypatch):
+    import torch
+    N, K, B = 1024, 1024, 384
+    W, dense, rp, ci, X, dY = layer(N, K, B, 0.4, seed=6)
+    Xd, dYd = t(X), t(dY)
+    big = L1.workspace_bytes(L1.OP_SPMM_PACKED, N, K, W.nnz, B)
+    packed = h(L1.csr_spmm_fwd(W, Xd))
+    # beyond the bound no buffer outlives its call
+    monkeypatch.setattr(L1, "_ws_cache", {})
+    monkeypatch.setattr(L1, "_WS_KEEP", big - 1)
+    assert bits_equal(h(L1.csr_spmm_fwd(W, Xd)), packed)
+    L1.dense_wgrad(dYd, Xd)
+    assert all(b.numel() < big for b in L1._ws_cache.values())
+    # and where there is no memory for one, the calls run without it
+    real = L1._empty_bytes
+
+    def scarce(nbytes, device, stream):
+        if nbytes >= (1 << 20):
+            raise torch.OutOfMemoryError("no memory for packed operands")
+        return real(nbytes, device, stream)
+
+    monkeypatch.setattr(L1, "_ws_cache", {})
+    monkeypatch.setattr(L1, "_empty_bytes", scarce)
+    plain = L1.workspace_bytes(L1.OP_SPMM, N, K, W.nnz, B)
+    if plain < (1 << 20):
+        Y = h(L1.csr_spmm_fwd(W, Xd))
+        assert (np.abs(Y - dense @ X) <= bound(6 * K) * (np.abs(dense) @ np.abs(X))).all()
+    G = h(L1.dense_wgrad(dYd, Xd, precision=L1.BF16X3)).astype(np.float64)
+    ref, m = dY.astype(np.float64) @ X.T.astype(np.float64), np.abs(dY).astype(np.float64) @ X.T
+    assert (np.abs(G - ref) <= 1e-4 * m).all()
+
+
+def test_captured_planned_product_keeps_its_memory():
+    # a graph of a planned product, replayed after a larger call on its stream: neither
+    # does the replay write to memory that was handed on, nor the other way round
+    import torch
+    N, K, B = 1024, 1024, 384
+    W, dense, rp, ci, X, dY = layer(N, K, B, 0.4, seed=6)
+    W2, _, _, _, X2, _ = layer(2048, 2305, 384, 0.4, seed=7)
+    need = L1.workspace_bytes(L1.OP_SPMM_PACKED, N, K, W.nnz, B)
+    assert 0 < need < L1.workspace_bytes(L1.OP_SPMM_PACKED, 2048, 2305, W2.nnz, B)
+    Xd, X2d = t(X), t(X2)
+    Y = torch.empty((N, B), device="cuda")
+    s = torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(s):
+        plan = L1.csr_spmm_plan(W, B)
+        L1.csr_spmm_planned(W, Xd, plan, Y)
+        want = Y.clone()
+    s.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=s):
+        L1.csr_spmm_planned(W, Xd, plan, Y)
+    with torch.cuda.stream(s):
+        L1.csr_spmm_fwd(W2, X2d)
+        others = [torch.full((need,), 7, dtype=torch.uint8, device="cuda") for _ in range(4)]
+        for _ in range(3):
+            Y.zero_()
+            g.replay()
+            assert torch.equal(Y, want)
+            assert all(bool((o == 7).all()) for o in others)
+            for o in others:
+                o.fill_(7)
+    s.synchronize()
