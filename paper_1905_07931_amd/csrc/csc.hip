@@ -106,7 +106,9 @@ __global__ __launch_bounds__(256) void csc_colscan_kernel(int n_chunks, int n_co
 constexpr int kRunCols = 8;
 constexpr int kRunCap = 256;
 constexpr int kRunPer = kRunCols * kRunCap / kCscThreads;  // staged entries per thread per chunk
+constexpr int64_t kEmitItems = 1 << 23;  // of one launch, which holds less than 2^32 threads
 
+// (items first .. first + gridDim.x - 1)
 __global__ __launch_bounds__(kCscThreads) void csc_emit_kernel(int n_rows, int n_cols, int kw,
                                                                const unsigned *__restrict__ mask,
                                                                const int *__restrict__ pos,
@@ -115,7 +117,7 @@ __global__ __launch_bounds__(kCscThreads) void csc_emit_kernel(int n_rows, int n
                                                                const int *__restrict__ col_ptr,
                                                                int *__restrict__ row_idx,
                                                                int *__restrict__ perm,
-                                                               float *__restrict__ vals_t) {
+                                                               float *__restrict__ vals_t, int64_t first) {
     constexpr int NW = kCscThreads / kWave, G = kWaveRows / kWave;
     __shared__ int start[NW + 1][kRunCols];  // [j][c]: column c's entries of waves < j (row NW: block total)
     __shared__ int64_t dst0[kRunCols];       // first output position of column c's entries of this block
@@ -125,6 +127,7 @@ __global__ __launch_bounds__(kCscThreads) void csc_emit_kernel(int n_rows, int n
     {
         const int64_t total = (int64_t)gridDim.x, per = total / 8;
         if (item < per * 8) item = (item % 8) * per + item / 8;
+        item += first;
     }
     const int kq = kw * (32 / kRunCols);
     const int rb = (int)(item / kq), wq = (int)(item - (int64_t)rb * kq);
@@ -253,7 +256,7 @@ csc_layout layout(int n_rows, int n_cols) {
 }  // namespace
 
 bool csc_grid_fits(int n_rows, int n_cols) {
-    return ceil_div(n_cols, 32) * ceil_div(n_rows, kRowBlock) <= INT32_MAX / (32 / kRunCols) && ceil_div(n_rows, kRowBlock) <= 65535;
+    return ceil_div(n_cols, 32) * ceil_div(n_rows, kRowBlock) <= INT32_MAX && ceil_div(n_rows, kRowBlock) <= 65535;
 }
 
 size_t csc_workspace_bytes(int n_rows, int n_cols, int64_t nnz) {
@@ -290,9 +293,14 @@ hipError_t launch_csc_build(int n_rows, int n_cols, int64_t nnz, const int *ptr,
     }
     if ((e = launch_exclusive_scan(tot, col_ptr, n_cols, nullptr, s)) != hipSuccess) return e;
     if (nnz == 0) return hipSuccess;
-    csc_emit_kernel<<<(unsigned)((int64_t)l.kw * l.n_blocks * (32 / kRunCols)), kCscThreads, 0, s>>>(
-        n_rows, n_cols, l.kw, mask, pos, vals, one ? nullptr : cnt, col_ptr, row_idx, perm, vals_t);
-    return hipGetLastError();
+    const int64_t items = (int64_t)l.kw * l.n_blocks * (32 / kRunCols);
+    for (int64_t first = 0; first < items; first += kEmitItems) {
+        const int64_t n = items - first < kEmitItems ? items - first : kEmitItems;
+        csc_emit_kernel<<<(unsigned)n, kCscThreads, 0, s>>>(n_rows, n_cols, l.kw, mask, pos, vals, one ? nullptr : cnt,
+                                                            col_ptr, row_idx, perm, vals_t, first);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 hipError_t launch_csc_gather_vals(int n_cols, int64_t nnz_bound, const int *col_ptr, const int *perm,

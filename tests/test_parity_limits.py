@@ -69,3 +69,25 @@ def test_prox_recompress_at_the_int32_limit():
     _check_structure(out, Zr[0, 0])
     del out
     torch.cuda.empty_cache()
+
+
+def test_csc_build_beyond_one_launch_of_the_emit_pass():
+    # 13108.x row blocks x 320 words x 4 column groups of 256 threads: more than the 2^32 threads
+    # of one launch; entries at both ends and in every row block's last row.  36 GB of bitmap index.
+    import torch
+    n, k = 13108 * 1024 + 5, 10240
+    rows = np.unique(np.concatenate([np.arange(1023, n, 1024), [0, 1, n - 2, n - 1]]))
+    cols = (rows.astype(np.int64) * 7919) % k
+    cols[0], cols[-1] = k - 1, 0
+    rp = np.zeros(n + 1, np.int32)
+    rp[rows + 1] = 1
+    rp = np.cumsum(rp, dtype=np.int32)
+    vals = np.arange(1, len(rows) + 1, dtype=np.float32)
+    W = L1.CSR.from_host(rp, cols.astype(np.int32), vals, k, device=cuda())
+    csc = L1.csc_build(W)
+    order = np.lexsort((rows, cols))
+    assert np.array_equal(h(csc.col_ptr), np.concatenate([[0], np.cumsum(np.bincount(cols, minlength=k))]))
+    assert np.array_equal(h(csc.row_idx), rows[order]) and np.array_equal(h(csc.perm), order)
+    assert np.array_equal(h(csc.vals_t), vals[order])
+    del W, csc
+    torch.cuda.empty_cache()
