@@ -1345,7 +1345,9 @@ hipError_t launch_rows(int n_rows, int n_cols, int64_t nnz, const int *ptr, cons
     const int64_t nrb = ceil_div(n_rows, kRowsPerBlock), nch = ceil_div(B, kWave * vec);
     if (nrb * nch > INT32_MAX - kLongBlocks) return hipErrorInvalidConfiguration;
     const int longest = long_row(n_rows, nnz, B);
-    const int extra = n_cols > longest && n_rows <= kLongMaxRows ? kLongBlocks : 0;
+    // (a launch holds less than 2^32 threads)
+    const bool room = nrb * nch + kLongBlocks < (int64_t)1 << 24;
+    const int extra = n_cols > longest && n_rows <= kLongMaxRows && room ? kLongBlocks : 0;
     const unsigned grid = (unsigned)(nrb * nch) + extra;
     if (vec == 4)
         spmm_rows_kernel<4><<<grid, 256, 0, s>>>(n_rows, ptr, idx, vals, X, ldx, B, Y, ldy, (int)nrb, extra, longest);

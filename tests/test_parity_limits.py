@@ -91,3 +91,29 @@ def test_csc_build_beyond_one_launch_of_the_emit_pass():
     assert np.array_equal(h(csc.vals_t), vals[order])
     del W, csc
     torch.cuda.empty_cache()
+
+
+def test_row_product_of_nearly_a_whole_launch():
+    # 4095 x 4097 workgroups, 2^24 - 1 (a launch's most): none can be added for long rows.  17 GB of Y.
+    import torch
+    n, k, b = 4095 * 4, 400, 4097 * 64 - 1
+    rp = np.zeros(n + 1, np.int32)
+    rp[1], rp[8], rp[n // 2], rp[n] = 300, 5, 2, 7  # one long row
+    rp = np.cumsum(rp, dtype=np.int32)
+    ci = np.concatenate([np.arange(300), np.arange(5), [7, 399], np.arange(7)]).astype(np.int32)
+    v = np.random.default_rng(1).standard_normal(len(ci)).astype(np.float32)
+    W = L1.CSR.from_host(rp, ci, v, k, device=cuda())
+    X = torch.zeros((k, b), device=cuda())
+    cols = torch.tensor([0, 63, 64, b // 2, b - 65, b - 1], device=cuda())
+    X[:, cols] = torch.rand((k, 6), device=cuda(), generator=torch.Generator("cuda").manual_seed(2))
+    Y = torch.full((n, b), 3.0, device=cuda())
+    L1.csr_spmm_fwd(W, X, Y)
+    x, got = h(X[:, cols]).astype(np.float64), h(Y[:, cols])
+    ref, m = np.zeros((n, 6)), np.zeros((n, 6))
+    rows = np.repeat(np.arange(n), np.diff(rp))
+    np.add.at(ref, rows, v[:, None] * x[ci])
+    np.add.at(m, rows, np.abs(v)[:, None] * x[ci])
+    assert (np.abs(got - ref) <= 304 * 2.0 ** -24 * m).all()
+    assert not bool((Y[-1] == 3.0).any()) and not bool((Y[1] != 0).any())
+    del X, Y
+    torch.cuda.empty_cache()
