@@ -30,6 +30,8 @@
 //
 // Rows kernel (small, narrow or very sparse operands): one wave per (row,
 // batch chunk) reading X directly from the cache hierarchy.
+#include <type_traits>
+
 #include "common.hpp"
 #include "launch.hpp"
 #include "seg.hpp"
@@ -983,30 +985,43 @@ __device__ __forceinline__ void row_sum(int start, int end, const int *__restric
 // X) for as long as all others together: they are left to the grid's first
 // `extra` workgroups, which find them by a pass over the row pointers and take
 // (long row, 64 columns) items, a consecutive quarter of the entries per wave
-// with 32 loads in flight, the quarters added in order.  Where no row is long
-// they end after that pass (768 workgroups: 16.9 -> 17.3 us at 4096 x 4096 x 512
-// with 1 % uniform; power-law rows: 680 -> 176 us at 1000 x 9000 x 512 and 561 -> 134 at
-// 4096 x 9216 x 64, 43 -> 16 at 300 x 784 x 256).  Eight waves
-// per SIMD have to fit: with 64 registers and more the uniform layers lose 10 %.
+// with 32 loads in flight, the quarters added in order.  Power-law rows, a wave a
+// row -> this, us: 1000 x 9000 x 200 at 4 % 671 -> 128, 4096 x 9216 x 64 at 9 % 722 -> 150, 300 x
+// 784 x 256 at 30 % 44 -> 18.  Where no row is long they end after the pass, which
+// holds slots for as long as its loads take.  So beyond 2048 rows a workgroup
+// looks at a slice of them, 32 rows (a cache line of pointers) of every 256, or of
+// every 512 beyond 8192 rows, and shares its slice's items with 1/8 or 1/16 of the
+// workgroups.  Uniform layers without the workgroups, all rows each, slices:
+// 20000 x 600 x 128 at 5 % 23.1, 28.9, 23.1; 8000 x 3000 x 100 at 1 % 11.3, 13.1, 11.0; 5688 x
+// 612 x 448 at 2 % 9.9, 11.1, 9.7; up to 2048 rows slices cost power-law layers more
+// (few items a slice: 1000 x 9000 x 200 163) than they save.  Eight waves per SIMD
+// have to fit: with 64 registers and more the uniform layers lose 10 %.
 constexpr int kRowsPerBlock = 4;
 constexpr int kLongRow = 256;
-constexpr int kLongList = 2048;       // long rows held in LDS at a time
+constexpr int kLongList = 2048;        // rows of a slice at most
 constexpr int kLongBlocks = 768;
-constexpr int kLongMaxRows = 1 << 15;  // rows a workgroup scans at most
+static_assert(kLongBlocks % (16 * 8) == 0, "whole slices, a column range's workgroups on one XCD");
+constexpr int kLongMaxRows = 16 * kLongList;
 
+template <int SLICES>
 __device__ void long_rows(int n_rows, const int *__restrict__ ptr, const int *__restrict__ idx,
                           const float *__restrict__ vals, const float *__restrict__ X, int64_t ldx, int B,
-                          float *__restrict__ Y, int64_t ldy, int extra, int longest) {
+                          float *__restrict__ Y, int64_t ldy, int longest) {
     __shared__ int list[kLongList];
     __shared__ int wtot[kRowsPerBlock];
     __shared__ float part[kRowsPerBlock][kWave];
     const int lane = threadIdx.x & 63, wave = uniform(threadIdx.x >> 6);
+    // this workgroup's slice: 32 rows of every 32 * SLICES (entry j of it: row_of(j), past the last row too)
+    constexpr int group = kLongBlocks / SLICES;
+    const int slice = blockIdx.x / group;
+    const int nr = SLICES == 1 ? n_rows : ((n_rows + 31) / 32 - slice + SLICES - 1) / SLICES * 32;
+    auto row_of = [&](int j) { return SLICES == 1 ? j : ((unsigned)j / 32 * SLICES + slice) * 32 + (unsigned)j % 32; };
     bool any = false;
-    for (int r = threadIdx.x; r < n_rows; r += 4 * 256) {
+    for (int j = threadIdx.x; j < nr; j += 4 * 256) {
         int a[4], e[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            const int q = min(r + u * 256, n_rows - 1);
+            const int q = min((int)row_of(j + u * 256), n_rows - 1);
             a[u] = ptr[q];
             e[u] = ptr[q + 1];
         }
@@ -1014,9 +1029,10 @@ __device__ void long_rows(int n_rows, const int *__restrict__ ptr, const int *__
         for (int u = 0; u < 4; ++u) any |= e[u] - a[u] > longest;
     }
     if (!__syncthreads_or(any)) return;
-    const int per = (n_rows + 255) / 256, r0 = threadIdx.x * per, r1 = min(n_rows, r0 + per);
-    int mine = 0;  // long rows among this thread's consecutive ones
-    for (int r = r0; r < r1; ++r) mine += ptr[r + 1] - ptr[r] > longest;
+    const int per = (nr + 255) / 256, j0 = threadIdx.x * per, j1 = min(nr, j0 + per);
+    auto is_long = [&](int j) { const int r = row_of(j); return r < n_rows && ptr[r + 1] - ptr[r] > longest; };
+    int mine = 0;  // long rows among this thread's consecutive ones of the slice
+    for (int j = j0; j < j1; ++j) mine += is_long(j);
     const int incl = wave_incl_scan(mine);
     if (lane == kWave - 1) wtot[wave] = incl;
     __syncthreads();
@@ -1026,44 +1042,41 @@ __device__ void long_rows(int n_rows, const int *__restrict__ ptr, const int *__
         first += w < wave ? wtot[w] : 0;
         total += wtot[w];
     }
+    if (mine > 0)
+        for (int j = j0; j < j1; ++j)
+            if (is_long(j)) list[first++] = row_of(j);
+    __syncthreads();
     const int nsub = (B + kWave - 1) / kWave;
-    for (int l0 = 0; l0 < total; l0 += kLongList) {
-        __syncthreads();  // the previous list is consumed
-        int q = first;
-        if (mine > 0)
-            for (int r = r0; r < r1; ++r)
-                if (ptr[r + 1] - ptr[r] > longest) {
-                    if (q >= l0 && q < l0 + kLongList) list[q - l0] = r;
-                    ++q;
-                }
+    const int64_t items = (int64_t)total * nsub;
+    for (int64_t it = blockIdx.x - slice * group; it < items; it += group) {
+        // consecutive workgroups (XCDs) on different columns of one row
+        const int row = list[it / nsub], b = (int)(it % nsub) * kWave + lane;
+        const int start = uniform(ptr[row]), len = uniform(ptr[row + 1]) - start;
+        float acc[1] = {0.f};
+        row_sum<1, 16>(start + (int)((int64_t)len * wave / kRowsPerBlock),
+                       start + (int)((int64_t)len * (wave + 1) / kRowsPerBlock), idx, vals, X, ldx, b, b < B, acc);
+        part[wave][lane] = acc[0];
         __syncthreads();
-        const int64_t items = (int64_t)min(kLongList, total - l0) * nsub;
-        for (int64_t it = blockIdx.x; it < items; it += extra) {
-            // consecutive workgroups (XCDs) on different columns of one row
-            const int row = list[it / nsub], b = (int)(it % nsub) * kWave + lane;
-            const int start = uniform(ptr[row]), len = uniform(ptr[row + 1]) - start;
-            float acc[1] = {0.f};
-            row_sum<1, 16>(start + (int)((int64_t)len * wave / kRowsPerBlock),
-                           start + (int)((int64_t)len * (wave + 1) / kRowsPerBlock), idx, vals, X, ldx, b, b < B, acc);
-            part[wave][lane] = acc[0];
-            __syncthreads();
-            if (wave == 0 && b < B)
-                Y[(int64_t)row * ldy + b] = part[0][lane] + part[1][lane] + part[2][lane] + part[3][lane];
-            __syncthreads();
-        }
+        if (wave == 0 && b < B)
+            Y[(int64_t)row * ldy + b] = part[0][lane] + part[1][lane] + part[2][lane] + part[3][lane];
+        __syncthreads();
     }
 }
 
-template <int VEC>
+// SLICES: of the rows that the first kLongBlocks workgroups look through, 0 without them
+template <int VEC, int SLICES>
 __global__ __launch_bounds__(256, 8) void spmm_rows_kernel(int n_rows, const int *__restrict__ ptr,
                                                         const int *__restrict__ idx,
                                                         const float *__restrict__ vals,
                                                         const float *__restrict__ X, int64_t ldx,
                                                         int B, float *__restrict__ Y, int64_t ldy,
-                                                        int nrb, int extra, int longest) {
-    if ((int)blockIdx.x < extra) {
-        long_rows(n_rows, ptr, idx, vals, X, ldx, B, Y, ldy, extra, longest);
-        return;
+                                                        int nrb, int longest) {
+    constexpr int extra = SLICES > 0 ? kLongBlocks : 0;
+    if constexpr (SLICES > 0) {
+        if ((int)blockIdx.x < extra) {
+            long_rows<SLICES>(n_rows, ptr, idx, vals, X, ldx, B, Y, ldy, longest);
+            return;
+        }
     }
     // blocks of one XCD take a contiguous run of batch chunks, so the rows that
     // share an X row segment read it through the same L2
@@ -1076,7 +1089,7 @@ __global__ __launch_bounds__(256, 8) void spmm_rows_kernel(int n_rows, const int
     const bool active = b < B;
     const int start = uniform(ptr[row]);
     const int end = uniform(ptr[row + 1]);
-    if (extra > 0 && end - start > longest) return;
+    if (SLICES > 0 && end - start > longest) return;
     float acc[VEC];
 #pragma unroll
     for (int e = 0; e < VEC; ++e) acc[e] = 0.f;
@@ -1349,12 +1362,19 @@ hipError_t launch_rows(int n_rows, int n_cols, int64_t nnz, const int *ptr, cons
     const bool room = nrb * nch + kLongBlocks < (int64_t)1 << 24;
     const int extra = n_cols > longest && n_rows <= kLongMaxRows && room ? kLongBlocks : 0;
     const unsigned grid = (unsigned)(nrb * nch) + extra;
+    auto launch = [&](auto v) {
+        constexpr int VEC = decltype(v)::value;
+        const auto kernel = extra == 0 ? spmm_rows_kernel<VEC, 0>
+                            : n_rows <= kLongList ? spmm_rows_kernel<VEC, 1>
+                            : n_rows <= 4 * kLongList ? spmm_rows_kernel<VEC, 8> : spmm_rows_kernel<VEC, 16>;
+        kernel<<<grid, 256, 0, s>>>(n_rows, ptr, idx, vals, X, ldx, B, Y, ldy, (int)nrb, longest);
+    };
     if (vec == 4)
-        spmm_rows_kernel<4><<<grid, 256, 0, s>>>(n_rows, ptr, idx, vals, X, ldx, B, Y, ldy, (int)nrb, extra, longest);
+        launch(std::integral_constant<int, 4>{});
     else if (vec == 2)
-        spmm_rows_kernel<2><<<grid, 256, 0, s>>>(n_rows, ptr, idx, vals, X, ldx, B, Y, ldy, (int)nrb, extra, longest);
+        launch(std::integral_constant<int, 2>{});
     else
-        spmm_rows_kernel<1><<<grid, 256, 0, s>>>(n_rows, ptr, idx, vals, X, ldx, B, Y, ldy, (int)nrb, extra, longest);
+        launch(std::integral_constant<int, 1>{});
     return hipGetLastError();
 }
 

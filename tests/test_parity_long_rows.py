@@ -69,3 +69,15 @@ def test_even_rows_keep_a_wave(B):
 def test_few_rows_around_their_mean():
     # 12 rows, mean 400: the line lies at 300 entries
     check([299, 300, 301, 257, 400, 480, 500, 460, 440, 463, 500, 400], 600, 40, 6)
+
+
+@pytest.mark.parametrize("N", [2047, 2048, 2049, 2081, 8192, 8193, 8225, 20000, 32768])
+def test_long_rows_in_every_slice(N):
+    # the rows are looked at in slices of 32 (of every 256 from 2049 rows, of every 512 from 8193):
+    # long ones at the slices' edges, and in the last, partial, one
+    n = np.zeros(N, np.int64)
+    n[np.unique(np.concatenate([np.arange(0, N, 32 * 7), np.arange(31, N, 32 * 7), np.arange(224, N, 256),
+                                np.arange(480, N, 512), [N - 1, N - 2]]))] = 260
+    n[::97] = 257
+    n[5] = 256
+    check(n, 300, 5, N)
