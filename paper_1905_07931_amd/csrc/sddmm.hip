@@ -68,39 +68,67 @@ __device__ __forceinline__ void load_vec(const float *p, float (&v)[VEC]) {
     }
 }
 
-// What the gather needs besides the CSR, in one launch.  Workgroup 0: the extra
-// pieces (row, j), j = 1 .. k_row - 1 with k_row = ceil(len / lsplit), listed in
-// row order, their number in *ext_n; it walks the rows with a carried offset,
-// ROWS consecutive ones a thread: four, so that 4096 rows take one round, or one
-// up to 1024 rows (a thread then lists one row's pieces: 500 x 800 x 300 at 10 %
-// 15.4 us a call, 16.3 with four).  The others, if R > 1: the rows' column-range
-// bounds, a row per wave.  Both are latency, 4.8 and 5.7 us one after another,
-// 4.6 together: the debiasing step at 4096 x 4096 x 512 and 1 % 73.1 -> 68.9, the
-// call at 2958 x 1017 x 960 and 5 % 39.3 -> 35.1.
+// What the gather needs besides the CSR, in one launch.  The first `lists`
+// workgroups: the extra pieces (row, j), j = 1 .. k_row - 1 with k_row = ceil(len /
+// lsplit), in row order, their number in *ext_n.  The others, if R > 1: the rows'
+// column-range bounds, a row per wave.  All of it is latency: 4.8 and 5.7 us as two
+// launches at 4096 x 4096 and 1 %, 4.6 as one.
+// A workgroup lists 1024 rows, one a thread (a row's pieces are stored one after
+// another, so four rows a thread take longer), and finds their place by counting
+// the pieces of all rows before them, eight rows a thread in flight.  The call with
+// one workgroup walking all rows four a thread, one a thread, and this: 1603 x 497 x 128 at
+// 14 % 15.7, 14.8, 14.0 us; 1708 x 354 x 256 at 28 % 19.9, 18.9, 17.3; power-law rows 9000 x 900 x 64
+// at 3 % 34.4, 39.3, 25.6.  Beyond kPrepRows rows, where the counting would outgrow the
+// listing, one workgroup walks them with a carried offset, four consecutive ones
+// a thread.
 constexpr int kPrepThreads = 1024;
+constexpr int kPrepRows = 1 << 15;
 
-template <int ROWS>
+// extra pieces of row i (none past the last row)
+__device__ __forceinline__ int extra_pieces(int i, int n_rows, const int *__restrict__ ptr, int lsplit) {
+    const int len = ptr[min(i + 1, n_rows)] - ptr[min(i, n_rows)];
+    return len > lsplit ? (len + lsplit - 1) / lsplit - 1 : 0;
+}
+
+// COUNT: a workgroup per 1024 rows; else one that walks all rows, ROWS a thread
+template <int ROWS, bool COUNT>
 __global__ __launch_bounds__(kPrepThreads) void sddmm_prep_kernel(int n_rows, const int *__restrict__ ptr,
                                                                   const int *__restrict__ idx, int lsplit,
                                                                   int2 *__restrict__ ext, int *__restrict__ ext_n,
-                                                                  int R, int shift, int *__restrict__ seg) {
+                                                                  int lists, int R, int shift, int *__restrict__ seg) {
+    constexpr int NW = kPrepThreads / kWave;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    if (blockIdx.x > 0) {
-        const int row = uniform(((int)blockIdx.x - 1) * (kPrepThreads / kWave) + wave);
+    if ((int)blockIdx.x >= lists) {
+        const int row = uniform(((int)blockIdx.x - lists) * NW + wave);
         if (row < n_rows) seg_row(row, R, shift, ptr, idx, seg);
         return;
     }
-    __shared__ int wave_tot[2][kPrepThreads / kWave];  // (two: the next rows' totals while these are read)
+    __shared__ int wave_tot[2][NW];  // (two: the next rows' totals while these are read)
+    __shared__ int before[NW];
+    const int first = COUNT ? blockIdx.x * kPrepThreads : 0, end = COUNT ? min(n_rows, first + kPrepThreads) : n_rows;
     int carry = 0, buf = 0;
-    for (int base = 0; base < n_rows; base += kPrepThreads * ROWS, buf ^= 1) {
-        const int i0 = base + tid * ROWS;
-        int at[ROWS + 1], e[ROWS], mine = 0;
+    if constexpr (COUNT) {  // the pieces of the rows before (first is a multiple of the threads)
+        int n = 0;
+        for (int i = tid; i < first; i += 8 * kPrepThreads) {
+            int at[8], e[8];
 #pragma unroll
-        for (int u = 0; u <= ROWS; ++u) at[u] = ptr[min(i0 + u, n_rows)];  // rows past the last are empty
+            for (int u = 0; u < 8; ++u) {
+                const int q = min(i + u * kPrepThreads, first);  // (row `first`, not before it, counts as empty)
+                at[u] = ptr[q];
+                e[u] = ptr[min(q + 1, first)];
+            }
+#pragma unroll
+            for (int u = 0; u < 8; ++u) n += e[u] - at[u] > lsplit ? (e[u] - at[u] + lsplit - 1) / lsplit - 1 : 0;
+        }
+        n = wave_sum_int(n);
+        if (lane == 0) before[wave] = n;
+    }
+    for (int base = first; base < end; base += kPrepThreads * ROWS, buf ^= 1) {
+        const int i0 = base + tid * ROWS;
+        int e[ROWS], mine = 0;
 #pragma unroll
         for (int u = 0; u < ROWS; ++u) {
-            const int len = at[u + 1] - at[u];
-            e[u] = len > lsplit ? (len + lsplit - 1) / lsplit - 1 : 0;
+            e[u] = extra_pieces(i0 + u, n_rows, ptr, lsplit);
             mine += e[u];
         }
         const int incl = wave_incl_scan(mine);
@@ -108,16 +136,16 @@ __global__ __launch_bounds__(kPrepThreads) void sddmm_prep_kernel(int n_rows, co
         __syncthreads();
         int off = carry + incl - mine;
 #pragma unroll
-        for (int w = 0; w < kPrepThreads / kWave; ++w) {
-            const int t = wave_tot[buf][w];
-            off += w < wave ? t : 0;
-            carry += t;
+        for (int w = 0; w < NW; ++w) {
+            const int t = wave_tot[buf][w], b = COUNT ? before[w] : 0;
+            off += (w < wave ? t : 0) + b;
+            carry += t + b;
         }
 #pragma unroll
         for (int u = 0; u < ROWS; ++u)
             for (int j = 0; j < e[u]; ++j) ext[off++] = make_int2(i0 + u, j + 1);
     }
-    if (tid == 0) *ext_n = carry;
+    if (tid == 0 && end == n_rows) *ext_n = carry;
 }
 
 // The entries of one item in steps of G: loads of all G entries issued
@@ -602,9 +630,12 @@ hipError_t launch_sddmm(int n_rows, int n_cols, int64_t nnz, const int *ptr, con
     const gwork w = carve(pl, n_rows, nnz, ws);
     if (pl.extras) {
         const int64_t seg_blocks = pl.R > 1 ? ceil_div(n_rows, kPrepThreads / kWave) : 0;
-        const auto prep = n_rows <= kPrepThreads ? sddmm_prep_kernel<1> : sddmm_prep_kernel<4>;
-        prep<<<(unsigned)(1 + seg_blocks), kPrepThreads, 0, s>>>(n_rows, ptr, idx, pl.lsplit, w.ext, w.ext_n, pl.R,
-                                                               pl.shift, w.seg);
+        const bool count = n_rows > kPrepThreads && n_rows <= kPrepRows;
+        const int lists = count ? (int)ceil_div(n_rows, kPrepThreads) : 1;
+        const auto prep = count ? sddmm_prep_kernel<1, true>
+                                : (n_rows <= kPrepThreads ? sddmm_prep_kernel<1, false> : sddmm_prep_kernel<4, false>);
+        prep<<<(unsigned)(lists + seg_blocks), kPrepThreads, 0, s>>>(n_rows, ptr, idx, pl.lsplit, w.ext, w.ext_n, lists,
+                                                                   pl.R, pl.shift, w.seg);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     } else if (pl.R > 1 && (e = launch_seg(n_rows, pl.R, pl.shift, ptr, idx, w.seg, s)) != hipSuccess) {
         return e;

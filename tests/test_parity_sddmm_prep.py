@@ -11,11 +11,12 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("N,K,B", [(1, 300, 8), (15, 900, 32), (4095, 500, 8), (4096, 500, 8), (4097, 500, 8), (8200, 500, 12),
-                                   (17, 4096, 512), (4099, 2600, 516), (1024, 500, 8), (1025, 500, 8)])
+                                   (17, 4096, 512), (4099, 2600, 516), (1024, 500, 8), (1025, 500, 8), (2048, 500, 8),
+                                   (32768, 400, 4), (32769, 400, 4), (41000, 300, 4)])
 def test_row_pieces(N, K, B):
     rng = np.random.default_rng(N)
     n = rng.integers(0, 4, N)
-    for i in (0, 1, 4095, 4096, 4097, 8191, N // 2, N - 1):
+    for i in (0, 1, 1023, 1024, 2047, 4095, 4096, 4097, 8191, 32767, 32768, N // 2, N - 1):
         if i < N:
             n[i] = K - i % 7
     rp = np.concatenate([[0], np.cumsum(n)]).astype(np.int32)
