@@ -829,6 +829,30 @@ wgrad_split spmm_splits(int N, int K, int B) {
     const int64_t per = ceil_div(kb, s > 0 ? s : 1);
     return wgrad_split{(int)ceil_div(kb, per), (int)per * kPackK};
 }
+
+// The models above are fitted where packing gains most.  At their line they were up to
+// 1.6x wrong: the tiled kernel has no such fixed cost on few entries, packing slows
+// down beyond 12 M weights (its output leaves the last-level cache), and a product
+// without a tiled plan runs the row kernel.  These are fitted to 250 products of 200-
+// 12000 rows and columns, batches of 32-1024 and 2-56 % stored, within 15 % (us; the
+// packed one 25 % beyond 36 M weights).  The row kernel may also wait for its longest
+// row (0.056 us an entry), so unless that is bounded the packed product is kept up
+// to 1.25 of its time on even rows.  Sparse kernel, packed: 1978 x 5941 x 256 at 7 % 41, 66;
+// 8944 x 3077 x 1024 at 11 % 267, 319; 9027 x 5314 x 512 at 12 % 317, 376; 5128 x 8214 x 256 at 14 % 232,
+// 252; 1544 x 383 x 512 at 50 % 27, 32; kept: 6662 x 6879 x 432 at 33 % 638, 400; with power-law
+// rows 5915 x 4822 x 118 at 11 % 182, 125, 525 x 7183 x 512 at 10 % 117, 61.
+bool packed_spmm_loses(int N, int K, int64_t nnz, int B, const wgrad_split &w) {
+    const double np = (double)ceil_div(N, BM) * BM, bp = (double)ceil_div(B, BN) * BN, nk = (double)N * K;
+    const double n = (double)nnz, products = n * B, density = n / nk;
+    const double packed = 23.4 + 0.594e-6 * nk + (nk > 12e6 ? 1.88e-6 * (nk - 12e6) : 0) + 1.96e-6 * K * (double)B +
+                          4.38e-6 * n + 8e-9 * np * K * bp + (w.splits > 1 ? 0.755e-6 * w.splits * N * (double)B : 0) +
+                          (density > 0.2 ? 8 * (density - 0.2) : 0);
+    if (B % 4 == 0 && spmm_workspace_bytes(N, K, nnz, B) > 0)  // the tiled kernel
+        return packed > (nk > 36e6 ? 0.8 : 1.04) * (36.6 + products / 21.8e6 + 13e-6 * n + 11.7e-3 * K);
+    const double rate = B % 4 ? (B % 2 ? 3.6e6 : 4.2e6) : (B > 2 * kWave ? 5.9e6 : (B > kWave ? 3.8e6 : 2.5e6));
+    const double chain = 0.056 * n / N, even = 6 + (products / rate > chain ? products / rate : chain);
+    return packed > (0.056 * K < even ? 0.95 : 1.25) * even;
+}
 }  // namespace
 
 size_t packed_spmm_bytes(int N, int K, int64_t nnz, int B) {
@@ -841,7 +865,7 @@ size_t packed_spmm_bytes(int N, int K, int64_t nnz, int B) {
     const double products = (double)nnz * B;
     const double sparse_us = B % 4 ? 5 + products / 2.7e6
                                    : (products < 1.7e8 ? 5 + products / 4.5e6 : 60 + products / 12e6);
-    if (packed_us > 0.95 * sparse_us) return 0;
+    if (packed_us > 0.95 * sparse_us || packed_spmm_loses(N, K, nnz, B, w)) return 0;
     const size_t need = (size_t)(packed_bytes(N, K, 3) + flag_bytes(N, K) + packed_bytes(B, K, 3) + flag_bytes(B, K)) +
                         (w.splits > 1 ? sizeof(float) * (size_t)w.splits * N * B : 0);
     return packed_size(need, spmm_workspace_bytes(N, K, nnz, B));

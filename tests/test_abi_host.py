@@ -457,6 +457,19 @@ def test_packed_workspaces_exceed_the_plain_ones(lib):
 def test_packed_workspaces_have_a_ceiling(lib):
     # 6 bytes per weight, stored or not: none beyond 4 GiB, where the plain routes run as before
     ws = lib.l1csr_workspace_bytes
-    assert 0 < ws(12, 16384, 16384, 16384 * 16384 // 5, 512) <= 4 << 30
+    assert 0 < ws(12, 12000, 12000, 12000 * 12000 * 3 // 10, 512) <= 4 << 30
     for pack in (10, 11, 12):
         assert ws(pack, 65536, 30000, 65536 * 30000 // 5, 16384) == 0
+
+
+def test_packed_sparse_product_is_taken_where_it_is_faster(lib):
+    # (N, K, B, density) with both routes timed: the packed one slower, faster
+    ws = lib.l1csr_workspace_bytes
+    for N, K, B, d in [(1978, 5941, 256, .0712), (8944, 3077, 1024, .1141), (9027, 5314, 512, .1197), (5128, 8214, 256, .1358),
+                       (8214, 5128, 256, .1358), (1544, 383, 512, .5035), (3485, 1494, 1024, .0779), (2300, 6069, 256, .0906),
+                       (6062, 3999, 114, .0805)]:
+        assert ws(12, N, K, int(d * N * K), B) == 0, (N, K, B, d)
+    for N, K, B, d in [(4096, 4096, 512, .1), (4096, 4096, 512, .2), (4096, 4096, 512, .5), (2049, 3001, 333, .1),
+                       (3001, 2049, 333, .1), (2000, 700, 1000, .25), (6662, 6879, 432, .3333), (1303, 1221, 757, .1701),
+                       (5915, 4822, 118, .1132), (441, 6309, 256, .4239), (5738, 1556, 128, .1947)]:
+        assert ws(12, N, K, int(d * N * K), B) > 0, (N, K, B, d)
