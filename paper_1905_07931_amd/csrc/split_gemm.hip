@@ -768,15 +768,19 @@ hipError_t launch_split_wgrad_prox(int N, int K, int B, int precision, const flo
 // Measured at 4096 x 4096 x 512, entry-wise -> whole: 5 % stored 81 -> 105, 10 %
 // 135 -> 106, 20 % 259 -> 111, 50 % 369 -> 128; 4096 x 9216 x 1024 at 9 % 693 ->
 // 393; 503 x 7856 x 736 at 20 % 143 -> 68, 1738 x 1321 x 531 77 -> 45 (10 % 40 -> 44);
-// 1000 x 1000 x 256 at 20 % 22 -> 29, 1024 x 1024 x 1024 43 -> 57.
+// 1000 x 1000 x 256 at 20 % 22 -> 29, 1024 x 1024 x 1024 43 -> 57; 4096 x 9216 x 64 at 3 % 62 -> 74, 757 x
+// 7865 x 51 at 8 % 26 -> 29, 1497 x 11913 x 43 at 5 % 42 -> 53, 569 x 1700 x 32 at 41 % 59 -> 20.
 size_t packed_sddmm_bytes(int N, int K, int64_t nnz, int B) {
     if (B < 32 || B > (1 << 22) || N == 0 || K == 0) return 0;
     const double np = (double)ceil_div(N, BM) * BM, kp = (double)ceil_div(K, BN) * BN, n = (double)nnz;
     const double mfma = 12 * np * kp * B / 1.25e9, chain = 0.55 * ceil_div(B, kStep);
-    const double whole = 24 + 10.0 * ((double)N + K) * B / 5e6 + (mfma > chain ? mfma : chain) + n / 250e3;
+    // batches under 256 do not cover a tile's first loads, mask and stores (11 us per 1000 tiles)
+    const double tiles = np * kp / (BM * BN), edge = B < 256 ? 11e-3 * tiles * (1 - B / 256.0) : 0;
+    const double wide = K > 10240 ? 10 : 0;  // the bitmap index of such rows is made word by word
+    const double whole = 24 + 10.0 * ((double)N + K) * B / 5e6 + (mfma > chain ? mfma : chain) + n / 250e3 + edge + wide;
     const double rate = B % 4 ? 3.5e6 : (3 * n > (double)N * K ? 12e6 : 6.6e6);  // products per us
     const double products = n * B / rate, fixed = n / 23e3;
-    if (whole > 0.88 * (14 + (products > fixed ? products : fixed))) return 0;
+    if (whole > (B < 256 ? 0.92 : 0.88) * (14 + (products > fixed ? products : fixed))) return 0;
     const size_t need = (size_t)(packed_bytes(N, B, 3) + flag_bytes(N, B) + packed_bytes(K, B, 3) + flag_bytes(K, B)) +
                         2 * (size_t)ceil_div(word_counts_bytes(N, K), 256) * 256;
     return packed_size(need, sddmm_workspace_bytes(N, K, nnz, B));

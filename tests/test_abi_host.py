@@ -473,3 +473,13 @@ def test_packed_sparse_product_is_taken_where_it_is_faster(lib):
                        (3001, 2049, 333, .1), (2000, 700, 1000, .25), (6662, 6879, 432, .3333), (1303, 1221, 757, .1701),
                        (5915, 4822, 118, .1132), (441, 6309, 256, .4239), (5738, 1556, 128, .1947)]:
         assert ws(12, N, K, int(d * N * K), B) > 0, (N, K, B, d)
+
+
+def test_packed_masked_gradient_is_taken_where_it_is_faster(lib):
+    # as above for the masked gradient
+    ws = lib.l1csr_workspace_bytes
+    for N, K, B, d in [(4096, 9216, 64, .03), (757, 7865, 51, .08), (1497, 11913, 43, .0476), (1000, 1000, 256, .2), (4096, 4096, 512, .05)]:
+        assert ws(11, N, K, int(d * N * K), B) == 0, (N, K, B, d)
+    for N, K, B, d in [(4096, 4096, 512, .1), (4096, 4096, 512, .2), (4096, 9216, 1024, .09), (503, 7856, 736, .2),
+                       (1738, 1321, 531, .2), (569, 1700, 32, .4056), (252, 4100, 64, .4148), (4229, 3543, 40, .051)]:
+        assert ws(11, N, K, int(d * N * K), B) > 0, (N, K, B, d)
