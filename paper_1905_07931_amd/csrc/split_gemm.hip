@@ -725,14 +725,23 @@ size_t packed_size(size_t need, size_t plain) {
 // x 1000 x 3000 33.3 -> 29.4, 300 x 9216 x 1024 114 -> 70.  BF16X3 (whose other
 // path does not split a reduction): 2048 x 2048 x 256 17.0 -> 19.6, 2049 x 3001 x
 // 333 47 -> 31, 4096 x 4096 x 512 67 -> 60, 50 x 500 x 16384 712 -> 50.
+// Rows that are 16-byte aligned let the other kernels load vectors, and outputs
+// that fill the chip once let them run without a last partial round (up to 512
+// tiles with two BF16X3 workgroups on a CU, 256 tiles with one of fp32): there the
+// batch has to be longer.  BF16X3 4096 x 2048 x 320 25.0 -> 29.4, x 512 34.4 -> 36.1, x 640
+// 41.3 -> 41.4 (3000 x 4000 x 320, 768 tiles, 43 -> 38; 1024 x 1024, 64 tiles, x 448 21.3 ->
+// 20.5); F32 500 x 8000 x 96 14.0 -> 15.9, x 160 19.4 -> 20.6, x 224 24.4 -> 24.6, 2048 x 2048 x 128
+// 16.7 -> 17.3.
 size_t split_wgrad_bytes(int N, int K, int B, int precision) {
     const bool f32 = precision == kPrecF32;
     if ((!f32 && precision != kPrecBF16X3) || N == 0 || K == 0) return 0;
     const double nk = (double)N * K, rows = (double)N + K;
+    const int64_t tiles = ceil_div(N, BM) * ceil_div(K, BN);
     if (f32) {
         if (B < (nk >= 4e6 ? 96 : 160)) return 0;
         if (nk < 200 * rows && rows * B > 4e6) return 0;
-    } else if (B < 320) {
+        if (B % 4 == 0 && tiles > 192 && tiles <= 256 && B < 208) return 0;
+    } else if (B < 320 || (B % 4 == 0 && tiles > 75 && tiles <= 512 && B <= 512)) {
         return 0;
     }
     if (B > (1 << 22)) return 0;  // 32-bit offsets inside a group

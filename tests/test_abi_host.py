@@ -483,3 +483,14 @@ def test_packed_masked_gradient_is_taken_where_it_is_faster(lib):
     for N, K, B, d in [(4096, 4096, 512, .1), (4096, 4096, 512, .2), (4096, 9216, 1024, .09), (503, 7856, 736, .2),
                        (1738, 1321, 531, .2), (569, 1700, 32, .4056), (252, 4100, 64, .4148), (4229, 3543, 40, .051)]:
         assert ws(11, N, K, int(d * N * K), B) > 0, (N, K, B, d)
+
+
+def test_packed_gradient_is_taken_where_it_is_faster(lib):
+    # as above for the dense gradient: OP_WGRAD_PACKED is the larger of the two precisions' sizes, so
+    # the shapes are those where neither or only the fp32 product (6 bytes an operand element) packs
+    ws = lib.l1csr_workspace_bytes
+    for N, K, B in [(500, 8000, 96), (500, 8000, 160), (2048, 2048, 128)]:
+        assert ws(10, N, K, 0, B) == 0, (N, K, B)
+    three = lambda N, K, B: 6 * (-(-N // 32) + -(-K // 32)) * 32 * (-(-B // 16) * 16)
+    for N, K, B in [(500, 8000, 224), (4096, 2048, 128), (4096, 9216, 128), (300, 784, 256), (300, 784, 1024)]:
+        assert ws(10, N, K, 0, B) >= three(N, K, B), (N, K, B)
