@@ -30,12 +30,16 @@ launches; the backward product itself needs dY and runs beside the weight
 update.  Every launch is deterministic, so the outputs equal those
 of the same calls made one after another on one stream, bit for bit.
 
-The overlap pays where a product takes the tiled path (a workspace for its
-plan and pair stream).  Small layers run the rows kernel, a few short launches
-with no planning to hide; there the waits between the streams cost more than
-they save (at 784 -> 300, batch 64: 180 us on two streams against 100 us on
-one), so the default schedule ("auto") makes the calls one after another on
-the caller's stream unless one of the two products is tiled.
+The overlap pays where a product takes the tiled path (its plan is made beside
+the forward product) and, from 2 million weights on, where one packs its operands
+(the CSC build and the packing run beside a product that the matrix cores
+bound).  Elsewhere the waits between the streams cost more than they save, so the
+default schedule ("auto") makes the calls one after another on the caller's
+stream.  us per step, one stream and two: tiled 4096 x 9216, batch 1024, power-law
+rows 1296 and 1228; packed 2000 x 2000 x 512 at 30 % 187 and 163, 4096 x 4096 x 512 at 50 %
+578 and 553, but 1024 x 1024 x 1024 at 40 % 146 and 166, 2000 x 700 x 1000 164 and 187; row
+kernels 784 -> 300, batch 64, 100 and 180, 2048 x 4096 x 333 at 5 % 220 and 241 (waited
+for; 198 and 195 in a row).
 
 Each entry point keeps its own workspace per stream, so the two streams never
 share scratch memory.  The function is capture-safe: it forks the side stream
@@ -46,7 +50,7 @@ for every entry point under capture, W's nnz must be known on the host
 """
 from __future__ import annotations
 
-from . import (CSC, CSR, F32, OP_SPMM, AdaptiveState, Bitmap, SpmmPlan, csc_build, csr_bitmap_build,
+from . import (CSC, CSR, F32, OP_SPMM, OP_SPMM_PACKED, AdaptiveState, Bitmap, SpmmPlan, csc_build, csr_bitmap_build,
                csr_recompress_counted, csr_spmm_bwd_t, csr_spmm_bwd_t_plan, csr_spmm_bwd_t_planned, csr_spmm_fwd,
                dense_wgrad, dense_wgrad_prox, prox_adaptive_recompress, workspace_bytes)
 
@@ -86,11 +90,21 @@ def side_stream(device):
     return s
 
 
+_PACKED_FORK_WEIGHTS = 2_000_000
+
+
 def two_stream_pays(W: CSR, B: int) -> bool:
-    """True if either product of W at batch B takes the tiled path."""
+    """True if a product of W at batch B takes the tiled path, or the packed one
+    in a layer of at least 2 million weights.  (By the sizes alone: activations
+    whose rows are not 16-byte aligned run the row kernel at any B.)"""
     nnz = W.host_nnz()
-    return (workspace_bytes(OP_SPMM, W.n_rows, W.n_cols, nnz, B) > 0
-            or workspace_bytes(OP_SPMM, W.n_cols, W.n_rows, nnz, B) > 0)
+    for n, k in ((W.n_rows, W.n_cols), (W.n_cols, W.n_rows)):
+        if workspace_bytes(OP_SPMM_PACKED, n, k, nnz, B) > 0:
+            if n * k >= _PACKED_FORK_WEIGHTS:
+                return True
+        elif B % 4 == 0 and workspace_bytes(OP_SPMM, n, k, nnz, B) > 0:
+            return True
+    return False
 
 
 def l1_step(W: CSR, X, dY, eta: float, lam: float, *, Y, dX, dW, csc: CSC, out: CSR,
@@ -112,7 +126,7 @@ def l1_step(W: CSR, X, dY, eta: float, lam: float, *, Y, dX, dW, csc: CSC, out: 
     "dense_wgrad_prox", "csr_recompress_counted"; adaptive:
     "dense_wgrad",
     "prox_adaptive_recompress").  schedule: "two_stream", "serial" (every call on the
-    caller's stream) or "auto" (two_stream where a product is tiled).
+    caller's stream) or "auto" (two_stream where two_stream_pays()).
     adaptive: Prox-RMSProp / Prox-ADAM state with dense [N][K] m, v; the step
     then ends with prox_adaptive_recompress (state updated in place, t
     advanced) instead of dense_wgrad_prox + csr_recompress_counted.  bitmap: buffers for

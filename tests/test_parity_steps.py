@@ -619,7 +619,7 @@ def test_calls_on_two_streams_use_separate_workspaces():
 
 
 def test_l1_step_schedule_choice():
-    """"auto" forks only where a product takes the tiled path, and a bad
+    """"auto" forks only where two_stream_pays(), and a bad
     schedule name is rejected before anything is enqueued."""
     from paper_1905_07931_amd.step import two_stream_pays
     dev = cuda()
