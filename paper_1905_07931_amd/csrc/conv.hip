@@ -15,6 +15,8 @@
 // maps of LeNet-sized layers fit in L2, so the shifted re-reads of X by the
 // direct products stay on chip; only the lowered operand of the weight
 // gradient is streamed from HBM.
+#include <type_traits>
+
 #include "common.hpp"
 #include "launch.hpp"
 
@@ -243,20 +245,30 @@ constexpr int wave_positions(bool bwd) { return bwd ? 1 : 2; }
 // conv1 forward at 1024 34.7 -> 22.8.  Two positions and four entries a time
 // forward, one and eight backward (its neighbours' valid entries differ): conv1
 // forward with one and eight 30.1, conv2 backward with two and eight 21.8.
-template <int VEC, bool BWD>
+template <int VEC, bool BWD, bool MAPPED>
 __global__ __launch_bounds__(kThreads) void conv_wave_kernel(geom_t g, int B, int chunks,
                                                              const int *__restrict__ ptr,
                                                              const int *__restrict__ idx,
                                                              const float *__restrict__ vals,
                                                              const float *__restrict__ in, int64_t ldi,
-                                                             float *__restrict__ out, int64_t ldo, int tasks) {
+                                                             float *__restrict__ out, int64_t ldo, int tasks, int slices) {
     typedef vec_t<VEC> V;
     constexpr int kPB = wave_positions(BWD), kNB = BWD ? 8 : 4;
     __shared__ int map_s[kStage];  // first row of the entry's input map
     __shared__ int khw_s[kStage];
     __shared__ float w_s[kStage];
     __shared__ int cp_s[BWD ? kMaxKK + 1 : 1];
-    const int ch = blockIdx.x, kk = g.KH * g.KW;
+    // slices of the outputs: (channel, slice) by the grid, or a grid of one dimension
+    // and all channels of a slice on one XCD (blocks are dealt to them round-robin)
+    int ch = blockIdx.x, slice = blockIdx.y;
+    if constexpr (MAPPED) {
+        const int channels = gridDim.x / slices, whole = slices / 8 * 8;
+        const bool tail = (int)blockIdx.x >= whole * channels;
+        const int r = tail ? blockIdx.x - whole * channels : blockIdx.x / 8;
+        ch = r % channels;
+        slice = tail ? whole + r / channels : r / channels * 8 + blockIdx.x % 8;
+    }
+    const int kk = g.KH * g.KW;
     const int lane = threadIdx.x & 63, wave = uniform(threadIdx.x >> 6);
     int s, e;
     if constexpr (BWD) {  // the column pointers of this channel's KH*KW filter columns (kk <= kMaxKK)
@@ -296,7 +308,7 @@ __global__ __launch_bounds__(kThreads) void conv_wave_kernel(geom_t g, int B, in
     if (one_pass) stage(s, e - s);
     const int ow_ = BWD ? g.W : g.OW, npos = ow_ * (BWD ? g.H : g.OH);
     // (a uniform trip count: every wave of the workgroup stages)
-    for (int t0 = blockIdx.y * (kThreads / kWave); t0 < tasks; t0 += gridDim.y * (kThreads / kWave)) {
+    for (int t0 = slice * (kThreads / kWave); t0 < tasks; t0 += (MAPPED ? slices : gridDim.y) * (kThreads / kWave)) {
         const int t = t0 + wave;
         const bool live = t < tasks;
         const int pg = t / chunks, b = (t - pg * chunks) * (kWave * VEC) + lane * VEC;
@@ -458,13 +470,27 @@ hipError_t launch_wave(int vec, const geom_t &g, int channels, int B, const int 
     const int chunks = (int)ceil_div(B, kWave * vec);
     const int64_t tasks = ceil_div(npos, wave_positions(BWD)) * chunks;
     if (tasks > INT32_MAX - 65535 * 4 || channels > kMaxGridX) return hipErrorInvalidConfiguration;
-    const dim3 grid((unsigned)channels, (unsigned)slice_blocks(ceil_div(tasks, kThreads / kWave), channels));
+    // The channels of a slice read the same input rows.  Where the input is more
+    // than a few L2s they have to do so on one XCD at a time, or each fetches all of
+    // it: forward 256 -> 64 channels, 14 x 14, 1 x 1 filters at 40 %, batch 1024: 515 us by
+    // (channel, slice), 185 mapped, 357 with a thread per output; 64 -> 128, 3 x 3 at 5 %, batch 1024: 224,
+    // 111, 174.  Smaller inputs gain nothing (12.8 MB: 46.4 -> 48.9) and strided
+    // backward products leave whole slices without work (46 -> 67).
+    const int64_t all = ceil_div(tasks, kThreads / kWave);
+    const bool map = !BWD && (double)g.C * g.H * g.W * B * sizeof(float) > 16e6 && all * channels < (int64_t)1 << 24;
+    const int64_t slices = map ? all : slice_blocks(all, channels);
+    const dim3 grid = map ? dim3((unsigned)(slices * channels)) : dim3((unsigned)channels, (unsigned)slices);
+    auto launch = [&](auto v) {
+        constexpr int VEC = decltype(v)::value;
+        const auto kernel = map ? conv_wave_kernel<VEC, BWD, !BWD> : conv_wave_kernel<VEC, BWD, false>;
+        kernel<<<grid, kThreads, 0, s>>>(g, B, chunks, ptr, idx, vals, in, ldi, out, ldo, (int)tasks, (int)slices);
+    };
     if (vec == 4)
-        conv_wave_kernel<4, BWD><<<grid, kThreads, 0, s>>>(g, B, chunks, ptr, idx, vals, in, ldi, out, ldo, (int)tasks);
+        launch(std::integral_constant<int, 4>{});
     else if (vec == 2)
-        conv_wave_kernel<2, BWD><<<grid, kThreads, 0, s>>>(g, B, chunks, ptr, idx, vals, in, ldi, out, ldo, (int)tasks);
+        launch(std::integral_constant<int, 2>{});
     else
-        conv_wave_kernel<1, BWD><<<grid, kThreads, 0, s>>>(g, B, chunks, ptr, idx, vals, in, ldi, out, ldo, (int)tasks);
+        launch(std::integral_constant<int, 1>{});
     return hipGetLastError();
 }
 

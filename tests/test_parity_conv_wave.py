@@ -83,3 +83,27 @@ def test_conv_wave_many_entries():
     _, dx = reference(g2, w2.astype(np.float64), x2, d2.astype(np.float64))
     _, mdx = reference(g2, np.abs(w2).astype(np.float64), x2, np.abs(d2).astype(np.float64))
     assert (np.abs(dX - dx) <= n2 * 25 * 2.0 ** -24 * mdx).all()
+
+
+@pytest.mark.parametrize("geom,n,B", [((40, 11, 11, 1, 1, 1, 1, 0, 0), 7, 1000), ((33, 13, 11, 3, 3, 2, 1, 1, 1), 9, 1020),
+                                      ((300, 5, 3, 1, 1, 1, 1, 0, 0), 1, 1024)])
+def test_conv_wave_mapped_slices(geom, n, B):
+    # inputs beyond 16 MB: the (channel, slice) items are dealt to the XCDs by slice; counts of
+    # slices and channels that are no multiple of 8, fewer slices than XCDs
+    g = L1.ConvGeom(*geom)
+    assert g.in_rows * B * 4 > 16e6
+    rng = np.random.default_rng(n)
+    dense = rng.standard_normal((n, g.filter_cols)) * (rng.random((n, g.filter_cols)) < 0.3)
+    dense = dense.astype(np.float32).astype(np.float64)
+    rp = np.concatenate([[0], np.cumsum((dense != 0).sum(1))]).astype(np.int32)
+    ci = np.nonzero(dense)[1].astype(np.int32)
+    W = L1.CSR.from_host(rp, ci, dense[dense != 0].astype(np.float32), g.filter_cols)
+    OH, OW = g.out_hw
+    X = rng.random((g.in_rows, B)).astype(np.float32)
+    none = np.zeros((n * OH * OW, B))
+    y, _ = reference(g, dense, X.astype(np.float64), none)
+    my, _ = reference(g, np.abs(dense), X.astype(np.float64), none)
+    import torch
+    Y = torch.full((n * OH * OW, B + 4), 3.0, device="cuda")
+    L1.csr_conv_fwd(g, W, t(X), Y[:, :B])
+    assert (np.abs(h(Y)[:, :B] - y) <= g.filter_cols * 2.0 ** -24 * my).all() and bool((Y[:, B:] == 3.0).all())
