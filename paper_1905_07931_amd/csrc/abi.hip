@@ -790,7 +790,7 @@ int csr_conv_bwd_data(const int32_t *geom, int32_t n_out, int64_t nnz, const int
     if ((int64_t)n_out * OH * OW > INT32_MAX) return L1CSR_EUNSUPPORTED;
     if (bad_dense(dY, (int64_t)n_out * OH * OW, B, ldy) || bad_dense(dX, (int64_t)g.C * g.H * g.W, B, ldx))
         return L1CSR_EINVAL;
-    return hip_status(launch_conv_bwd_data(g, n_out, B, col_ptr, row_idx, vals_t, dY, ldy, dX, ldx, stream));
+    return hip_status(launch_conv_bwd_data(g, n_out, B, nnz, col_ptr, row_idx, vals_t, dY, ldy, dX, ldx, stream));
 }
 
 int conv_im2col(const int32_t *geom, const float *X, int64_t ldx, int32_t B, float *Xcol, int64_t ldc,

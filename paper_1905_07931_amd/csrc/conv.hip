@@ -463,6 +463,18 @@ int wave_vec(bool bwd, int B, int64_t lda, const void *a, int64_t ldb, const voi
     return 0;
 }
 
+// Backward, single floats against four a thread: a wave per position is four
+// times the waves of the other kernel, which pays where a channel's entries are
+// many (its index arithmetic) or the positions few (its waves).  Thread per output,
+// wave, us: 256 -> 64 channels, 14 x 14, 1 x 1 filters at 10 %, batch 48 19.0, 33.2, batch 64 22.9,
+// 33.4; 20 -> 16, 28 x 28, 1 x 1 at 5 %, batch 64 6.9, 10.6; 16 -> 32, 28 x 28, 2 x 2 at 10 %, batch 48
+// 12.7, 15.2; 64 -> 256, 14 x 14, 1 x 1 at 10 %, batch 64 22.8, 20.2; 20 -> 512, 7 x 7, 1 x 1 at
+// 10 %, batch 48 22.5, 7.5.  Strides are divisions in the other kernel.
+bool short_rows(const geom_t &g, int B, int64_t nnz) {
+    const double entries = (double)nnz / (g.C > 0 ? g.C : 1), positions = (double)g.C * g.H * g.W;
+    return entries * (B >= kWave || g.SH > 1 || g.SW > 1 ? 1000 : 300) < positions;
+}
+
 template <bool BWD>
 hipError_t launch_wave(int vec, const geom_t &g, int channels, int B, const int *ptr, const int *idx, const float *vals,
                        const float *in, int64_t ldi, float *out, int64_t ldo, hipStream_t s) {
@@ -474,10 +486,10 @@ hipError_t launch_wave(int vec, const geom_t &g, int channels, int B, const int 
     // than a few L2s they have to do so on one XCD at a time, or each fetches all of
     // it: forward 256 -> 64 channels, 14 x 14, 1 x 1 filters at 40 %, batch 1024: 515 us by
     // (channel, slice), 185 mapped, 357 with a thread per output; 64 -> 128, 3 x 3 at 5 %, batch 1024: 224,
-    // 111, 174.  Smaller inputs gain nothing (12.8 MB: 46.4 -> 48.9) and strided
+    // 111, 174.  Smaller inputs gain nothing (12.8 MB: 46.4 -> 48.9; 16 MB: 7.0 -> 7.4) and strided
     // backward products leave whole slices without work (46 -> 67).
     const int64_t all = ceil_div(tasks, kThreads / kWave);
-    const bool map = !BWD && (double)g.C * g.H * g.W * B * sizeof(float) > 16e6 && all * channels < (int64_t)1 << 24;
+    const bool map = !BWD && (double)g.C * g.H * g.W * B * sizeof(float) > 24e6 && all * channels < (int64_t)1 << 24;
     const int64_t slices = map ? all : slice_blocks(all, channels);
     const dim3 grid = map ? dim3((unsigned)(slices * channels)) : dim3((unsigned)channels, (unsigned)slices);
     auto launch = [&](auto v) {
@@ -527,16 +539,17 @@ hipError_t launch_conv_fwd(const conv_geom &cg, int N, int B, const int *ptr, co
     return hipGetLastError();
 }
 
-hipError_t launch_conv_bwd_data(const conv_geom &cg, int N, int B, const int *col_ptr, const int *row_idx,
-                                const float *vals_t, const float *dY, int64_t ldy, float *dX, int64_t ldx,
+hipError_t launch_conv_bwd_data(const conv_geom &cg, int N, int B, int64_t nnz, const int *col_ptr,
+                                const int *row_idx, const float *vals_t, const float *dY, int64_t ldy, float *dX, int64_t ldx,
                                 hipStream_t s) {
     const geom_t g = to_geom(cg);
     const int64_t F = (int64_t)g.H * g.W * B;
     if (F == 0) return hipSuccess;
     (void)N;
-    if (const int vec = wave_vec(true, B, ldy, dY, ldx, dX))
-        return launch_wave<true>(vec, g, g.C, B, col_ptr, row_idx, vals_t, dY, ldy, dX, ldx, s);
     const bool v4 = vec4_ok(B, ldy, dY, ldx, dX);
+    const int vec = wave_vec(true, B, ldy, dY, ldx, dX);
+    if (vec > 0 && !(vec == 1 && v4 && short_rows(g, B, nnz)))
+        return launch_wave<true>(vec, g, g.C, B, col_ptr, row_idx, vals_t, dY, ldy, dX, ldx, s);
     const int64_t sl = slices_of(F, v4 ? 4 : 1);
     if (sl > INT32_MAX || g.C > kMaxGridX) return hipErrorInvalidConfiguration;
     const dim3 grid((unsigned)g.C, (unsigned)slice_blocks(sl, g.C));

@@ -245,7 +245,7 @@ bool conv_out_dims(const conv_geom &g, int *OH, int *OW);
 hipError_t launch_conv_fwd(const conv_geom &g, int N, int B, const int *ptr, const int *idx,
                            const float *vals, const float *X, int64_t ldx, float *Y, int64_t ldy,
                            hipStream_t s);
-hipError_t launch_conv_bwd_data(const conv_geom &g, int N, int B, const int *col_ptr, const int *row_idx,
+hipError_t launch_conv_bwd_data(const conv_geom &g, int N, int B, int64_t nnz, const int *col_ptr, const int *row_idx,
                                 const float *vals_t, const float *dY, int64_t ldy, float *dX, int64_t ldx,
                                 hipStream_t s);
 hipError_t launch_im2col(const conv_geom &g, int B, const float *X, int64_t ldx, float *Xc, int64_t ldc,

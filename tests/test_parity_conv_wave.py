@@ -85,13 +85,13 @@ def test_conv_wave_many_entries():
     assert (np.abs(dX - dx) <= n2 * 25 * 2.0 ** -24 * mdx).all()
 
 
-@pytest.mark.parametrize("geom,n,B", [((40, 11, 11, 1, 1, 1, 1, 0, 0), 7, 1000), ((33, 13, 11, 3, 3, 2, 1, 1, 1), 9, 1020),
-                                      ((300, 5, 3, 1, 1, 1, 1, 0, 0), 1, 1024)])
+@pytest.mark.parametrize("geom,n,B", [((52, 11, 11, 1, 1, 1, 1, 0, 0), 7, 1000), ((42, 13, 11, 3, 3, 2, 1, 1, 1), 9, 1020),
+                                      ((400, 5, 3, 1, 1, 1, 1, 0, 0), 1, 1024)])
 def test_conv_wave_mapped_slices(geom, n, B):
-    # inputs beyond 16 MB: the (channel, slice) items are dealt to the XCDs by slice; counts of
+    # inputs beyond 24 MB: the (channel, slice) items are dealt to the XCDs by slice; counts of
     # slices and channels that are no multiple of 8, fewer slices than XCDs
     g = L1.ConvGeom(*geom)
-    assert g.in_rows * B * 4 > 16e6
+    assert g.in_rows * B * 4 > 24e6
     rng = np.random.default_rng(n)
     dense = rng.standard_normal((n, g.filter_cols)) * (rng.random((n, g.filter_cols)) < 0.3)
     dense = dense.astype(np.float32).astype(np.float64)
@@ -107,3 +107,24 @@ def test_conv_wave_mapped_slices(geom, n, B):
     Y = torch.full((n * OH * OW, B + 4), 3.0, device="cuda")
     L1.csr_conv_fwd(g, W, t(X), Y[:, :B])
     assert (np.abs(h(Y)[:, :B] - y) <= g.filter_cols * 2.0 ** -24 * my).all() and bool((Y[:, B:] == 3.0).all())
+
+
+@pytest.mark.parametrize("geom,B,density", [((8, 40, 40, 1, 1, 1, 1, 0, 0), 48, 0.3), ((8, 40, 40, 1, 1, 1, 1, 0, 0), 64, 0.3),
+                                            ((12, 40, 41, 1, 1, 2, 1, 0, 0), 64, 0.3), ((8, 13, 11, 2, 2, 1, 1, 1, 0), 48, 0.6),
+                                            ((8, 40, 40, 1, 1, 1, 1, 0, 0), 47, 0.3)])
+def test_conv_backward_few_entries(geom, B, density):
+    # short batches with few entries a channel and many positions: a thread per output (four batch
+    # columns), beside sizes on the wave's side of the line and a batch that has no vectors
+    g = L1.ConvGeom(*geom)
+    n = 9
+    rng = np.random.default_rng(B)
+    dense = (rng.standard_normal((n, g.filter_cols)) * (rng.random((n, g.filter_cols)) < density)).astype(np.float32)
+    rp = np.concatenate([[0], np.cumsum((dense != 0).sum(1))]).astype(np.int32)
+    W = L1.CSR.from_host(rp, np.nonzero(dense)[1].astype(np.int32), dense[dense != 0], g.filter_cols)
+    OH, OW = g.out_hw
+    dY = rng.standard_normal((n * OH * OW, B)).astype(np.float32)
+    none = np.zeros((g.in_rows, B))
+    _, dx = reference(g, dense.astype(np.float64), none, dY.astype(np.float64))
+    _, m = reference(g, np.abs(dense).astype(np.float64), none, np.abs(dY).astype(np.float64))
+    dX = h(L1.csr_conv_bwd_data(g, n, L1.csc_build(W), t(dY), nnz=W.nnz))
+    assert (np.abs(dX - dx) <= n * g.KH * g.KW * 2.0 ** -24 * m).all()
