@@ -47,6 +47,7 @@ def _step(L, W, fill):
             W1.row_ptr, W1.col_idx[:n1], W1.vals[:n1], gv[:n1]]
 
 
+@pytest.mark.usefixtures("both_routes")
 @pytest.mark.parametrize("shape", [(2000, 3000, 256, 0.05, "zipf"), (300, 784, 64, 0.10, "uniform")])
 def test_l1_and_debias_steps_bitwise_reproducible(shape):
     N, K, B, d, pattern = shape
@@ -58,6 +59,7 @@ def test_l1_and_debias_steps_bitwise_reproducible(shape):
         assert np.array_equal(x, y), i
 
 
+@pytest.mark.usefixtures("both_routes")
 def test_split_reduction_and_conv_reproducible():
     # dense gradient with few tiles and a long batch (split reduction), and
     # the direct convolution of LeNet-5 conv2

@@ -53,6 +53,7 @@ def _check_csr(out, rp, ci, v, what):
     assert bits_equal(h(out.vals)[:n], v), what + " vals"
 
 
+@pytest.mark.usefixtures("both_routes")
 @pytest.mark.parametrize("solver", SOLVERS, ids=SOLVER_IDS)
 @pytest.mark.parametrize("NK", [(1, 1), (7, 5), (64, 300), (33, 1031), (40, 9000), (3, 20000)])
 @pytest.mark.parametrize("hyper", HYPER, ids=["small_thr", "large_thr"])
@@ -112,6 +113,7 @@ def test_adaptive_dense_step_bit_exact_with_padding_and_aliasing(solver):
         assert not np.any(h(v_base)[:, K:]) and not np.any(h(m_base)[:, K:])
 
 
+@pytest.mark.usefixtures("both_routes")
 @pytest.mark.parametrize("solver", SOLVERS, ids=SOLVER_IDS)
 def test_adaptive_fused_equals_dense_step_then_recompress(solver):
     gpu_solver, _ = solver
@@ -192,6 +194,7 @@ def test_adaptive_csr_step_bit_exact(solver, lam):
         assert np.count_nonzero(vals == 0) > 0
 
 
+@pytest.mark.usefixtures("both_routes")
 def test_adaptive_empty_inputs():
     # no rows, no columns, and a layer with no stored weights (where every
     # weight with a nonzero gradient grows in)
@@ -214,6 +217,7 @@ def test_adaptive_empty_inputs():
             assert bits_equal(h(st.m), m) and bits_equal(h(st.v), vv)
 
 
+@pytest.mark.usefixtures("both_routes")
 def test_adaptive_full_size_fc9216x4096_adam_two_steps():
     # the large layer (4096 x 9216 CSR, 9% Zipf rows) with a gradient of the
     # layer's own shape: two Prox-ADAM steps, the whole output and state compared

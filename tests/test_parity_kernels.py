@@ -69,19 +69,23 @@ TILED = [  # (N, K, B, nnz, seed)
 ]
 
 
+@pytest.mark.usefixtures("both_routes")
 @pytest.mark.parametrize("shape", TILED, ids=_ids)
 def test_spmm_fwd_tiled_widths(shape):
     L = _layer(shape)
+    assert (L1.workspace_bytes(L1.OP_SPMM, L.N, L.K, L.nnz, L.B) > 0) == (L.B >= 128)
     Y = h(L1.csr_spmm_fwd(_W(L), t(L.X)))
     ref = oracle.spmm_fwd(L.row_ptr, L.col_idx, L.vals, L.X)
     m = oracle.spmm_fwd(L.row_ptr, L.col_idx, np.abs(L.vals), L.X)
     assert_scaled_close(Y, ref, m, what="Y")
 
 
+@pytest.mark.usefixtures("both_routes")
 @pytest.mark.parametrize("shape", [(300, 4096, 1024, 200000, 25), (64, 8192, 1024, 200000, 26)],
                          ids=_ids)
 def test_spmm_bwd_tiled_widths(shape):
     L = _layer(shape)
+    assert L1.workspace_bytes(L1.OP_SPMM, L.K, L.N, L.nnz, L.B) > 0
     W = _W(L)
     dX = h(L1.csr_spmm_bwd_t(W, t(L.dY), L1.csc_build(W)))
     ref = oracle.spmm_bwd_t(L.row_ptr, L.col_idx, L.vals, L.dY, L.K)
@@ -89,6 +93,7 @@ def test_spmm_bwd_tiled_widths(shape):
     assert_scaled_close(dX, ref, m, what="dX")
 
 
+@pytest.mark.usefixtures("both_routes")
 def test_spmm_power_law_rows_dyadic_bit_exact():
     # Zipf row lengths (a few full rows, many short ones) through the tiled
     # kernel on the dyadic grid: every sum is exact, so the bits must match
@@ -102,6 +107,7 @@ def test_spmm_power_law_rows_dyadic_bit_exact():
     assert bits_equal(h(L1.csr_spmm_fwd(W, t(X))), oracle.spmm_fwd(rp, ci, vals, X))
 
 
+@pytest.mark.usefixtures("both_routes")
 @pytest.mark.parametrize("case", ["zipf_steep", "mostly_empty_rows"])
 def test_spmm_tiled_skewed_patterns_both_directions(case):
     # the planner's pieces, deal and bucketing on skewed patterns: a steep
@@ -141,6 +147,7 @@ PLANNED = [  # (N, K, B, nnz, seed)
 ]
 
 
+@pytest.mark.usefixtures("both_routes")
 @pytest.mark.parametrize("shape", PLANNED, ids=_ids)
 def test_planned_product_equals_one_call(shape):
     import torch
@@ -151,6 +158,9 @@ def test_planned_product_equals_one_call(shape):
     dY = torch.empty((L.N, L.B), dtype=torch.float32, device=cuda())
     pf = L1.csr_spmm_plan(W, L.B)           # before X and dY hold anything
     pb = L1.csr_spmm_bwd_t_plan(W, csc, L.B)
+    for p, key in ((pf, (L.N, L.K, L.nnz, L.B)), (pb, (L.K, L.N, L.nnz, L.B))):
+        assert p.packed == (L1.workspace_bytes(L1.OP_SPMM_PACKED, *key) > 0)  # (never on the plain routes)
+        assert p.packed or p.nbytes == L1.workspace_bytes(L1.OP_SPMM, *key)
     X.copy_(t(L.X))
     dY.copy_(t(L.dY))
     Yp = h(L1.csr_spmm_planned(W, X, pf))
@@ -308,6 +318,7 @@ def test_spmm_bwd_csc_stays_valid_after_value_update():
 # dense weight gradient (fp32 matrix cores)
 # ----------------------------------------------------------------------------
 
+@pytest.mark.usefixtures("both_routes")
 @pytest.mark.parametrize("NKB", [(1, 1, 1), (7, 5, 3), (129, 130, 33), (300, 784, 64),
                                  (257, 1000, 100), (128, 128, 32), (64, 300, 256), (5, 9, 0)])
 def test_dense_wgrad(NKB):
@@ -339,6 +350,7 @@ def test_dense_wgrad_batch_one_bit_exact_and_padded():
     assert np.all(h(dWp)[:, 66:] == 3.0)
 
 
+@pytest.mark.usefixtures("both_routes")
 @pytest.mark.parametrize("NKB", [(50, 500, 16384), (7, 130, 9001), (20, 25, 147456), (129, 257, 2080),
                                  (300, 784, 256 * 8)])
 def test_dense_wgrad_split_reduction(NKB):
@@ -355,6 +367,7 @@ def test_dense_wgrad_split_reduction(NKB):
     assert bits_equal(h(L1.dense_wgrad(t(dY), t(X))), dW1)  # reproducible
 
 
+@pytest.mark.usefixtures("both_routes")
 @pytest.mark.parametrize("NKB", [(257, 10999, 370), (130, 38400, 300), (200, 32768, 96),
                                  (2048, 9216, 64), (2000, 9000, 70)])
 def test_dense_wgrad_many_tiles(NKB):
@@ -385,17 +398,20 @@ def test_dense_wgrad_empty_batch_large_shape(precision):
     assert not out[:, :9216].any() and np.all(out[:, 9216:] == 5.0)
 
 
+@pytest.mark.usefixtures("both_routes")
 def test_dense_wgrad_many_tiles_dyadic_bit_exact():
     L = synth.dyadic_layer(257, 10999, 370, 10, seed=7)
     assert bits_equal(h(L1.dense_wgrad(t(L.dY), t(L.X))), oracle.dense_wgrad(L.dY, L.X))
 
 
+@pytest.mark.usefixtures("both_routes")
 def test_dense_wgrad_split_reduction_dyadic_bit_exact():
     L = synth.dyadic_layer(50, 500, 16384, 10, seed=6)
     assert L1.workspace_bytes(L1.OP_DENSE_WGRAD, 50, 500, 0, 16384) > 0
     assert bits_equal(h(L1.dense_wgrad(t(L.dY), t(L.X))), oracle.dense_wgrad(L.dY, L.X))
 
 
+@pytest.mark.usefixtures("both_routes")
 def test_dense_wgrad_dyadic_bit_exact():
     L = synth.dyadic_layer(200, 300, 256, 10, seed=5)
     assert bits_equal(h(L1.dense_wgrad(t(L.dY), t(L.X))), oracle.dense_wgrad(L.dY, L.X))
@@ -442,6 +458,7 @@ def test_dense_wgrad_bf16_batch_one_bit_exact_and_padded():
 # bf16 hi + lo split, three products: against the oracle of the same split
 # (exact products, so only fp32 summation separates the two), and against the
 # exact fp32 definition within the 1e-4 contract itself
+@pytest.mark.usefixtures("both_routes")
 @pytest.mark.parametrize("NKB", [(1, 1, 1), (7, 5, 3), (129, 130, 33), (300, 784, 64),
                                  (257, 1000, 100), (64, 300, 256), (256, 384, 1024), (130, 2600, 300),
                                  (5, 9, 0),
@@ -459,6 +476,7 @@ def test_dense_wgrad_bf16x3(NKB):
     assert bits_equal(h(L1.dense_wgrad(t(dY), t(X), precision=L1.BF16X3)), dW)  # reproducible
 
 
+@pytest.mark.usefixtures("both_routes")
 def test_dense_wgrad_bf16x3_batch_one_dyadic_and_padded():
     rng = np.random.default_rng(3)
     # B = 1: three exact products added in fp32 (two roundings at most)
@@ -483,6 +501,7 @@ def test_dense_wgrad_bf16x3_batch_one_dyadic_and_padded():
     assert np.all(h(dWp)[:, 66:] == 3.0)
 
 
+@pytest.mark.usefixtures("both_routes")
 def test_dense_wgrad_bf16x3_full_size_sampled():
     # the 9216 -> 4096 layer's gradient at batch 1024, in the launch the step
     # uses; sampled rows and columns against the exact fp32 definition
@@ -552,6 +571,7 @@ def test_sddmm(shape):
 
 # dense patterns (50 % and 93 % of the entries stored) through the gather
 # kernel, with vector and scalar operand loads and ragged column ranges
+@pytest.mark.usefixtures("both_routes")
 @pytest.mark.parametrize("shape", [(2048, 2048, 256, 2097152, 11), (1100, 1030, 333, 1050000, 12)],
                          ids=_ids)
 def test_sddmm_dense_patterns(shape):
@@ -567,6 +587,7 @@ def test_sddmm_dense_patterns(shape):
 # one per XCD, instead of 4; ragged columns and batch in the second shape, a
 # batch of 513 (scalar loads, three batch ranges, the last one column wide) in
 # the third
+@pytest.mark.usefixtures("both_routes")
 @pytest.mark.parametrize("shape", [(1024, 4096, 512, 838861, 13), (700, 4000, 500, 600000, 14),
                                    (600, 4096, 513, 400000, 16)], ids=_ids)
 def test_sddmm_xcd_column_split(shape):
@@ -577,6 +598,7 @@ def test_sddmm_xcd_column_split(shape):
     assert_scaled_close(gv, ref, m, what="gv")
 
 
+@pytest.mark.usefixtures("both_routes")
 def test_sddmm_xcd_column_split_dyadic_bit_exact():
     L = synth.dyadic_layer(512, 4096, 512, 419430, seed=15, empty_rows=(5,), full_rows=(9,))
     gv = h(L1.sddmm_masked_wgrad(_W(L), t(L.dY), t(L.X)))[: L.nnz]
@@ -586,6 +608,7 @@ def test_sddmm_xcd_column_split_dyadic_bit_exact():
 # a third of the entries stored or more, with vector loads: the row-block
 # kernel (8-row blocks, 64-column windows); rows not a multiple of 8, columns
 # not a multiple of 64, a batch whose last range is partial
+@pytest.mark.usefixtures("both_routes")
 @pytest.mark.parametrize("shape", [(300, 1000, 260, 150000, 17), (1027, 4096, 512, 2400000, 18)], ids=_ids)
 def test_sddmm_row_blocks(shape):
     L = _layer(shape)
@@ -595,6 +618,7 @@ def test_sddmm_row_blocks(shape):
     assert_scaled_close(gv, ref, m, what="gv")
 
 
+@pytest.mark.usefixtures("both_routes")
 def test_sddmm_row_blocks_dyadic_bit_exact():
     L = synth.dyadic_layer(301, 1000, 516, 120000, seed=19, empty_rows=(4,), full_rows=(0, 300))
     gv = h(L1.sddmm_masked_wgrad(_W(L), t(L.dY), t(L.X)))[: L.nnz]

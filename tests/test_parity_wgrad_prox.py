@@ -78,6 +78,7 @@ def test_fused_update_equals_unfused_calls(shape, precision):
     _fused_vs_unfused(L, precision)
 
 
+@pytest.mark.usefixtures("both_routes")
 @pytest.mark.parametrize("precision", [L1.F32, L1.BF16X3])
 def test_fused_update_full_size_9216x4096(precision):
     # the 256 x 288 tiles (two rounds of the chip), Zipf rows; a lambda that
@@ -97,6 +98,7 @@ def test_fused_update_direct_load_tiles_with_ragged_edges():
     assert 0 < n < L.N * L.K
 
 
+@pytest.mark.usefixtures("both_routes")
 def test_fused_update_split_reduction_fallback():
     # 50 x 500 with a reduction of 16384: the fp32 product splits its batch
     # (no fused epilogue there), so dW goes through Z and the prox runs after
@@ -104,6 +106,7 @@ def test_fused_update_split_reduction_fallback():
     _fused_vs_unfused(L, L1.F32)
 
 
+@pytest.mark.usefixtures("both_routes")
 def test_fused_update_dyadic_full_size_bit_exact_with_independent_oracle():
     # every fp32 sum of dW is exact on the dyadic grid, so the update must
     # equal the fully independent oracle step (its own dW) bit for bit
