@@ -51,6 +51,8 @@ def test_packed_products(N, K, B, d, pattern):
     csc = L1.csc_build(W)
     dX = L1.csr_spmm_bwd_t(W, dYd, csc)
     assert (np.abs(h(dX) - dense.T @ dY) <= bound(6 * N) * (np.abs(dense).T @ np.abs(dY))).all()
+    for got, ref in ((h(Y), dense @ X), (h(dX), dense.T @ dY)):  # (two parts are at some 5e-6)
+        assert np.linalg.norm(got - ref) <= 8e-7 * np.linalg.norm(ref)
     # again, planned, and into padded rows: the same bits
     import torch
     assert bits_equal(h(L1.csr_spmm_planned(W, Xd, L1.csr_spmm_plan(W, B))), h(Y))
@@ -72,6 +74,7 @@ def test_packed_masked_gradient(N, K, B, d, pattern):
     ref = (dY.astype(np.float64) @ X.astype(np.float64).T)[rows, ci]
     m = (np.abs(dY).astype(np.float64) @ np.abs(X).astype(np.float64).T)[rows, ci]
     assert (np.abs(h(gv)[:W.nnz] - ref) <= bound(6 * B) * m).all()
+    assert np.linalg.norm(h(gv)[:W.nnz] - ref) <= 3e-7 * np.linalg.norm(ref)
     assert bool((gv[W.nnz:] == 3.0).all())
 
 
@@ -250,3 +253,23 @@ def test_captured_planned_product_keeps_its_memory():
             for o in others:
                 o.fill_(7)
     s.synchronize()
+
+
+def test_packed_products_take_all_six_terms():
+    # one stored value meets one nonzero of X: exact only with each of the six part products
+    N, K, B = 1024, 2048, 256
+    W, dense, rp, ci, X, dY = layer(N, K, B, 0.4, seed=11)
+    assert min(L1.workspace_bytes(op, N, K, W.nnz, B) for op in (L1.OP_SPMM_PACKED, L1.OP_SDDMM_PACKED)) > 0
+    hi, mid, lo = 1.0, 1 + 2.0 ** -9, 1 + 2.0 ** -9 + 2.0 ** -18
+    v, x = np.zeros(len(ci), np.float32), np.zeros((K, B), np.float32)
+    dy, xg = np.zeros((N, B), np.float32), np.zeros((K, B), np.float32)
+    want, wantg = np.zeros((N, B)), np.zeros(len(ci))
+    for n, (a, b) in enumerate([(hi, hi), (mid, hi), (hi, mid), (mid, mid), (lo, hi), (hi, lo)]):
+        i, col = 150 * n + 1, 40 * n + 7  # (row 341 is empty)
+        p = rp[i] + 30 * n + 2  # this row's value stands alone in its column of X and of the batch
+        v[p], x[ci[p], col], want[i, col] = a, b, a * b
+        dy[i, col], xg[ci[p], col], wantg[p] = a, b, a * b
+    assert np.count_nonzero(x) == 6
+    W.vals.copy_(t(v))
+    assert np.array_equal(h(L1.csr_spmm_fwd(W, t(x))), want.astype(np.float32))
+    assert np.array_equal(h(L1.sddmm_masked_wgrad(W, t(dy), t(xg)))[:W.nnz], wantg.astype(np.float32))

@@ -41,6 +41,22 @@ def test_packed_wgrad(N, K, B, pad, prec):
     a, x = dYh[:, :B].astype(np.float64), Xh[:, :B].astype(np.float64)
     err = np.abs(got - a @ x.T)
     assert (err <= bound(B, prec) * (np.abs(a) @ np.abs(x).T)).all()
+    # that bound holds for two parts as well: three are some ten times closer (2-norm)
+    rel = np.linalg.norm(got - a @ x.T) / np.linalg.norm(a @ x.T)
+    assert rel <= 8e-7 if prec == L1.F32 else rel <= 2e-5
+
+
+def test_packed_wgrad_takes_all_six_products():
+    # one batch index meets one: the entry is exact only with each of hi hi, hi mid, mid hi, mid
+    # mid, hi lo and lo hi
+    N, K, B = 130, 260, 322
+    hi, mid, lo = 1.0, 1 + 2.0 ** -9, 1 + 2.0 ** -9 + 2.0 ** -18  # of 1, 2 and 3 parts
+    dYh, Xh = np.zeros((N, B), np.float32), np.zeros((K, B), np.float32)
+    for b, a, x in [(3, hi, hi), (40, mid, hi), (70, hi, mid), (255, mid, mid), (256, lo, hi), (321, hi, lo)]:
+        dYh[b % N, b], Xh[b % K, b] = a, x
+    got = h(L1.dense_wgrad(t(dYh), t(Xh)))
+    assert np.array_equal(got, (dYh.astype(np.float64) @ Xh.astype(np.float64).T).astype(np.float32))
+    assert got[255 % N, 255 % K] == np.float32(mid * mid) and got[256 % N, 256 % K] == np.float32(lo)
 
 
 def test_packed_is_deterministic_and_needs_its_workspace():
