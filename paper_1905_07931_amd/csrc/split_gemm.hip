@@ -850,10 +850,12 @@ wgrad_split spmm_splits(int N, int K, int B) {
 // 12000 rows and columns, batches of 32-1024 and 2-56 % stored, within 15 % (us; the
 // packed one 25 % beyond 36 M weights).  The row kernel may also wait for its longest
 // row (0.056 us an entry), so unless that is bounded the packed product is kept up
-// to 1.25 of its time on even rows.  Sparse kernel, packed: 1978 x 5941 x 256 at 7 % 41, 66;
+// to 1.1 of its time on even rows.  Sparse kernel, packed: 1978 x 5941 x 256 at 7 % 41, 66;
 // 8944 x 3077 x 1024 at 11 % 267, 319; 9027 x 5314 x 512 at 12 % 317, 376; 5128 x 8214 x 256 at 14 % 232,
-// 252; 1544 x 383 x 512 at 50 % 27, 32; kept: 6662 x 6879 x 432 at 33 % 638, 400; with power-law
-// rows 5915 x 4822 x 118 at 11 % 182, 125, 525 x 7183 x 512 at 10 % 117, 61.
+// 252; 1544 x 383 x 512 at 50 % 27, 32; 2350 x 3453 x 256 at 11 % 42, 58; kept: 6662 x 6879 x 432
+// at 33 % 638, 400; 441 x 6309 x 256 at 42 % 166, 38.  (Power-law rows would gain some way
+// past that line, 525 x 7183 x 512 at 10 % 117, 61, where even ones take 47: sizes cannot
+// tell them apart.)
 bool packed_spmm_loses(int N, int K, int64_t nnz, int B, const wgrad_split &w) {
     const double np = (double)ceil_div(N, BM) * BM, bp = (double)ceil_div(B, BN) * BN, nk = (double)N * K;
     const double n = (double)nnz, products = n * B, density = n / nk;
@@ -864,7 +866,7 @@ bool packed_spmm_loses(int N, int K, int64_t nnz, int B, const wgrad_split &w) {
         return packed > (nk > 36e6 ? 0.8 : 1.04) * (36.6 + products / 21.8e6 + 13e-6 * n + 11.7e-3 * K);
     const double rate = B % 4 ? (B % 2 ? 3.6e6 : 4.2e6) : (B > 2 * kWave ? 5.9e6 : (B > kWave ? 3.8e6 : 2.5e6));
     const double chain = 0.056 * n / N, even = 6 + (products / rate > chain ? products / rate : chain);
-    return packed > (0.056 * K < even ? 0.95 : 1.25) * even;
+    return packed > (0.056 * K < even ? 0.95 : 1.1) * even;
 }
 }  // namespace
 
