@@ -463,16 +463,27 @@ int wave_vec(bool bwd, int B, int64_t lda, const void *a, int64_t ldb, const voi
     return 0;
 }
 
-// Backward, single floats against four a thread: a wave per position is four
-// times the waves of the other kernel, which pays where a channel's entries are
-// many (its index arithmetic) or the positions few (its waves).  Thread per output,
-// wave, us: 256 -> 64 channels, 14 x 14, 1 x 1 filters at 10 %, batch 48 19.0, 33.2, batch 64 22.9,
-// 33.4; 20 -> 16, 28 x 28, 1 x 1 at 5 %, batch 64 6.9, 10.6; 16 -> 32, 28 x 28, 2 x 2 at 10 %, batch 48
-// 12.7, 15.2; 64 -> 256, 14 x 14, 1 x 1 at 10 %, batch 64 22.8, 20.2; 20 -> 512, 7 x 7, 1 x 1 at
-// 10 %, batch 48 22.5, 7.5.  Strides are divisions in the other kernel.
-bool short_rows(const geom_t &g, int B, int64_t nnz) {
+// Backward, fewer floats a lane than the other kernel's four.  Single floats: a
+// wave per position is four times the waves of the other kernel, which pays
+// where a channel's entries are many (its index arithmetic) or the positions few
+// (its waves).  Thread per output, wave, us: 256 -> 64 channels, 14 x 14, 1 x 1
+// filters at 10 %, batch 48 19.0, 33.2, batch 64 22.9, 33.4; 20 -> 16, 28 x 28, 1 x 1 at
+// 5 %, batch 64 6.9, 10.6; 16 -> 32, 28 x 28, 2 x 2 at 10 %, batch 48 12.7, 15.2; 64 ->
+// 256, 14 x 14, 1 x 1 at 10 %, batch 64 22.8, 20.2; 20 -> 512, 7 x 7, 1 x 1 at 10 %,
+// batch 48 22.5, 7.5.  Strides are divisions in the other kernel.
+//
+// Pairs: twice the waves, so only where a twelfth of the lanes is idle, the grid
+// is full, the entries are fewer still and no stride divides (128 -> 64, 28 x 28, 1 x 1,
+// stride 2, batch 320 166, 145).  256 -> 64, 14 x 14, 1 x 1 at 5 %, batch 96 22.9,
+// 29.6, batch 300 60.5, 82.4; 20 -> 16, 28 x 28, 1 x 1 at 5 %, batch 112 10.1, 11.1, batch 300
+// 20.9, 27.8; 20 -> 6, 14 x 14, 1 x 1 at 10 %, batch 300 7.9, 8.9, batch 96 5.2, 4.4; 64 -> 256,
+// 14 x 14, 1 x 1 at 5 %, batch 100 17.6, 15.2; 64 -> 64 at 5 %, batch 128 10.4, 9.5.
+bool short_rows(const geom_t &g, int vec, int B, int64_t nnz) {
     const double entries = (double)nnz / (g.C > 0 ? g.C : 1), positions = (double)g.C * g.H * g.W;
-    return entries * (B >= kWave || g.SH > 1 || g.SW > 1 ? 1000 : 300) < positions;
+    const bool strided = g.SH > 1 || g.SW > 1;
+    if (vec == 1) return entries * (B >= kWave || strided ? 1000 : 300) < positions;
+    const bool idle = 12 * (int64_t)B <= 11 * ceil_div(B, kWave * vec) * kWave * vec;
+    return idle && !strided && positions * B > 600e3 && entries * 3000 < positions;
 }
 
 template <bool BWD>
@@ -548,7 +559,7 @@ hipError_t launch_conv_bwd_data(const conv_geom &cg, int N, int B, int64_t nnz, 
     (void)N;
     const bool v4 = vec4_ok(B, ldy, dY, ldx, dX);
     const int vec = wave_vec(true, B, ldy, dY, ldx, dX);
-    if (vec > 0 && !(vec == 1 && v4 && short_rows(g, B, nnz)))
+    if (vec > 0 && !(vec <= 2 && v4 && short_rows(g, vec, B, nnz)))
         return launch_wave<true>(vec, g, g.C, B, col_ptr, row_idx, vals_t, dY, ldy, dX, ldx, s);
     const int64_t sl = slices_of(F, v4 ? 4 : 1);
     if (sl > INT32_MAX || g.C > kMaxGridX) return hipErrorInvalidConfiguration;

@@ -111,10 +111,13 @@ def test_conv_wave_mapped_slices(geom, n, B):
 
 @pytest.mark.parametrize("geom,B,density", [((8, 40, 40, 1, 1, 1, 1, 0, 0), 48, 0.3), ((8, 40, 40, 1, 1, 1, 1, 0, 0), 64, 0.3),
                                             ((12, 40, 41, 1, 1, 2, 1, 0, 0), 64, 0.3), ((8, 13, 11, 2, 2, 1, 1, 1, 0), 48, 0.6),
-                                            ((8, 40, 40, 1, 1, 1, 1, 0, 0), 47, 0.3)])
+                                            ((8, 40, 40, 1, 1, 1, 1, 0, 0), 47, 0.3), ((8, 40, 40, 1, 1, 1, 1, 0, 0), 96, 0.3),
+                                            ((8, 40, 40, 1, 1, 1, 1, 0, 0), 116, 0.3), ((8, 40, 40, 1, 1, 1, 1, 0, 0), 336, 0.3),
+                                            ((12, 40, 41, 1, 1, 2, 1, 0, 0), 100, 0.3), ((8, 40, 40, 1, 1, 1, 1, 0, 0), 352, 0.2),
+                                            ((8, 40, 40, 1, 1, 1, 1, 0, 0), 98, 0.3)])
 def test_conv_backward_few_entries(geom, B, density):
-    # short batches with few entries a channel and many positions: a thread per output (four batch
-    # columns), beside sizes on the wave's side of the line and a batch that has no vectors
+    # batches that leave lanes idle, few entries a channel and many positions: a thread per output (four
+    # batch columns), beside sizes on the wave's side of the line and a batch that has no vectors
     g = L1.ConvGeom(*geom)
     n = 9
     rng = np.random.default_rng(B)
