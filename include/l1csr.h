@@ -124,10 +124,13 @@ int l1csr_host_free_mapped(void *host);
  * the kernel).  ws (nullable) enables the LDS-tiled kernel and must then hold
  * l1csr_workspace_bytes(L1CSR_OP_SPMM, n_rows, n_cols, nnz, B) bytes; without
  * it a row-per-wave kernel runs.  Summation order (fp32 fused multiply-adds):
- * the row-per-wave kernel sums each Y entry in ascending p order (rows of more
- * than 256 entries: four consecutive parts, each in ascending p order, added in
- * that order, for up to 32768 rows); the tiled
- * kernel sums a row in ascending p order too unless it cuts the row into k
+ * the row-per-wave kernel sums each Y entry in ascending p order; long rows in
+ * four consecutive parts, each in ascending p order, added in that order.  With
+ * mean = nnz / n_rows and cols = n_rows * (B up to the next multiple of 64), a
+ * row is long beyond L = max(256, 3 mean / 4) entries if cols is below 140000
+ * (110000 for mean < 340), else beyond L = max(256, 3 mean / 2); no row is if
+ * n_cols <= L, n_rows > 32768 or the launch has 2^24 workgroups or more.  The
+ * tiled kernel sums a row in ascending p order too unless it cuts the row into k
  * strided pieces (long rows: piece j takes p = row_ptr[i] + j, + j + k, ...),
  * each summed in ascending p order and the k partial sums then added in piece
  * order.  The order is fixed by the operands and by which of these workspaces
@@ -238,8 +241,8 @@ int csr_spmm_bwd_t(int32_t n_rows, int32_t n_cols, int64_t nnz,
  *   matrix cores, all exact, summed in fp32.  Per product the error is at most
  *   3 (1 + 2^-7) 2^-16 |ab| < 4.7e-5 |ab| (the dropped lo_a lo_b and the
  *   parts' rounding), so |dW - exact| <= 4.7e-5 sum_b |dY X| plus the fp32
- *   summation error: inside the 1e-4 contract, at about twice the speed of
- *   L1CSR_F32.
+ *   summation error: inside the 1e-4 contract, at about 1.5 times the speed
+ *   of L1CSR_F32.
  * Any other precision value returns L1CSR_EINVAL.
  * ws (nullable) with l1csr_workspace_bytes(L1CSR_OP_DENSE_WGRAD, N, K, 0, B)
  * bytes lets an fp32 product with few 128 x 128 output tiles and a long batch

@@ -23,10 +23,10 @@
 // its parts zero; a tile adds the products of its flagged blocks (both operands'
 // groups over those 256 indices) from the operands themselves, by the fp32
 // matrix-core instruction, or over a CSR operand entry by entry.  What that
-// costs, us per call for ordinary operands, one infinity in X and 2 % of X
+// costs, us per call for ordinary operands, one infinity in X, and 2 % of X
 // infinite (a flag on every block): forward product 4096 x 4096 x 512 at 20 %
-// 128 / 197 / 1450 (7000 and 8200 with whole tiles
-// left to a thread per column), gradient 102 / 115 / 215; gradient 4096 x 9216 x 1024 399 / 410 / 821.
+// 128, 197, 1450 (7000 and 8200 with whole tiles left to a thread per column),
+// masked gradient there 102, 115, 215; gradient 4096 x 9216 x 1024 399, 410, 821.
 //
 // What bounds it: the matrix pipe, and through it the power limit.  With every
 // CU's matrix pipe 71 % busy the shader clock falls to 1.64 GHz (2.38 GHz under

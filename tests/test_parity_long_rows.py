@@ -1,7 +1,8 @@
-"""GPU: the row kernel's long rows (more than 256 entries, taken by workgroups of
-their own) around that length, with more of them than one LDS list holds, among
-empty rows, past the row count that a workgroup scans, at batches on both sides of
-each vector width, against 64-bit references and run to run."""
+"""GPU: the row kernel's long rows (beyond 256 entries and a share of their layer's
+mean length, taken by workgroups of their own) around that length, with more of them
+than one LDS list holds, in every slice of the search, among empty rows, past the row
+count that is searched, at batches on both sides of each vector width, against 64-bit
+references and run to run."""
 import numpy as np
 import pytest
 
