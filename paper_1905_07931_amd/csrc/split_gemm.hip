@@ -728,10 +728,28 @@ size_t packed_size(size_t need, size_t plain) {
 // Rows that are 16-byte aligned let the other kernels load vectors, and outputs
 // that fill the chip once let them run without a last partial round (up to 512
 // tiles with two BF16X3 workgroups on a CU, 256 tiles with one of fp32): there the
-// batch has to be longer.  BF16X3 4096 x 2048 x 320 25.0 -> 29.4, x 512 34.4 -> 36.1, x 640
-// 41.3 -> 41.4 (3000 x 4000 x 320, 768 tiles, 43 -> 38; 1024 x 1024, 64 tiles, x 448 21.3 ->
-// 20.5); F32 500 x 8000 x 96 14.0 -> 15.9, x 160 19.4 -> 20.6, x 224 24.4 -> 24.6, 2048 x 2048 x 128
-// 16.7 -> 17.3.
+// batch has to be longer.  F32 500 x 8000 x 96 14.0 -> 15.9, x 160 19.4 -> 20.6, x 224
+// 24.4 -> 24.6, 2048 x 2048 x 128 16.7 -> 17.3.  BF16X3: x3_unpacked().
+namespace {
+// The line rises with the tiles to pack for, falls where the last tiles are partly
+// empty, which costs the other kernel more, and lies past 512 indices where
+// the packed product would be cut into two ranges there.  Other kernel -> packed,
+// us: 3072 x 2560 x 512 34.3 -> 36.5, x 608 41.0 -> 40.2; 4096 x 2048 x 320 25.6 -> 30.1; 2600 x 2600 x
+// 448 31.7 -> 33.3, x 576 39.9 -> 37.7; 2048 x 2048 x 384 21.5 -> 23.3, x 544 27.6 -> 28.0, x 640 31.4 ->
+// 30.1; 1024 x 3072 x 384 20.6 -> 21.7, x 512 25.1 -> 25.1; 1700 x 1700 x 320 20.2 -> 20.8, x 512
+// 28.7 -> 26.3; 800 x 2600 x 320 19.9 -> 18.8, x 512 28.2 -> 24.3; 1300 x 1300 x 448 26.2 -> 22.7;
+// 1024 x 2048 x 448 22.3 -> 21.9, x 512 24.2 -> 26.0, x 576 26.8 -> 26.9.  768 tiles, 3000 x 4000 x
+// 320: 41.5 -> 37.2.  Cards put it apart: 4000 x 2000 x 512 33.4 -> 35.6 on one, 37.3 ->
+// 37.2 on another.
+bool x3_unpacked(int N, int K, int B, int64_t tiles) {
+    if (B % 4 || tiles > 512) return false;
+    const bool whole = N % BM == 0 && K % BN == 0;
+    if (tiles > 256) return B < (whole ? 600 : 516);
+    if (tiles > 200) return B < (whole ? 540 : 416);
+    if (tiles > 128) return whole ? B < 450 : tiles > 160 && B < 384;
+    return whole && tiles > 112 && B >= 512 && B < 560;
+}
+}  // namespace
 size_t split_wgrad_bytes(int N, int K, int B, int precision) {
     const bool f32 = precision == kPrecF32;
     if ((!f32 && precision != kPrecBF16X3) || N == 0 || K == 0) return 0;
@@ -741,7 +759,7 @@ size_t split_wgrad_bytes(int N, int K, int B, int precision) {
         if (B < (nk >= 4e6 ? 96 : 160)) return 0;
         if (nk < 200 * rows && rows * B > 4e6) return 0;
         if (B % 4 == 0 && tiles > 192 && tiles <= 256 && B < 208) return 0;
-    } else if (B < 320 || (B % 4 == 0 && tiles > 75 && tiles <= 512 && B <= 512)) {
+    } else if (B < 320 || x3_unpacked(N, K, B, tiles)) {
         return 0;
     }
     if (B > (1 << 22)) return 0;  // 32-bit offsets inside a group
