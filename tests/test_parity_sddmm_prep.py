@@ -14,8 +14,18 @@ pytestmark = pytest.mark.gpu
                                    (17, 4096, 512), (4099, 2600, 516), (1024, 500, 8), (1025, 500, 8), (2048, 500, 8),
                                    (32768, 400, 4), (32769, 400, 4), (41000, 300, 4)])
 def test_row_pieces(N, K, B):
+    check(N, K, B, 0)
+
+
+@pytest.mark.parametrize("N,K,B", [(1025, 500, 8), (2048, 500, 8), (2049, 500, 12), (4095, 500, 8), (4096, 500, 8)])
+def test_row_pieces_up_to_4096_rows(N, K, B):
+    # beyond 16 entries a row a workgroup lists 1024 rows here too, and one lists all of them below
+    check(N, K, B, 16)
+
+
+def check(N, K, B, least):
     rng = np.random.default_rng(N)
-    n = rng.integers(0, 4, N)
+    n = rng.integers(least, least + 4, N)
     for i in (0, 1, 1023, 1024, 2047, 4095, 4096, 4097, 8191, 32767, 32768, N // 2, N - 1):
         if i < N:
             n[i] = K - i % 7
