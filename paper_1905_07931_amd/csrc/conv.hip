@@ -470,7 +470,9 @@ int wave_vec(bool bwd, int B, int64_t lda, const void *a, int64_t ldb, const voi
 // filters at 10 %, batch 48 19.0, 33.2, batch 64 22.9, 33.4; 20 -> 16, 28 x 28, 1 x 1 at
 // 5 %, batch 64 6.9, 10.6; 16 -> 32, 28 x 28, 2 x 2 at 10 %, batch 48 12.7, 15.2; 64 ->
 // 256, 14 x 14, 1 x 1 at 10 %, batch 64 22.8, 20.2; 20 -> 512, 7 x 7, 1 x 1 at 10 %,
-// batch 48 22.5, 7.5.  Strides are divisions in the other kernel.
+// batch 48 22.5, 7.5.  Strides are divisions in the other kernel.  And a small grid is
+// latency, of which the other kernel has more: 64 -> 128, 8 x 8, 1 x 1, stride 2, padding 2
+// at 3 %, batch 48 6.7, 4.4; 40 -> 16, 14 x 14, 1 x 1 at 5 %, batch 64 5.5, 6.2.
 //
 // Pairs: twice the waves, so only where a twelfth of the lanes is idle, the grid
 // is full, the entries are fewer still and no stride divides (128 -> 64, 28 x 28, 1 x 1,
@@ -481,9 +483,10 @@ int wave_vec(bool bwd, int B, int64_t lda, const void *a, int64_t ldb, const voi
 bool short_rows(const geom_t &g, int vec, int B, int64_t nnz) {
     const double entries = (double)nnz / (g.C > 0 ? g.C : 1), positions = (double)g.C * g.H * g.W;
     const bool strided = g.SH > 1 || g.SW > 1;
+    if (positions * B < (vec == 1 ? 350e3 : 500e3)) return false;
     if (vec == 1) return entries * (B >= kWave || strided ? 1000 : 300) < positions;
     const bool idle = 12 * (int64_t)B <= 11 * ceil_div(B, kWave * vec) * kWave * vec;
-    return idle && !strided && positions * B > 600e3 && entries * 3000 < positions;
+    return idle && !strided && entries * 3000 < positions;
 }
 
 template <bool BWD>
