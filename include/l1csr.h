@@ -127,9 +127,10 @@ int l1csr_host_free_mapped(void *host);
  * the row-per-wave kernel sums each Y entry in ascending p order; long rows in
  * four consecutive parts, each in ascending p order, added in that order.  With
  * mean = nnz / n_rows and cols = n_rows * (B up to the next multiple of 64), a
- * row is long beyond L = max(256, 3 mean / 4) entries if cols is below 140000
- * (110000 for mean < 340), else beyond L = max(256, 3 mean / 2); no row is if
- * n_cols <= L, n_rows > 32768 or the launch has 2^24 workgroups or more.  The
+ * row is long beyond L = max(256, n) entries, n = 3 mean / 4 if cols is below
+ * 140000 (110000 for mean < 340), 9 mean / 8 + 16 between these two and 3 mean / 2
+ * from 140000 on (integer arithmetic); none is if n_cols <= L, n_rows > 32768 or
+ * the launch has 2^24 workgroups or more.  The
  * tiled kernel sums a row in ascending p order too unless it cuts the row into k
  * strided pieces (long rows: piece j takes p = row_ptr[i] + j, + j + k, ...),
  * each summed in ascending p order and the k partial sums then added in piece

@@ -1334,17 +1334,20 @@ hipError_t exec_any(const spmm_plan &pl, int n_rows, int n_cols, const int *ptr,
 // products per us, the waves of a full grid reach 4.7 M.  So layers of few rows
 // (waves that hold columns for less than 0.056 us per entry and row: n_rows * columns
 // under 140,000, under 110,000 where the mean is below 340 entries) take all rows
-// near the mean length as long ones, others only those that outlast their layer's
+// near the mean length as long ones; between the two lines those past the
+// longest of a uniform layer; others only those that outlast their layer's
 // uniform row by half.  256 entries for all -> this rule, us: uniform 1733 x 3370 x
 // 224 at 10 % 65.8 -> 27.2, 1024 x 3000 x 256 at 12 % 41.8 -> 22.6, power-law rows 1000 x
 // 9000 x 200 at 4 % 162 -> 127, 4096 x 4096 x 32 at 13 % 145 -> 92; kept: uniform 512 x 4096 x
-// 128 18.3 (29.1 with one wave a row), 128 x 2000 x 64 at 50 % 14.8 (43.7).  140,000 for all
-// -> with the lower line: 900 x 4000 x 128 at 7 % 21.1 -> 17.0, 1063 x 3344 x 128 at 8 % 24.7 ->
-// 20.4 (one wave a row 21.8); 900 x 4000 x 128 at 10 % keeps 22.2 (22.8).
+// 128 18.3 (29.1 with one wave a row), 128 x 2000 x 64 at 50 % 14.8 (43.7).  Between the
+// lines, 3/4 of the mean, 3/2 of it, this: 900 x 4000 x 128 at 7 % 20.7, 17.0, 17.0 (power-law
+// 55, 46, 47), 1063 x 3344 x 128 at 8 % 24.9, 21.2, 21.9 (one wave a row 22.6), 450 x 1500 x 256
+// at 20 % 18.9, 18.2, 18.3 (power-law 23.9, 31.4, 27.3).
 int long_row(int64_t n_rows, int64_t nnz, int B) {
-    const int64_t mean = nnz / (n_rows > 0 ? n_rows : 1);
-    const bool few = n_rows * (ceil_div(B, kWave) * kWave) < (mean < 340 ? 110000 : 140000);
-    const int64_t n = few ? mean * 3 / 4 : mean * 3 / 2;
+    const int64_t mean = nnz / (n_rows > 0 ? n_rows : 1), held = n_rows * (ceil_div(B, kWave) * kWave);
+    const int64_t n = held < (mean < 340 ? 110000 : 140000) ? mean * 3 / 4
+                      : held < 140000                       ? mean * 9 / 8 + 16
+                                                            : mean * 3 / 2;
     return (int)(n < kLongRow ? kLongRow : (n < INT32_MAX ? n : INT32_MAX));
 }
 

@@ -72,6 +72,16 @@ def test_few_rows_around_their_mean():
     check([299, 300, 301, 257, 400, 480, 500, 460, 440, 463, 500, 400], 600, 40, 6)
 
 
+@pytest.mark.parametrize("N", [859, 860, 900, 1093, 1094])
+def test_rows_between_the_lines(N):
+    # N * 128 columns on both sides of 110,000 and 140,000, a mean of about 290: 9/8 of it and 16 between
+    rng = np.random.default_rng(N)
+    n = rng.integers(255, 300, N)
+    n[::29] = rng.integers(320, 360, len(n[::29]))
+    n[::97] = 700
+    check(n, 900, 128, N)
+
+
 @pytest.mark.parametrize("N", [2047, 2048, 2049, 2081, 8192, 8193, 8225, 20000, 32768])
 def test_long_rows_in_every_slice(N):
     # the rows are looked at in slices of 32 (of every 256 from 2049 rows, of every 512 from 8193):
