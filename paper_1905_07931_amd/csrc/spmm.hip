@@ -994,7 +994,11 @@ __device__ __forceinline__ void row_sum(int start, int end, const int *__restric
 // workgroups.  Uniform layers without the workgroups, all rows each, slices:
 // 20000 x 600 x 128 at 5 % 23.1, 28.9, 23.1; 8000 x 3000 x 100 at 1 % 11.3, 13.1, 11.0; 5688 x
 // 612 x 448 at 2 % 9.9, 11.1, 9.7; up to 2048 rows slices cost power-law layers more
-// (few items a slice: 1000 x 9000 x 200 163) than they save.  Eight waves per SIMD
+// (few items a slice: 1000 x 9000 x 200 163) than they save.  Past 256 columns a
+// long row is so many items that a slice with more of them than others lasts
+// longer: two slices up to 4096 rows, four up to 8192 (8, 2 or 4 slices: power-law
+// 2495 x 1869 x 833 at 2 % 55.8, 41.2; 4000 x 2000 x 333 at 3 % 56.0, 53.8; 6000 x 2000 x
+// 300 at 2 % 56.0, 53.6; uniform 3000 x 2000 x 1000 13.4, 13.4).  Eight waves per SIMD
 // have to fit: with 64 registers and more the uniform layers lose 10 %.
 constexpr int kRowsPerBlock = 4;
 constexpr int kLongRow = 256;
@@ -1367,11 +1371,14 @@ hipError_t launch_rows(int n_rows, int n_cols, int64_t nnz, const int *ptr, cons
     const bool room = nrb * nch + kLongBlocks < (int64_t)1 << 24;
     const int extra = n_cols > longest && n_rows <= kLongMaxRows && room ? kLongBlocks : 0;
     const unsigned grid = (unsigned)(nrb * nch) + extra;
+    const bool wide = B > 4 * kWave;  // (long_rows())
     auto launch = [&](auto v) {
         constexpr int VEC = decltype(v)::value;
         const auto kernel = extra == 0 ? spmm_rows_kernel<VEC, 0>
                             : n_rows <= kLongList ? spmm_rows_kernel<VEC, 1>
-                            : n_rows <= 4 * kLongList ? spmm_rows_kernel<VEC, 8> : spmm_rows_kernel<VEC, 16>;
+                            : n_rows <= 2 * kLongList && wide ? spmm_rows_kernel<VEC, 2>
+                            : n_rows <= 4 * kLongList ? (wide ? spmm_rows_kernel<VEC, 4> : spmm_rows_kernel<VEC, 8>)
+                                                      : spmm_rows_kernel<VEC, 16>;
         kernel<<<grid, 256, 0, s>>>(n_rows, ptr, idx, vals, X, ldx, B, Y, ldy, (int)nrb, longest);
     };
     if (vec == 4)

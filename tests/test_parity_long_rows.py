@@ -82,13 +82,15 @@ def test_rows_between_the_lines(N):
     check(n, 900, 128, N)
 
 
-@pytest.mark.parametrize("N", [2047, 2048, 2049, 2081, 8192, 8193, 8225, 20000, 32768])
-def test_long_rows_in_every_slice(N):
-    # the rows are looked at in slices of 32 (of every 256 from 2049 rows, of every 512 from 8193):
-    # long ones at the slices' edges, and in the last, partial, one
+@pytest.mark.parametrize("N,B", [(n, 5) for n in (2047, 2048, 2049, 2081, 8192, 8193, 8225, 20000, 32768)] +
+                         [(n, b) for n in (2049, 2081, 4095, 4096, 4097, 4129, 8192) for b in (257, 260)] + [(8193, 257)])
+def test_long_rows_in_every_slice(N, B):
+    # the rows are looked at in slices of 32 (of every 256 from 2049 rows, of every 512 from 8193; past 256
+    # columns of every 64 from 2049, of every 128 from 4097): long ones at the slices' edges, and in the
+    # last, partial, one
     n = np.zeros(N, np.int64)
     n[np.unique(np.concatenate([np.arange(0, N, 32 * 7), np.arange(31, N, 32 * 7), np.arange(224, N, 256),
                                 np.arange(480, N, 512), [N - 1, N - 2]]))] = 260
     n[::97] = 257
     n[5] = 256
-    check(n, 300, 5, N)
+    check(n, 300, B, N)
